@@ -10,7 +10,7 @@
 namespace esi {
 
 esi_status_t launch_step2d(Plan* P, unsigned flags, const StepArgs& a, int shape);
-int step2d_loop_shape(unsigned flags, int shape);
+int step2d_loop_shape(unsigned flags, int shape, int64_t fsize);
 void step2d_tile_shape(int* tx, int* tz);
 void step2d_shape_tile(int shape, int* tx, int* tz);
 esi_status_t launch_step3d(Plan* P, unsigned flags, const StepArgs& a);
@@ -46,7 +46,7 @@ esi_status_t launch_step(Plan* P, unsigned flags, const StepArgs& a, int shape) 
 // 3D: two steps per launch (LS_T2_32) for the variants the two-step kernel has
 int loop_shape(Plan* P, unsigned flags, bool adjoint) {
     const int want = adjoint ? P->tb_adj : P->tb_fwd;
-    if (P->ndim == 2) return step2d_loop_shape(flags, want);
+    if (P->ndim == 2) return step2d_loop_shape(flags, want, P->fsize);
     return want != LS_ONE && step3d_t2_has(flags) ? LS_T2_32 : LS_ONE;
 }
 

@@ -23,6 +23,8 @@
 //
 // Workgroup ids are remapped so that consecutive tiles land on the same XCD
 // (8 XCDs take workgroups round-robin), keeping halo neighbours in one L2.
+#include <type_traits>
+
 #include "esi_internal.h"
 
 namespace esi {
@@ -475,441 +477,557 @@ __global__ __launch_bounds__(256, ESI_MINW) void k_step2d(const StepArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Two steps, tA = a.step and tB = a.step + a.dir, in one launch, on 56 x 32
-// output tiles.  The first step runs on the tile grown by 4 cells, 64 x 40:
-// one lane per column (a wave spans it exactly), 10 rows per wave, z
-// neighbours from a register window.  The second step runs on the tile, one
-// lane per column (lanes 56..63 idle), 8 rows per wave.
-// The tile height TH (24, 32 or 40 rows) is a template parameter: the
-// autotuner's candidates.  Every height computes the same bits per cell.
+// Two steps, tA = a.step and tB = a.step + a.dir, in one launch, on 56 x TH
+// output tiles (TH a template parameter; every height computes the same bits
+// per cell).  The first step runs on the tile grown by 4 cells, 64 columns: a
+// wave spans it exactly, one lane per column.  Wave w owns the tile's rows
+// [w TH/4, (w+1) TH/4) and two of the eight rows of the ring above and below
+// them; the second step runs on the same lanes and rows (lanes 4..59), so c,
+// the new increment and the new field of a cell stay in registers between the
+// steps and only the field itself is exchanged, through LDS.
+//
+// The kernel is bound by instruction issue as much as by HBM: with a reload of
+// c and d between the steps and masks and addresses per row, the modelling
+// variant issued 1232 vector and 1169 scalar instructions a wave, 58 of its 60
+// us on 32 shots of 801 x 401, and few-tile launches waited for their surface
+// tiles, whose lanes walked up to 64 receivers one after another.  So what a row
+// costs beyond its arithmetic stays in scalar registers:
+//  * fields and dense vectors are buffers: a lane's column is a byte offset in
+//    one vector register for all rows, the row a scalar offset.  Columns off
+//    the grid, the window or the tile hold an offset past the buffer's end,
+//    which loads 0 and drops stores, so rows need no masks of their own;
+//  * rows off the padded grid read a row of the zero ghost frame instead;
+//  * tiles whose grown region lies in the physical window, away from the
+//    shot's source and receivers, run rows without damping (k = 0 there: the
+//    increment is fmaf(c, lq, d) exactly), injection or edge masks;
+//  * the z differences u_{+k} - u of a row serve as the negated u_{-k} - u of
+//    the row k below: (u_{+k} - u) + (u_{-k} - u) in one subtraction.
+//  * a thread reads the injection entry of its own index while the tile's loads
+//    fly and drops it into an LDS plane that is dead at the time.
+// Interior tiles of the modelling variant issue 725 vector and 427 scalar
+// instructions.  Microseconds per launch on 32-row tiles, before and now:
+// modelling 32 shots of 801 x 401, 60.1 and 41.4 (its state moved at 5.6 TB/s);
+// CG on 8 of them (forward pass, adjoint), 42.7 and 33.6, now 40.4 and 30.4; FWI
+// windows, 32 shots of 1601 x 601 (modelling, segment recompute, correlating
+// adjoint), 65.3, 95.8 and 110.4, now 51.1, 83.8 and 89.0; one shot of 201 x 201
+// (modelling, CG forward and adjoint averaged), 8.7 and 16.3, now 6.9 and 10.2.
 constexpr int T2W = 56;                           // output tile width
 constexpr int A_W = T2W + 2 * HALO;               // 64: first-step region width
 constexpr int U0W = T2W + 4 * HALO;               // 72
 static_assert(A_W == 64, "two-step tile geometry");
 
-// Occupancy targets: five waves per SIMD for the injecting (adjoint)
-// variants, whose registers and LDS allow it without spilling, and at least
-// four for the others (the flexible-CG direction update would otherwise take
-// 129 VGPRs and drop to three).
+// A global array as a raw buffer (base and size uniform over the wave).
+// Offset past the end of every buffer: loads return 0 and stores are dropped.
+// Buffers are below 2 GiB (launch2d's callers see to it), so adding a row's
+// scalar offset never wraps.
+constexpr uint32_t OOB = 0x80000000u;
+struct Buf {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Buf(const float* p, uint32_t bytes)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)bytes, 0x00027000)) {}
+    // element at byte offset v (per lane) + s (uniform)
+    __device__ __forceinline__ float ld(uint32_t v, uint32_t s) const {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)v, (int)s, 0));
+    }
+    __device__ __forceinline__ void st(float x, uint32_t v, uint32_t s) const {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, (int)v, (int)s, 0);
+    }
+};
+__device__ __forceinline__ uint32_t buf_bytes(int64_t floats) {
+    return (uint32_t)min<int64_t>(4 * floats, (int64_t)OOB);
+}
+
+// x part of the Laplacian at an LDS cell, as lap_lds forms it.  The address of
+// the leftmost neighbour is made opaque: from one base per row the eight loads
+// pair up with immediate offsets; left to itself the compiler forms a base per
+// pair (96 address additions of 777 vector instructions a wave).
+__device__ __forceinline__ float lap_x(const StepArgs& a, const float* p, float cv) {
+    typedef const __attribute__((address_space(3))) float lds_float;
+    lds_float* q = (lds_float*)(p - HALO);
+    asm("" : "+v"(q));
+    float lx = a.w1 * ((q[3] - cv) + (q[5] - cv));
+    lx = fmaf(a.w2, (q[2] - cv) + (q[6] - cv), lx);
+    lx = fmaf(a.w3, (q[1] - cv) + (q[7] - cv), lx);
+    return fmaf(a.w4, (q[0] - cv) + (q[8] - cv), lx);
+}
+
+// z part at rows 0, 1, ... of a column held in registers, in order: the
+// differences e_k(j) = col[j + k] - col[j] are formed once and serve the rows
+// j (as u_{+k} - u) and j + k (negated, as u_{-k} - u): the same bits as
+// lap_lds, since negation is exact.
+struct LapZ {
+    float e1, e2[2], e3[3], e4[4];
+    template <int N>
+    __device__ __forceinline__ explicit LapZ(const float (&col)[N]) {
+        e1 = col[4] - col[3];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) e2[j] = col[4 + j] - col[2 + j];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) e3[j] = col[4 + j] - col[1 + j];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) e4[j] = col[4 + j] - col[j];
+    }
+    template <int N>
+    __device__ __forceinline__ float row(const StepArgs& a, const float (&col)[N], int i) {
+        const float cv = col[i + 4];
+        const float n1 = col[i + 5] - cv, n2 = col[i + 6] - cv, n3 = col[i + 7] - cv, n4 = col[i + 8] - cv;
+        float lz = a.w1 * (n1 - e1);
+        lz = fmaf(a.w2, n2 - e2[0], lz);
+        lz = fmaf(a.w3, n3 - e3[0], lz);
+        lz = fmaf(a.w4, n4 - e4[0], lz);
+        e1 = n1;
+        e2[0] = e2[1]; e2[1] = n2;
+        e3[0] = e3[1]; e3[1] = e3[2]; e3[2] = n3;
+        e4[0] = e4[1]; e4[1] = e4[2]; e4[2] = e4[3]; e4[3] = n4;
+        return lz;
+    }
+};
+
+// Occupancy target, waves per SIMD: LDS (24 KB at 32 rows) would hold six
+// workgroups per CU, the registers of a variant decide.
 template <unsigned FL, int TH>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(((FL & F_INJ) != 0 && TH <= 32) ? 5 : 4)))
-void k_step2d_t2(const StepArgs a) {
+constexpr int t2_waves() { return (FL & F_INJ) != 0 && (FL & F_NORMAL) == 0 && TH <= 32 ? 5 : 4; }
+
+template <unsigned FL, int TH, bool GEN>
+__device__ __forceinline__ void step2d_t2_body(const StepArgs& a, int s, int t, const Aperture& ap, int ibeg, int iend,
+                                               int srow, int scol, float* __restrict__ U0, float* __restrict__ U1,
+                                               double& acc) {
     constexpr int T2Z = TH;                       // output tile rows
     constexpr int A_H = T2Z + 2 * HALO;           // first-step region rows
-    constexpr int A_RZ = A_H / 4;                 // first-step rows per wave
-    constexpr int B_RZ = T2Z / 4;                 // second-step rows per wave
+    constexpr int RZ2 = T2Z / 4;                  // tile rows per wave
+    constexpr int NR = RZ2 + 2;                   // rows per wave in the first step: tile rows, then two ring rows
     constexpr int U0H = T2Z + 4 * HALO;
-    static_assert(T2Z % 4 == 0 && A_H % 4 == 0 && U0H % 4 == 0, "two-step tile geometry");
-    // LDS (31 KB, five workgroups per CU): u^{tA} on the tile + 8 (dead after
-    // the first step, then holding the second step's injection), u after the
-    // first step on the tile + 4, d after the first step on the tile.  The
-    // first step's injection goes to registers.
-    __shared__ float U0[U0H * U0W];
-    __shared__ float U1[A_H * A_W];
-    __shared__ float D1[T2Z * T2W];
-    __shared__ double sred[4];
+    static_assert(T2Z % 4 == 0 && U0H % 4 == 0 && U0H <= 64, "two-step tile geometry");
     float* const sinjB = U0;
     static_assert(U0H * U0W >= A_H * A_W, "the second step's injection fits the u^{tA} buffer");
     // Gradient accumulators are read and written once per launch: both steps'
     // products are chained per cell in the second step, g = fmaf(B, fmaf(A, g))
-    // as two one-step launches would add them.  CORR takes the first step's
-    // field from U1 and reloads its stored (dA/dm)u there; PENALTY recomputes
-    // the first step's (dA/dm)u from u^{tA}, which U0 still holds (no
-    // injection reuses it in forward variants).  The DTFT source is not
-    // recomputed: that variant keeps one update per step.
-    constexpr bool CHAIN_CORR = (FL & F_CORR) != 0;
+    // as two one-step launches would add them (the DTFT source keeps one update
+    // per step).
+    constexpr bool CORR = (FL & F_CORR) != 0;
     constexpr bool CHAIN_PEN = (FL & F_PENALTY) != 0 && (FL & (F_DTFT_SRC | F_INJ)) == 0;
-    constexpr unsigned FL_A = FL & ~((CHAIN_CORR ? F_CORR : 0u) | (CHAIN_PEN ? F_PENALTY : 0u));
+    constexpr bool WB = (FL & (F_NORMAL | F_PENALTY | F_RUPD)) != 0;   // needs beta B^2
+    constexpr bool DENSE = (FL & (F_SRC_DENSE | F_DTFT_SRC | F_CG_FUSE)) != 0;
+    constexpr bool RUPD = (FL & F_RUPD) != 0, SCALE = (FL & F_SCALE) != 0;
 
-    int s, t;
-    work_item(a, xcd_remap(blockIdx.x, gridDim.x), &s, &t);
-    if (a.active && !a.active[s]) return;   // uniform over the workgroup
     const int gs = a.shot0 + s;
-    const Aperture ap = aperture(a, gs);
     const int tzi = t / a.tiles_x, txi = t - tzi * a.tiles_x;
     const int x0 = txi * T2W, z0 = tzi * T2Z;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index: uniform
-    const int XS = a.XS;
+    const uint32_t XB = 4u * (uint32_t)a.XS, NXB = 4u * (uint32_t)a.nx;   // row pitches in bytes
     const int tA = a.step, tB = a.step + a.dir;
-    const float* __restrict__ cur = a.cur + s * a.fstride;
-    float* __restrict__ nxt = a.nxt + s * a.fstride;
-    const float* __restrict__ din = a.din + s * a.fstride;
-    float* __restrict__ dnx = a.dnx + s * a.fstride;
+    const uint32_t fb = buf_bytes(a.fstride / RING), pb = buf_bytes(a.nphys);
+    const Buf cur(a.cur + s * a.fstride, fb), nxt(a.nxt + s * a.fstride, fb);
+    const Buf din(a.din + s * a.fstride, fb), dnx(a.dnx + s * a.fstride, fb);
+    const Buf c2(a.c2, fb);
     const int64_t vA = ((int64_t)s * a.nt + tA) * a.nphys;
     const int64_t vB = ((int64_t)s * a.nt + tB) * a.nphys;
-    const StepPtrs oA = step_ptrs(a, s, tA, vA, a.store_slot);
-    const StepPtrs oB = step_ptrs(a, s, tB, vB, a.store_slot2);
+    // byte offset of a padded row in a field; rows off the padded grid take a
+    // row of the zero ghost frame.  Byte offset of a physical row, and the mask
+    // that puts a row off the physical grid out of range.
+    auto zin = [&](int z) { return !GEN || (unsigned)z < (unsigned)a.nzp; };
+    auto zph = [&](int z) { return !GEN || (unsigned)(z - a.nb) < (unsigned)a.nz; };
+    auto frow = [&](int z) -> uint32_t { return zin(z) ? (uint32_t)(z + GH) * XB : 0u; };
+    auto prow = [&](int z) -> uint32_t { return zph(z) ? (uint32_t)(z - a.nb) * NXB : 0u; };
+    auto pmask = [&](int z) -> uint32_t { return zph(z) ? 0u : OOB; };
 
-    // U0 (r, c) <- padded (z0 - 8 + r, x0 - 8 + c) = storage (z0 + r, x0 + c).
-    // Cells off the padded grid sit in the zero ghost frame: they take 0
-    // without a load (the last tile column and row reach well into it).
-    constexpr int RPW0 = U0H / 4;
-    float tb[RPW0], th[RPW0];
+    // U0 (r, c) <- padded (z0 - 8 + r, x0 - 8 + c): 64 columns a row per wave,
+    // the other 8 of 32 rows at a time over the workgroup.
+    constexpr int RPW0 = U0H / 4, NHL = (U0H + 31) / 32;
+    float tb[RPW0], th[NHL];
+    const int hr = tid >> 3, hc = tid & 7;
     {
-        const float* src = cur + (z0 + GH - 2 * HALO + wv) * XS + x0 + GH - 2 * HALO;
-        const int xb = x0 - 2 * HALO + lane, xh = x0 - 2 * HALO + 64 + (lane & 7);
-        const bool xbin = xb >= 0 && xb < a.nxp, xhin = xh >= 0 && xh < a.nxp;
+        const int xb = x0 - 2 * HALO + lane;
+        const uint32_t vb = !GEN || (unsigned)xb < (unsigned)a.nxp ? 4u * (uint32_t)(xb + GH) : OOB;
 #pragma unroll
-        for (int k = 0; k < RPW0; ++k) {
-            const int z = z0 - 2 * HALO + wv + 4 * k;
-            const bool zin = z >= 0 && z < a.nzp;
-            tb[k] = (zin && xbin) ? at(src, (uint32_t)(k * 4 * XS) + (uint32_t)lane) : 0.f;
-            th[k] = (zin && xhin) ? at(src, (uint32_t)(k * 4 * XS + 64) + (uint32_t)(lane & 7)) : 0.f;
+        for (int k = 0; k < RPW0; ++k) tb[k] = cur.ld(vb, frow(z0 - 2 * HALO + wv + 4 * k));
+        const int xh = x0 - 2 * HALO + 64 + hc;
+#pragma unroll
+        for (int k = 0; k < NHL; ++k) {
+            const int z = z0 - 2 * HALO + hr + 32 * k;
+            const bool in = (!GEN || (xh < a.nxp && (unsigned)z < (unsigned)a.nzp)) && hr + 32 * k < U0H;
+            th[k] = cur.ld(in ? (uint32_t)(z + GH) * XB + 4u * (uint32_t)(xh + GH) : OOB, 0u);
         }
     }
 
-    // ---- first-step loads: lane = region column, rows wv*A_RZ + i of the region
-    const int xa = x0 - HALO + lane;                      // padded column
-    const bool xa_in = xa >= 0 && xa < a.nxp;
-    const float kxa = at(ap.kx, (uint32_t)min(max(xa, 0), a.nxp - 1));
-    const int ixa = xa - a.nb;
-    const bool xa_phys = ixa >= ap.lo && ixa < ap.hi;
-    const bool xa_win = xa >= ap.lo && xa < ap.hi + 2 * a.nb;
-    const bool xa_tile = lane >= HALO && lane < HALO + T2W;
-    const int zra = wv * A_RZ;                            // first region row of this wave
-    const uint32_t soA = (uint32_t)((z0 - HALO + zra + GH) * XS + xa + GH);
-    float cA[A_RZ], dA[A_RZ], kA[A_RZ], qA[A_RZ], pvA[A_RZ], stA[A_RZ], poA[A_RZ], xoA[A_RZ], rA[A_RZ];
-    uint32_t piA[A_RZ];
-    bool inA[A_RZ], phA[A_RZ], tlA[A_RZ];   // tlA: physical cell of the output tile
+    // ---- this lane's column and this wave's rows: row i of the first step is
+    // padded row zrow(i), region row rrow(i)
+    const int zt = z0 + wv * RZ2;                          // first tile row
+    const int rr0 = wv < 2 ? 2 * wv : T2Z + 2 * wv;        // first ring row, region coordinates
+    auto rrow = [&](int i) { return i < RZ2 ? wv * RZ2 + HALO + i : rr0 + i - RZ2; };
+    auto zrow = [&](int i) { return z0 - HALO + rrow(i); };
+    const int x = x0 - HALO + lane;                        // padded column
+    const int ix = x - a.nb;
+    const bool tile_lane = lane >= HALO && lane < HALO + T2W;
+    const bool xin = !GEN || (unsigned)x < (unsigned)a.nxp;
+    const bool xph = !GEN || (ix >= ap.lo && ix < ap.hi);
+    const bool xout = xph && tile_lane;                    // physical column of the tile
+    const float kxv = GEN ? at(ap.kx, (uint32_t)min(max(x, 0), a.nxp - 1)) : 0.f;
+    const uint32_t vf = xin ? 4u * (uint32_t)(x + GH) : OOB;                 // field column
+    const uint32_t vst = xin && tile_lane ? 4u * (uint32_t)(x + GH) : OOB;   // field column to store
+    const uint32_t vc = !GEN || (x >= ap.lo && x < ap.hi + 2 * a.nb) ? 4u * (uint32_t)(x + GH) : OOB;
+    const uint32_t vp = xph ? 4u * (uint32_t)ix : OOB;     // dense column
+    const uint32_t vo = xout ? 4u * (uint32_t)ix : OOB;    // dense column of the tile
+    float c[NR], d[NR], kz[GEN ? NR : 1], qA[NR], poA[NR], rA[NR], xoA[RZ2], pvA[RZ2];
 #pragma unroll
-    for (int i = 0; i < A_RZ; ++i) {
-        const int z = z0 - HALO + zra + i;
-        inA[i] = xa_in && z >= 0 && z < a.nzp;
-        cA[i] = xa_win ? at(a.c2, soA + (uint32_t)(i * XS)) : 0.f;
-        // (the injecting variants load the ghost frame's zeros: the test would
-        // cost them their fifth wave's registers)
-        if constexpr ((FL & F_INJ) != 0) dA[i] = at(din, soA + (uint32_t)(i * XS));
-        else dA[i] = inA[i] ? at(din, soA + (uint32_t)(i * XS)) : 0.f;
-        kA[i] = kxa + at(a.kz, (uint32_t)min(max(z, 0), a.nzp - 1));
-        const int iz = z - a.nb;
-        phA[i] = xa_phys && iz >= 0 && iz < a.nz;
-        piA[i] = phA[i] ? (uint32_t)(iz * a.nx + ixa) : 0u;
-        tlA[i] = phA[i] && xa_tile && zra + i >= HALO && zra + i < HALO + T2Z;
-        qA[i] = 0.f; pvA[i] = 0.f; stA[i] = 0.f; poA[i] = 0.f; xoA[i] = 0.f; rA[i] = 0.f;
+    for (int i = 0; i < NR; ++i) {
+        c[i] = c2.ld(vc, frow(zrow(i)));
+        d[i] = din.ld(vf, frow(zrow(i)));
+        if constexpr (GEN) kz[i] = at(a.kz, (uint32_t)min(max(zrow(i), 0), a.nzp - 1));
+        qA[i] = 0.f; poA[i] = 0.f; rA[i] = 0.f;
+        if (i < RZ2) { xoA[i] = 0.f; pvA[i] = 0.f; }
     }
-    // (values that only the output tile uses, x, p, r of N p and the stored
-    // (dA/dm)u, are loaded there alone: the grown region's ring is the
-    // neighbours' tiles)
+    // dense vectors of step t at rows i < N: values that only the output tile
+    // uses (x, p, r of N p) are not loaded on the ring, the neighbours' tiles
+    auto dense = [&](const float* base, uint32_t v, auto& out, int n) {
+        const Buf b(base, pb);
+#pragma unroll
+        for (int i = 0; i < n; ++i) out[i] = b.ld(v | pmask(zrow(i)), prow(zrow(i)));
+    };
     if constexpr ((FL & F_SRC_DENSE) != 0) {
-        const float* __restrict__ q = a.dsrc + blk_off(a, s, tA, vA);
+        dense(a.dsrc + blk_off(a, s, tA, vA), vp, qA, NR);
+        if constexpr (SCALE) {
+            float sc[NR];
+            dense(a.cg_s + (int64_t)s * a.nphys, vp, sc, NR);
 #pragma unroll
-        for (int i = 0; i < A_RZ; ++i) qA[i] = phA[i] ? at(q, piA[i]) : 0.f;
-        if constexpr ((FL & F_SCALE) != 0) {
-            const float* __restrict__ sc = a.cg_s + (int64_t)s * a.nphys;
-#pragma unroll
-            for (int i = 0; i < A_RZ; ++i) qA[i] = qA[i] * at(sc, piA[i]);
+            for (int i = 0; i < NR; ++i) qA[i] = qA[i] * sc[i];
         }
     }
-    if constexpr ((FL & F_DTFT_SRC) != 0) dtft_source<A_RZ>(a, s, tA, piA, phA, qA);
+    // dense-vector indices of rows i < N for the DTFT helpers
+    auto dtft_q = [&](int step, auto& q, auto n) {
+        constexpr int N = decltype(n)::value;
+        uint32_t pi[N];
+        bool ph[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            ph[i] = xph && zph(zrow(i));
+            pi[i] = ph[i] ? (uint32_t)((zrow(i) - a.nb) * a.nx + ix) : 0u;
+        }
+        dtft_source<N>(a, s, step, pi, ph, q);
+    };
+    if constexpr ((FL & F_DTFT_SRC) != 0) dtft_q(tA, qA, std::integral_constant<int, NR>{});
     float alp = 0.f, bet = 0.f;
     if constexpr ((FL & F_CG_FUSE) != 0) {
         alp = (float)a.cg_alpha[s];
         bet = (float)a.cg_beta[s];
-        const float* __restrict__ p = a.cg_p + vA;
-        const float* __restrict__ r = a.cg_r + vA;
-        const float* __restrict__ xv = a.cg_x + vA;
+        dense(a.cg_p + vA, vp, poA, NR);
+        dense(a.cg_r + vA, vp, qA, NR);
+        dense(a.cg_x + vA, vo, xoA, RZ2);
+        if constexpr (SCALE) {
+            float sc[NR];
+            dense(a.cg_s + (int64_t)s * a.nphys, vp, sc, NR);
 #pragma unroll
-        for (int i = 0; i < A_RZ; ++i) {
-            poA[i] = at(p, piA[i]);
-            qA[i] = at(r, piA[i]);
-            xoA[i] = tlA[i] ? at(xv, piA[i]) : 0.f;
-        }
-        if constexpr ((FL & F_SCALE) != 0) {
-            const float* __restrict__ sc = a.cg_s + (int64_t)s * a.nphys;
-#pragma unroll
-            for (int i = 0; i < A_RZ; ++i) { rA[i] = qA[i]; qA[i] = qA[i] * at(sc, piA[i]); }
+            for (int i = 0; i < NR; ++i) { rA[i] = qA[i]; qA[i] = qA[i] * sc[i]; }
         }
     }
     if constexpr ((FL & F_NORMAL) != 0) {
-        const float* __restrict__ p = a.dp + vA;
-#pragma unroll
-        for (int i = 0; i < A_RZ; ++i) pvA[i] = tlA[i] ? at(p, piA[i]) : 0.f;
-        if constexpr ((FL & F_RUPD) != 0) {   // r^tA into rA (no F_SCALE here)
-#pragma unroll
-            for (int i = 0; i < A_RZ; ++i) rA[i] = tlA[i] ? at(oA.r, piA[i]) : 0.f;
-        }
+        dense(a.dp + vA, vo, pvA, RZ2);
+        if constexpr (RUPD) dense(a.cg_rw + vA, vo, rA, RZ2);   // r^tA (no F_SCALE here)
     }
 
-#pragma unroll
-    for (int k = 0; k < RPW0; ++k) {
-        const int r = wv + k * 4;
-        U0[r * U0W + lane] = tb[k];
-        if (lane < 2 * HALO) U0[r * U0W + 64 + lane] = th[k];
-    }
-
+    // ---- the tile's receivers: this thread's entry (cell, values of both
+    // steps; more than 256 entries loop), read while the tile's loads fly
     const int64_t nrec_s = (FL & (F_INJ | F_GATHER)) ? a.rec_ptr[gs + 1] - a.rec_ptr[gs] : 0;
     const int64_t doff = (FL & (F_INJ | F_GATHER)) ? (int64_t)a.nt * (a.rec_ptr[gs] - a.rec_ptr[a.shot0]) : 0;
-    int ibeg = 0, iend = 0;
+    int gbeg = 0, gend = 0, icell = 0, gcell = 0, grid = 0;
+    float ivA = 0.f, ivB = 0.f;
+    // sum of the data of step `tt` over the receivers of injection entry e
+    auto inj_value = [&](int e, int tt) -> float {
+        const float* dj = a.inj_data + doff + (int64_t)tt * nrec_s;
+        float v = 0.f;
+        for (int k = a.inj2_rptr[e]; k < a.inj2_rptr[e + 1]; ++k) v += dj[a.inj2_rid[k]];
+        return v;
+    };
+    if constexpr (GEN && (FL & F_INJ) != 0) {
+        if (ibeg + tid < iend) {
+            icell = a.inj2_cell[ibeg + tid];
+            ivA = inj_value(ibeg + tid, tA);
+            ivB = inj_value(ibeg + tid, tB);
+        }
+    }
+    if constexpr ((FL & F_GATHER) != 0) {
+        const int32_t* gp = a.gat_ptr + (int64_t)gs * (a.tiles + 1);
+        gbeg = gp[t];
+        gend = gp[t + 1];
+        if (gbeg + tid < gend) {
+            gcell = a.gat_cell[gbeg + tid];
+            grid = a.gat_rid[gbeg + tid];
+        }
+    }
+    const bool has_inj = GEN && (FL & F_INJ) != 0 && iend > ibeg;   // uniform over the workgroup
+
+#pragma unroll
+    for (int k = 0; k < RPW0; ++k) U0[(wv + k * 4) * U0W + lane] = tb[k];
+#pragma unroll
+    for (int k = 0; k < NHL; ++k)
+        if (hr + 32 * k < U0H) U0[(hr + 32 * k) * U0W + 64 + hc] = th[k];
+    if (has_inj) {   // the first step's injection, in U1 until the step overwrites it cell by cell
+#pragma unroll
+        for (int i = 0; i < NR; ++i) U1[rrow(i) * A_W + lane] = 0.f;
+        __syncthreads();
+        if (ibeg + tid < iend) U1[icell] = ivA;
+        for (int e = ibeg + tid + 256; e < iend; e += 256) U1[a.inj2_cell[e]] = inj_value(e, tA);
+    }
+    __syncthreads();
+
+    // d^{step} = R u at the tile's receivers, from a plane whose tile starts at
+    // `from` with rows `pitch` apart
+    auto record = [&](int step, const float* from, int pitch) {
+        float* dn = a.gat_data + doff + (int64_t)step * nrec_s;
+        auto rec = [&](int cell, int rid) {
+            const int r = cell / T2W, cc = cell - r * T2W;
+            dn[rid] = from[r * pitch + cc];
+        };
+        if (gbeg + tid < gend) rec(gcell, grid);
+        for (int e = gbeg + tid + 256; e < gend; e += 256) rec(a.gat_cell[e], a.gat_rid[e]);
+    };
+    if constexpr ((FL & F_GATHER) != 0)
+        if (tA > 0) record(tA - 1, U0 + 2 * HALO * U0W + 2 * HALO, U0W);   // d^{tA-1} (forward only)
+
+    // beta B^2 at padded row z of this lane's column
+    float sx = 0.f, sz = 0.f;
+    if constexpr (WB) {
+        sx = (float)a.src_pos[gs * 3 + 0];
+        sz = (float)a.src_pos[gs * 3 + 1];
+    }
+    const float wx = ((float)ix - sx) * ((float)ix - sx);
+    auto weight = [&](int z) -> float {
+        if (a.w_identity) return a.beta;   // uniform over the launch
+        const float ddz = (float)(z - a.nb) - sz;
+        // the hardware square root (within 1 ulp; the argument is a sum of squared
+        // integers, never denormal) instead of the correctly rounded sequence
+        const float bb = __builtin_amdgcn_sqrtf(wx + ddz * ddz) + a.b_eps;
+        return a.beta * (bb * bb);
+    };
+    const StepPtrs oA = step_ptrs(a, s, tA, vA, a.store_slot);
+    const StepPtrs oB = step_ptrs(a, s, tB, vB, a.store_slot2);
+    // fused outputs of one step at tile row i: new field un, dense source q, lap
+    // + dx^2 q; stores of lanes or rows off the tile's physical cells are
+    // dropped (v, out of range), their sums masked
+    auto outputs = [&](const StepPtrs& o, int64_t vbase, int i, float un, float q, float lq, float po, float xo,
+                       float pv, float rv) {
+        const uint32_t v = vo | pmask(zrow(i)), so = prow(zrow(i));
+        const bool on = xout && zph(zrow(i));
+        const float wb = WB ? weight(zrow(i)) : 0.f;
+        if constexpr ((FL & F_CG_FUSE) != 0) {
+            Buf(a.cg_pn + vbase, pb).st(q, v, so);
+            if (alp != 0.f) Buf(a.cg_x + vbase, pb).st(fmaf(alp, po, xo), v, so);
+            if constexpr (SCALE) acc += (double)(on ? q : 0.f) * (double)rv;
+        }
+        if constexpr ((FL & F_OUT) != 0) Buf(o.dout, pb).st(un, v, so);
+        if constexpr ((FL & F_NORMAL) != 0) {
+            const float np = fmaf(wb, pv, un);
+            if constexpr (RUPD) {   // r -= alpha N p, as a separate pass would
+                const float rn = fmaf(-o.al, np, rv);
+                Buf(o.r, pb).st(rn, v, so);
+                const float rs = on ? rn : 0.f;
+                acc += (double)(rs * rs);
+            } else {
+                Buf(o.dout, pb).st(np, v, so);
+                acc += (double)pv * (double)(on ? np : 0.f);
+            }
+        }
+        if constexpr ((FL & (F_CG_FUSE | F_SRC_DENSE)) != 0 && RUPD) {
+            const float qs = on ? q : 0.f;
+            acc += (double)(qs * (wb * qs));   // beta B^2 p.p of the direction (dense source)
+        }
+        if constexpr ((FL & F_PENALTY) != 0) {
+            if constexpr (!CHAIN_PEN) {
+                const Buf g(o.gacc, pb);
+                g.st(fmaf(wb * q, c[i] * a.inv_dt2 * lq, g.ld(v, so)), v, so);
+            }
+            const float qs = on ? q : 0.f;
+            acc += (double)(wb * qs) * (double)qs;   // penalty term beta W q^2 (kept when a.part is set)
+        }
+        if constexpr ((FL & F_STORE) != 0) Buf(o.store, pb).st(c[i] * a.inv_dt2 * lq, v, so);
+    };
+    // one cell of a step: field cv, Laplacian, source (extended part qd) -> new
+    // increment into d[i], the new field returned, lap + dx^2 q in lq
+    auto cell = [&](int i, float cv, float lap, float q, float& lq) -> float {
+        lq = (DENSE || GEN) ? fmaf(a.dx2, q, lap) : lap;
+        d[i] = GEN ? incr(c[i], lq, d[i], kxv + kz[GEN ? i : 0]) : fmaf(c[i], lq, d[i]);
+        return cv + d[i];
+    };
+
+    // ---- first step: ring rows, then the tile's rows
+    float u[RZ2], lqA[CHAIN_PEN ? RZ2 : 1];
+    auto step_a = [&](auto first, auto count) {
+        constexpr int I0 = decltype(first)::value, N = decltype(count)::value;
+        float col[N + 2 * HALO];
+        const float* cp = U0 + rrow(I0) * U0W + lane + HALO;
+#pragma unroll
+        for (int k = 0; k < N + 2 * HALO; ++k) col[k] = cp[k * U0W];
+        LapZ lz(col);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int i = I0 + j;
+            const float cv = col[j + HALO];
+            const float lap = lap_x(a, cp + (j + HALO) * U0W, cv) + lz.row(a, col, j);
+            float q = qA[i];
+            if constexpr ((FL & F_CG_FUSE) != 0) q = fmaf(bet, poA[i], qA[i]);   // 0 off the physical grid
+            const float qd = q;   // the extended (dense) part of the source
+            if constexpr (GEN && (FL & F_SRC_POINT) != 0) {
+                if (rrow(i) == srow && lane == scol) q += a.wavelet[(int64_t)s * a.nt + tA];
+            }
+            if (has_inj) q += U1[rrow(i) * A_W + lane];
+            float lq;
+            const float un = cell(i, cv, lap, q, lq);
+            U1[rrow(i) * A_W + lane] = xin && zin(zrow(i)) ? un : 0.f;
+            if (i < RZ2) {
+                u[i] = xin && zin(zrow(i)) ? un : 0.f;
+                if constexpr (CHAIN_PEN) lqA[i] = lq;
+                if constexpr (GEN && (FL & F_SRC_REC) != 0) {
+                    if (rrow(i) == srow && lane == scol && tile_lane) a.src_rec[(int64_t)s * a.nt + tA] = un;
+                }
+                outputs(oA, vA, i, un, qd, lq, poA[i], xoA[i], pvA[i], rA[i]);
+            }
+        }
+    };
+    step_a(std::integral_constant<int, RZ2>{}, std::integral_constant<int, 2>{});
+    step_a(std::integral_constant<int, 0>{}, std::integral_constant<int, RZ2>{});
+
+    // the second step's dense loads fly over the barrier (no other thread of
+    // this launch writes what they read)
+    float qB[RZ2], pvB[RZ2], stB[RZ2], stA[RZ2], gv[RZ2], poB[RZ2], xoB[RZ2], rB[RZ2];
+#pragma unroll
+    for (int i = 0; i < RZ2; ++i) {
+        qB[i] = 0.f; pvB[i] = 0.f; stB[i] = 0.f; stA[i] = 0.f; gv[i] = 0.f; poB[i] = 0.f; xoB[i] = 0.f; rB[i] = 0.f;
+    }
+    if constexpr ((FL & F_SRC_DENSE) != 0) {
+        dense(a.dsrc + blk_off(a, s, tB, vB), vo, qB, RZ2);
+        if constexpr (SCALE) {
+            float sc[RZ2];
+            dense(a.cg_s + (int64_t)s * a.nphys, vo, sc, RZ2);
+#pragma unroll
+            for (int i = 0; i < RZ2; ++i) qB[i] = qB[i] * sc[i];
+        }
+    }
+    if constexpr ((FL & F_DTFT_SRC) != 0) dtft_q(tB, qB, std::integral_constant<int, RZ2>{});
+    if constexpr ((FL & F_CG_FUSE) != 0) {
+        dense(a.cg_p + vB, vo, poB, RZ2);
+        dense(a.cg_r + vB, vo, qB, RZ2);
+        dense(a.cg_x + vB, vo, xoB, RZ2);
+        if constexpr (SCALE) {
+            float sc[RZ2];
+            dense(a.cg_s + (int64_t)s * a.nphys, vo, sc, RZ2);
+#pragma unroll
+            for (int i = 0; i < RZ2; ++i) { rB[i] = qB[i]; qB[i] = qB[i] * sc[i]; }
+        }
+    }
+    if constexpr ((FL & F_NORMAL) != 0) {
+        dense(a.dp + vB, vo, pvB, RZ2);
+        if constexpr (RUPD) dense(a.cg_rw + vB, vo, rB, RZ2);   // r^tB (no F_SCALE here)
+    }
+    if constexpr (CORR) {
+        dense(oA.stin, vo, stA, RZ2);
+        dense(oB.stin, vo, stB, RZ2);
+    }
+    if constexpr (CORR || CHAIN_PEN) dense(oB.gacc, vo, gv, RZ2);
+    __syncthreads();
+
+    if constexpr ((FL & F_GATHER) != 0) record(tA, U1 + HALO * A_W + HALO, A_W);   // d^{tA} = R u^{tA+1}
+    if (has_inj) {   // U0 is dead since the barrier after the first step
+        for (int i = tid; i < A_H * A_W; i += 256) sinjB[i] = 0.f;
+        __syncthreads();
+        if (ibeg + tid < iend) sinjB[icell] = ivB;
+        for (int e = ibeg + tid + 256; e < iend; e += 256) sinjB[a.inj2_cell[e]] = inj_value(e, tB);
+        __syncthreads();
+    }
+
+    // ---- second step on the tile (the ring's lanes compute values that go nowhere)
+    float col[RZ2 + 2 * HALO];
+    const int lc = min(max(lane, HALO), A_W - HALO - 1);   // keeps the ring's lanes inside their row
+    const float* cp = U1 + (wv * RZ2) * A_W + lc;
+#pragma unroll
+    for (int k = 0; k < HALO; ++k) {
+        col[k] = cp[k * A_W];
+        col[RZ2 + HALO + k] = cp[(RZ2 + HALO + k) * A_W];
+    }
+#pragma unroll
+    for (int i = 0; i < RZ2; ++i) col[HALO + i] = u[i];
+    LapZ lz(col);
+#pragma unroll
+    for (int i = 0; i < RZ2; ++i) {
+        const float cv = u[i];
+        const float lap = lap_x(a, cp + (i + HALO) * A_W, cv) + lz.row(a, col, i);
+        float q = qB[i];
+        if constexpr ((FL & F_CG_FUSE) != 0) q = fmaf(bet, poB[i], qB[i]);   // 0 off the physical grid
+        const float qd = q;   // the extended (dense) part of the source
+        if constexpr (GEN && (FL & F_SRC_POINT) != 0) {
+            if (rrow(i) == srow && lane == scol) q += a.wavelet[(int64_t)s * a.nt + tB];
+        }
+        if (has_inj) q += sinjB[rrow(i) * A_W + lane];
+        float lq;
+        const float un = cell(i, cv, lap, q, lq);
+        // cells past the padded grid sit in the zero ghost frame (they would
+        // compute 0): not stored
+        if (zin(zrow(i))) {   // uniform
+            dnx.st(d[i], vst, frow(zrow(i)));
+            nxt.st(un, vst, frow(zrow(i)));
+        }
+        if constexpr ((FL & F_DTFT_ACC) != 0) {
+            if (xout && zph(zrow(i)))
+                dtft_accumulate(a, s, (uint32_t)((zrow(i) - a.nb) * a.nx + ix), tB, un, tA, cv);
+        }
+        if constexpr (GEN && (FL & F_SRC_REC) != 0) {
+            if (rrow(i) == srow && lane == scol && tile_lane) a.src_rec[(int64_t)s * a.nt + tB] = un;
+        }
+        outputs(oB, vB, i, un, qd, lq, poB[i], xoB[i], pvB[i], rB[i]);
+        if constexpr (CORR)
+            Buf(oB.gacc, pb).st(fmaf(un, stB[i], fmaf(cv, stA[i], gv[i])), vo | pmask(zrow(i)), prow(zrow(i)));
+        if constexpr (CHAIN_PEN) {
+            const float wb = weight(zrow(i));
+            const float gA = fmaf(wb * qA[i], c[i] * a.inv_dt2 * lqA[i], gv[i]);
+            Buf(oB.gacc, pb).st(fmaf(wb * qd, c[i] * a.inv_dt2 * lq, gA), vo | pmask(zrow(i)), prow(zrow(i)));
+        }
+    }
+}
+
+template <unsigned FL, int TH>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(t2_waves<FL, TH>())))
+void k_step2d_t2(const StepArgs a) {
+    // u^{tA} on the tile + 8 (dead after the first step, then holding the second
+    // step's injection), u after the first step on the tile + 4 (before that,
+    // in its place cell by cell, the first step's injection)
+    __shared__ float U0[(TH + 4 * HALO) * U0W];
+    __shared__ float U1[(TH + 2 * HALO) * A_W];
+    __shared__ double sred[4];
+    int s, t;
+    work_item(a, xcd_remap(blockIdx.x, gridDim.x), &s, &t);
+    s = __builtin_amdgcn_readfirstlane(s);
+    t = __builtin_amdgcn_readfirstlane(t);
+    if (a.active && !a.active[s]) return;   // uniform over the workgroup
+    const int gs = a.shot0 + s;
+    const Aperture ap = aperture(a, gs);
+    const int tzi = t / a.tiles_x, txi = t - tzi * a.tiles_x;
+    const int px = txi * T2W - HALO - a.nb, pz = tzi * TH - HALO - a.nb;   // the grown region's physical origin
+    int ibeg = 0, iend = 0, srow = -1, scol = -1;
     if constexpr ((FL & F_INJ) != 0) {
         const int32_t* ip = a.inj2_ptr + (int64_t)gs * (a.tiles + 1);
         ibeg = ip[t];
         iend = ip[t + 1];
     }
-    __syncthreads();
-
-    const int32_t* gp = (FL & F_GATHER) ? a.gat_ptr + (int64_t)gs * (a.tiles + 1) : nullptr;
-    if constexpr ((FL & F_GATHER) != 0) {
-        // d^{tA-1} = R u^{tA} (forward only)
-        if (tA > 0) {
-            float* dn = a.gat_data + doff + (int64_t)(tA - 1) * nrec_s;
-            for (int e = gp[t] + tid; e < gp[t + 1]; e += 256) {
-                const int cell = a.gat_cell[e];
-                const int r = cell / T2W, c = cell - r * T2W;
-                dn[a.gat_rid[e]] = U0[(r + 2 * HALO) * U0W + c + 2 * HALO];
-            }
-        }
+    if constexpr ((FL & (F_SRC_POINT | F_SRC_REC)) != 0) {   // the source cell in the grown region
+        const int gx = a.src_pos[gs * 3 + 0] - px, gz = a.src_pos[gs * 3 + 1] - pz;
+        if ((unsigned)gz < (unsigned)(TH + 2 * HALO) && (unsigned)gx < (unsigned)A_W) { srow = gz; scol = gx; }
     }
-
-    // the point source and the source-cell record
-    int srcA = -1, srcB = -1;
-    float sx = 0.f, sz = 0.f;
-    if constexpr ((FL & (F_SRC_POINT | F_SRC_REC | F_NORMAL | F_PENALTY | F_RUPD)) != 0) {
-        sx = (float)a.src_pos[gs * 3 + 0];
-        sz = (float)a.src_pos[gs * 3 + 1];
-        const int gz = a.src_pos[gs * 3 + 1] + a.nb - (z0 - HALO);
-        const int gx = a.src_pos[gs * 3 + 0] + a.nb - (x0 - HALO);
-        if (gz >= 0 && gz < A_H && gx >= 0 && gx < A_W) srcA = gz * A_W + gx;
-        const int lz = gz - HALO, lx = gx - HALO;
-        if (lz >= 0 && lz < T2Z && lx >= 0 && lx < T2W) srcB = lz * T2W + lx;
-    }
-
-    // the first step's injection straight into registers: every lane walks the
-    // tile's entries (uniform loads) and keeps those of its own column, so the
-    // injecting variants need no LDS plane for it
-    float injA[(FL & F_INJ) ? A_RZ : 1];
-    if constexpr ((FL & F_INJ) != 0) {
-#pragma unroll
-        for (int i = 0; i < A_RZ; ++i) injA[i] = 0.f;
-        if (iend > ibeg) {   // uniform over the workgroup
-            const float* dj = a.inj_data + doff + (int64_t)tA * nrec_s;
-            for (int e = ibeg; e < iend; ++e) {
-                const int cell = a.inj2_cell[e];
-                const int zr = cell / A_W, col = cell - zr * A_W;
-                float v = 0.f;
-                for (int k = a.inj2_rptr[e]; k < a.inj2_rptr[e + 1]; ++k) v += dj[a.inj2_rid[k]];
-                if (col == lane) {
-#pragma unroll
-                    for (int i = 0; i < A_RZ; ++i)
-                        if (zr == zra + i) injA[i] = v;
-                }
-            }
-        }
-    }
-
-    // ---- first step
-    float colA[A_RZ + 2 * HALO];
-#pragma unroll
-    for (int k = 0; k < A_RZ + 2 * HALO; ++k) colA[k] = U0[(zra + k) * U0W + lane + HALO];
+    // Interior tiles (uniform): the grown region is physical, and neither the
+    // source nor a receiver to inject lies in it; the staged region is then on
+    // the padded grid (nb >= 4).
+    const bool inner = px >= ap.lo && px + A_W <= ap.hi && pz >= 0 && pz + TH + 2 * HALO <= a.nz && iend == ibeg &&
+                       srow < 0;
     double acc = 0.0;
-#pragma unroll
-    for (int i = 0; i < A_RZ; ++i) {
-        const int zr = zra + i;
-        const float* cp = U0 + (zr + HALO) * U0W + lane + HALO;
-        const float lap = lap_lds(a, cp, U0W);
-        float q = qA[i];
-        if constexpr ((FL & F_CG_FUSE) != 0) q = phA[i] ? fmaf(bet, poA[i], qA[i]) : 0.f;
-        const float qd = q;   // the extended (dense) part of the source
-        if constexpr ((FL & F_SRC_POINT) != 0) {
-            if (zr * A_W + lane == srcA) q += a.wavelet[(int64_t)s * a.nt + tA];
-        }
-        if constexpr ((FL & F_INJ) != 0) {
-            if (iend > ibeg) q += injA[i];
-        }
-        const float lq = fmaf(a.dx2, q, lap);
-        const float dn = incr(cA[i], lq, dA[i], kA[i]);
-        const float un = colA[i + HALO] + dn;
-        U1[zr * A_W + lane] = inA[i] ? un : 0.f;
-        const bool tile = xa_tile && zr >= HALO && zr < HALO + T2Z;
-        if (tile) {
-            D1[(zr - HALO) * T2W + lane - HALO] = dn;
-            if (phA[i]) {
-                if constexpr ((FL & F_CG_FUSE) != 0) {
-                    at(a.cg_pn + vA, piA[i]) = qd;
-                    if (alp != 0.f) at(a.cg_x + vA, piA[i]) = fmaf(alp, poA[i], xoA[i]);
-                    if constexpr ((FL & F_SCALE) != 0) acc += (double)qd * (double)rA[i];
-                }
-                if constexpr ((FL & F_SRC_REC) != 0) {
-                    if (zr * A_W + lane == srcA) a.src_rec[(int64_t)s * a.nt + tA] = un;
-                }
-                float wb = 0.f;
-                if constexpr ((FL & (F_NORMAL | F_PENALTY | F_RUPD)) != 0)
-                    wb = annih_w(a, ixa, z0 - HALO + zr - a.nb, sx, sz);
-                cell_outputs<FL_A>(a, oA, piA[i], un, qd, lq, cA[i], pvA[i], stA[i], rA[i], wb, acc);
-                if constexpr (CHAIN_PEN) acc += (double)(wb * qd) * (double)qd;   // penalty term
-            }
-        }
-    }
-    __syncthreads();
-
-    if constexpr ((FL & F_GATHER) != 0) {
-        // d^{tA} = R u^{tA+1}
-        float* dn = a.gat_data + doff + (int64_t)tA * nrec_s;
-        for (int e = gp[t] + tid; e < gp[t + 1]; e += 256) {
-            const int cell = a.gat_cell[e];
-            const int r = cell / T2W, c = cell - r * T2W;
-            dn[a.gat_rid[e]] = U1[(r + HALO) * A_W + c + HALO];
-        }
-    }
-    if constexpr ((FL & F_INJ) != 0) {
-        if (iend > ibeg) {   // U0 is dead since the barrier after the first step
-            for (int i = tid; i < A_H * A_W; i += 256) sinjB[i] = 0.f;
-            __syncthreads();
-            const float* dj = a.inj_data + doff + (int64_t)tB * nrec_s;
-            for (int e = ibeg + tid; e < iend; e += 256) {
-                float v = 0.f;
-                for (int k = a.inj2_rptr[e]; k < a.inj2_rptr[e + 1]; ++k) v += dj[a.inj2_rid[k]];
-                sinjB[a.inj2_cell[e]] = v;
-            }
-            __syncthreads();
-        }
-    }
-
-    // ---- second step on the tile: lane = column (lanes >= 56 idle), 8 rows per wave
-    const int lc = min(lane, T2W - 1);
-    const bool lane_on = lane < T2W;
-    const int x = x0 + lc;
-    const float kxv = at(ap.kx, (uint32_t)min(x, a.nxp - 1));
-    const int ix = x - a.nb;
-    const bool xphys = lane_on && ix >= ap.lo && ix < ap.hi;
-    const bool xwin = x >= ap.lo && x < ap.hi + 2 * a.nb;
-    const int zb = z0 + wv * B_RZ;
-    const uint32_t so0 = (uint32_t)((zb + GH) * XS + x + GH);
-    float c2v[B_RZ], kzv[B_RZ], qv[B_RZ], pvB[B_RZ], stB[B_RZ], poB[B_RZ], xoB[B_RZ], rB[B_RZ];
-    uint32_t pi[B_RZ];
-    bool ph[B_RZ];
-#pragma unroll
-    for (int i = 0; i < B_RZ; ++i) {
-        const int z = zb + i;
-        c2v[i] = xwin ? at(a.c2, so0 + (uint32_t)(i * XS)) : 0.f;
-        kzv[i] = at(a.kz, (uint32_t)min(z, a.nzp - 1));
-        const int iz = z - a.nb;
-        ph[i] = xphys && iz >= 0 && iz < a.nz;
-        pi[i] = ph[i] ? (uint32_t)(iz * a.nx + ix) : 0u;
-        qv[i] = 0.f; pvB[i] = 0.f; stB[i] = 0.f; poB[i] = 0.f; xoB[i] = 0.f; rB[i] = 0.f;
-    }
-    if constexpr ((FL & F_SRC_DENSE) != 0) {
-        const float* __restrict__ q = a.dsrc + blk_off(a, s, tB, vB);
-#pragma unroll
-        for (int i = 0; i < B_RZ; ++i) qv[i] = ph[i] ? at(q, pi[i]) : 0.f;
-        if constexpr ((FL & F_SCALE) != 0) {
-            const float* __restrict__ sc = a.cg_s + (int64_t)s * a.nphys;
-#pragma unroll
-            for (int i = 0; i < B_RZ; ++i) qv[i] = qv[i] * at(sc, pi[i]);
-        }
-    }
-    if constexpr ((FL & F_DTFT_SRC) != 0) dtft_source<B_RZ>(a, s, tB, pi, ph, qv);
-    if constexpr ((FL & F_CG_FUSE) != 0) {
-        const float* __restrict__ p = a.cg_p + vB;
-        const float* __restrict__ r = a.cg_r + vB;
-        const float* __restrict__ xv = a.cg_x + vB;
-#pragma unroll
-        for (int i = 0; i < B_RZ; ++i) { poB[i] = at(p, pi[i]); qv[i] = at(r, pi[i]); xoB[i] = at(xv, pi[i]); }
-        if constexpr ((FL & F_SCALE) != 0) {
-            const float* __restrict__ sc = a.cg_s + (int64_t)s * a.nphys;
-#pragma unroll
-            for (int i = 0; i < B_RZ; ++i) { rB[i] = qv[i]; qv[i] = qv[i] * at(sc, pi[i]); }
-        }
-    }
-    if constexpr ((FL & F_NORMAL) != 0) {
-        const float* __restrict__ p = a.dp + vB;
-#pragma unroll
-        for (int i = 0; i < B_RZ; ++i) pvB[i] = at(p, pi[i]);
-        if constexpr ((FL & F_RUPD) != 0) {   // r^tB into rB (no F_SCALE here)
-#pragma unroll
-            for (int i = 0; i < B_RZ; ++i) rB[i] = at(oB.r, pi[i]);
-        }
-    }
-    if constexpr ((FL & F_CORR) != 0) {
-#pragma unroll
-        for (int i = 0; i < B_RZ; ++i) stB[i] = at(oB.stin, pi[i]);
-    }
-    // the first step's stored (dA/dm)u (CORR) or dense source (PENALTY) on the tile
-    // and the accumulator, read here so that its latency overlaps the stencil
-    // (in the variants with a dense output too it would spill: read in place)
-    constexpr bool G_EARLY = (CHAIN_CORR || CHAIN_PEN) && (FL & F_OUT) == 0;
-    float chA[(CHAIN_CORR || CHAIN_PEN) ? B_RZ : 1], gv[G_EARLY ? B_RZ : 1];
-    if constexpr (CHAIN_CORR) {
-#pragma unroll
-        for (int i = 0; i < B_RZ; ++i) chA[i] = at(oA.stin, pi[i]);
-    }
-    if constexpr (CHAIN_PEN) {
-        const float* __restrict__ q = a.dsrc + blk_off(a, s, tA, vA);
-#pragma unroll
-        for (int i = 0; i < B_RZ; ++i) chA[i] = ph[i] ? at(q, pi[i]) : 0.f;
-    }
-    if constexpr (G_EARLY) {
-#pragma unroll
-        for (int i = 0; i < B_RZ; ++i) gv[i] = at(oB.gacc, pi[i]);
-    }
-
-    float colB[B_RZ + 2 * HALO];
-#pragma unroll
-    for (int k = 0; k < B_RZ + 2 * HALO; ++k) colB[k] = U1[(wv * B_RZ + k) * A_W + lc + HALO];
-#pragma unroll
-    for (int i = 0; i < B_RZ; ++i) {
-        const int zl = wv * B_RZ + i;
-        const int z = z0 + zl;
-        const float* cp = U1 + (zl + HALO) * A_W + lc + HALO;
-        const float lap = lap_lds(a, cp, A_W);
-        float q = qv[i];
-        if constexpr ((FL & F_CG_FUSE) != 0) q = ph[i] ? fmaf(bet, poB[i], qv[i]) : 0.f;
-        const float qd = q;   // the extended (dense) part of the source
-        if constexpr ((FL & F_SRC_POINT) != 0) {
-            if (lane_on && zl * T2W + lc == srcB) q += a.wavelet[(int64_t)s * a.nt + tB];
-        }
-        if constexpr ((FL & F_INJ) != 0) {
-            if (iend > ibeg) q += sinjB[(zl + HALO) * A_W + lc + HALO];
-        }
-        const float kap = kxv + kzv[i];
-        const float lq = fmaf(a.dx2, q, lap);
-        const float dn = incr(c2v[i], lq, D1[zl * T2W + lc], kap);
-        const float un = colB[i + HALO] + dn;
-        // cells past the padded grid sit in the zero ghost frame (they would
-        // compute 0): not stored
-        if (lane_on && x < a.nxp && zb + i < a.nzp) {
-            at(dnx, so0 + (uint32_t)(i * XS)) = dn;
-            at(nxt, so0 + (uint32_t)(i * XS)) = un;
-        }
-        if (!ph[i]) continue;
-        if constexpr ((FL & F_DTFT_ACC) != 0)
-            dtft_accumulate(a, s, pi[i], tB, un, tA, U1[(zl + HALO) * A_W + lc + HALO]);
-        if constexpr ((FL & F_CG_FUSE) != 0) {
-            at(a.cg_pn + vB, pi[i]) = qd;
-            if (alp != 0.f) at(a.cg_x + vB, pi[i]) = fmaf(alp, poB[i], xoB[i]);
-            if constexpr ((FL & F_SCALE) != 0) acc += (double)qd * (double)rB[i];
-        }
-        if constexpr ((FL & F_SRC_REC) != 0) {
-            if (zl * T2W + lc == srcB) a.src_rec[(int64_t)s * a.nt + tB] = un;
-        }
-        float wb = 0.f;
-        if constexpr ((FL & (F_NORMAL | F_PENALTY | F_RUPD)) != 0) wb = annih_w(a, ix, z - a.nb, sx, sz);
-        cell_outputs<FL_A>(a, oB, pi[i], un, qd, lq, c2v[i], pvB[i], stB[i], rB[i], wb, acc);
-        if constexpr (CHAIN_CORR) {
-            const float uA = U1[(zl + HALO) * A_W + lc + HALO];
-            const float gA = fmaf(uA, chA[i], G_EARLY ? gv[G_EARLY ? i : 0] : at(oB.gacc, pi[i]));
-            at(oB.gacc, pi[i]) = fmaf(un, stB[i], gA);
-        }
-        if constexpr (CHAIN_PEN) {
-            // the first step's lap + dx^2 q at this cell, as that step formed it
-            float qa = chA[i];
-            if constexpr ((FL & F_SRC_POINT) != 0) {
-                if ((zl + HALO) * A_W + lc + HALO == srcA) qa += a.wavelet[(int64_t)s * a.nt + tA];
-            }
-            const float lapA = lap_lds(a, U0 + (zl + 2 * HALO) * U0W + lc + 2 * HALO, U0W);
-            const float lqA = fmaf(a.dx2, qa, lapA);
-            const float gA = fmaf(wb * chA[i], c2v[i] * a.inv_dt2 * lqA, G_EARLY ? gv[G_EARLY ? i : 0] : at(oB.gacc, pi[i]));
-            at(oB.gacc, pi[i]) = fmaf(wb * qd, c2v[i] * a.inv_dt2 * lq, gA);
-            acc += (double)(wb * qd) * (double)qd;   // penalty term (kept when a.part is set)
-        }
-    }
+    if (inner) step2d_t2_body<FL, TH, false>(a, s, t, ap, ibeg, iend, srow, scol, U0, U1, acc);
+    else step2d_t2_body<FL, TH, true>(a, s, t, ap, ibeg, iend, srow, scol, U0, U1, acc);
 
     if constexpr ((FL & (F_NORMAL | F_SCALE | F_PENALTY | F_RUPD)) != 0) {
         if (a.part) {   // uniform over the launch
+            const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
             acc = wave_sum(acc);
             if (lane == 0) sred[wv] = acc;
             __syncthreads();
-            if (tid == 0) {
+            if (threadIdx.x == 0) {
                 double sum = 0.0;
                 for (int w = 0; w < 4; ++w) sum += sred[w];
                 a.part[(int64_t)s * a.part_stride + t] += sum;
@@ -1040,14 +1158,21 @@ esi_status_t launch_step2d(Plan* P, unsigned flags, const StepArgs& a, int shape
     }
 }
 
-int step2d_loop_shape(unsigned flags, int shape) {
-    return (shape == LS_T2_24 || shape == LS_T2_40) && !tuned_variant(flags) ? LS_T2_32 : shape;
+int step2d_loop_shape(unsigned flags, int shape, int64_t fsize) {
+    // the two-step kernels address a field with signed 32-bit byte offsets
+    if (fsize >= (int64_t)1 << 29) return LS_ONE;
+    return shape != LS_ONE && !tuned_variant(flags) ? LS_T2_32 : shape;
 }
 
 void step2d_tile_shape(int* tx, int* tz) { *tx = TX; *tz = TZ; }
 void step2d_shape_tile(int shape, int* tx, int* tz) {
     *tx = shape == LS_ONE ? TX : T2W;
-    *tz = shape == LS_ONE ? TZ : shape == LS_T2_24 ? 24 : shape == LS_T2_40 ? 40 : 32;
+    switch (shape) {
+        case LS_ONE: *tz = TZ; break;
+        case LS_T2_24: *tz = 24; break;
+        case LS_T2_40: *tz = 40; break;
+        default: *tz = 32;
+    }
 }
 
 esi_status_t launch_final_gather(Plan* P, const float* field, int64_t fstride, float* data,
