@@ -49,7 +49,7 @@ TWO_STEP = 1 << 15
 RUPD = 1 << 14
 CORR = 1 << 9
 VARIANT_MASK = (1 << 15) - 1
-TILE_2D = {2: "56x32", 3: "56x24", 4: "56x40"}
+TILE_2D = {2: "56x32", 3: "56x24", 4: "56x40", 5: "56x16", 6: "56x8"}
 
 
 def launch_label(flags: int, ndim: int = 2) -> str:

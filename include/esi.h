@@ -503,8 +503,9 @@ esi_status_t esi_grad_velocity(esi_plan_t plan, const float* vel, const float* g
 /*
  * Time blocking of the 2D kernels: 2 (default) advances two time steps per
  * launch wherever a call allows it (the wavefield state then crosses HBM once
- * per two steps; launch shape ESI_LAUNCH_TWO_STEP_32), 1 advances one step per
- * launch (ESI_LAUNCH_ONE_STEP).  Results are identical bit for bit either way.
+ * per two steps; launch shape ESI_LAUNCH_TWO_STEP_32, or tiles of 24, 16 or 8
+ * rows in loops over so few tiles that 32-row ones would leave the GPU idle),
+ * 1 advances one step per launch (ESI_LAUNCH_ONE_STEP).  Results are identical bit for bit either way.
  * Returns ESI_ERR_ARG for other values.
  */
 esi_status_t esi_plan_set_time_block(esi_plan_t plan, int32_t steps);
@@ -521,7 +522,10 @@ esi_status_t esi_plan_set_time_block(esi_plan_t plan, int32_t steps);
  * Every shape gives the same wavefield, data, dense outputs and gradients bit
  * for bit; float64 dot products sum their per-tile partials over a different
  * tiling, so CG results agree to rounding.  Time-loop variants the shapes of
- * 24 and 40 rows do not cover run on 32-row tiles.
+ * 24 and 40 rows do not cover run on 32-row tiles.  A 2D plan whose two-step
+ * shape is its default or the autotuner's takes shorter tiles (24, 16 or 8
+ * rows) for loops too small to fill the GPU; a shape set by
+ * esi_plan_set_launch_shape is taken as it is.
  */
 enum { ESI_LAUNCH_ONE_STEP = 1, ESI_LAUNCH_TWO_STEP_32 = 2, ESI_LAUNCH_TWO_STEP_24 = 3,
        ESI_LAUNCH_TWO_STEP_40 = 4 };

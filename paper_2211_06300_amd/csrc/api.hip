@@ -42,11 +42,43 @@ esi_status_t launch_step(Plan* P, unsigned flags, const StepArgs& a, int shape) 
     return shape == LS_ONE ? launch_step3d(P, flags, a) : launch_step3d_t2(P, flags, a);
 }
 
+// Workgroups of a 2D launch over shots [shot0, shot0 + nshots) on tx x tz tiles.
+static int64_t launch_tiles(Plan* P, int tx, int tz, int shot0, int nshots) {
+    const int tiles_z = (P->nzp + tz - 1) / tz;
+    if (P->h_win.empty()) return (int64_t)nshots * tiles_z * ((P->nxp + tx - 1) / tx);
+    int64_t cols = 0;
+    for (int s = shot0; s < shot0 + nshots; ++s)   // tile columns that meet the window and its layer
+        cols += (P->h_win[2 * s + 1] + 2 * P->nb - 1) / tx - P->h_win[2 * s] / tx + 1;
+    return cols * tiles_z;
+}
+
 // 2D: the plan's shape (32-row tiles for variants without other heights);
-// 3D: two steps per launch (LS_T2_32) for the variants the two-step kernel has
-int loop_shape(Plan* P, unsigned flags, bool adjoint) {
-    const int want = adjoint ? P->tb_adj : P->tb_fwd;
-    if (P->ndim == 2) return step2d_loop_shape(flags, want, P->fsize);
+// 3D: two steps per launch (LS_T2_32) for the variants the two-step kernel has.
+//
+// A launch of few tiles lasts as long as one workgroup takes, four waves that
+// issue the instructions of their rows one after another: there two-step loops
+// take the shortest tiles that keep the launch within about four workgroups per
+// CU.  Microseconds per launch, CG (forward pass and adjoint, averaged) on
+// grids of 10 m cells, 32 / 24 / 16 / 8 rows:
+//   201 x 201, 1 shot:   10.15 /  9.11 /  7.96 /  6.91  (8 rows: 155 workgroups)
+//   401 x 201, 4 shots:  12.23 / 11.71 / 10.70 / 10.42  (992)
+//   401 x 201, 8 shots:  15.13 / 14.69 / 14.20 / 16.03  (16 rows: 1024)
+//   801 x 401, 2 shots:  15.09 / 14.49 / 13.98 / 15.10  (16 rows: 896)
+//   801 x 401, 4 shots:  21.41 / 21.01 / 21.67 / 23.96  (24 rows: 1216)
+// and 8 shots of 801 x 401 run fastest on 32 rows.
+int loop_shape(Plan* P, unsigned flags, bool adjoint, int shot0, int nshots) {
+    constexpr struct { int shape, most; } SMALL[] = {{LS_T2_8, 1024}, {LS_T2_16, 1024}, {LS_T2_24, 1280}};
+    int want = adjoint ? P->tb_adj : P->tb_fwd;
+    if (P->ndim == 2) {
+        if (want != LS_ONE && P->small_tiles) {
+            for (const auto& t : SMALL) {
+                int tx, tz;
+                step2d_shape_tile(t.shape, &tx, &tz);
+                if (launch_tiles(P, tx, tz, shot0, nshots) <= t.most) { want = t.shape; break; }
+            }
+        }
+        return step2d_loop_shape(flags, want, P->fsize);
+    }
     return want != LS_ONE && step3d_t2_has(flags) ? LS_T2_32 : LS_ONE;
 }
 
@@ -72,11 +104,11 @@ int max_tiles(Plan* P) {
 namespace {
 // Build the tilings of the time loops of `fflags` (forward) and `aflags`
 // (adjoint) before per-tile partials are sized by max_tiles.
-esi_status_t loop_lists(Plan* P, unsigned fflags, unsigned aflags) {
+esi_status_t loop_lists(Plan* P, unsigned fflags, unsigned aflags, int shot0, int ns) {
     TileLists* L;
     ESI_TRY(lists_for(P, &L));
-    ESI_TRY(shape_lists(P, loop_shape(P, fflags, false), &L));
-    return shape_lists(P, loop_shape(P, aflags, true), &L);
+    ESI_TRY(shape_lists(P, loop_shape(P, fflags, false, shot0, ns), &L));
+    return shape_lists(P, loop_shape(P, aflags, true, shot0, ns), &L);
 }
 }  // namespace
 
@@ -164,7 +196,7 @@ struct ProfScope {
 // and their launch shape in bits 16-18.
 esi_status_t forward_loop(Plan* P, StepArgs a, unsigned flags, float* ring, int* cs, int n0,
                           int n1, float* ckpt, int K, int nseg) {
-    const int shape = loop_shape(P, flags, false);
+    const int shape = loop_shape(P, flags, false, a.shot0, a.nshots);
     ProfScope p1(P, flags, a.nshots), p2(P, flags | (1u << 15) | ((unsigned)shape << 16), a.nshots);
     TileLists* L2 = nullptr;
     if (shape != LS_ONE) ESI_TRY(shape_lists(P, shape, &L2));
@@ -202,7 +234,7 @@ esi_status_t forward_loop(Plan* P, StepArgs a, unsigned flags, float* ring, int*
 // Adjoint time loop over j = j1-1 .. j0 on `ring` whose state is in slot *cs.
 esi_status_t adjoint_loop(Plan* P, StepArgs a, unsigned flags, float* ring, int* cs, int j0,
                           int j1, int K) {
-    const int shape = loop_shape(P, flags, true);
+    const int shape = loop_shape(P, flags, true, a.shot0, a.nshots);
     ProfScope p1(P, flags, a.nshots), p2(P, flags | (1u << 15) | ((unsigned)shape << 16), a.nshots);
     TileLists* L2 = nullptr;
     if (shape != LS_ONE) ESI_TRY(shape_lists(P, shape, &L2));
@@ -281,7 +313,7 @@ esi_status_t do_normal(Plan* P, int shot0, int ns, const float* p, float* Ap, co
     ESI_TRY(grow_t(&P->dscr, &P->dscr_cap, std::max<int64_t>(dl, 1), P->stream));
     ESI_TRY(ring_for(P, &P->ring, &P->ring_cap, ns));
     ESI_TRY(loop_lists(P, cg_fuse ? F_CG_FUSE | F_GATHER | (cg_s ? F_SCALE : 0u) : F_SRC_DENSE | F_GATHER,
-                       F_INJ | F_NORMAL));
+                       F_INJ | F_NORMAL, shot0, ns));
     P->part_stride = max_tiles(P);
     ESI_TRY(grow_t(&P->part, &P->part_cap, (int64_t)ns * P->part_stride, P->stream));
     StepArgs a = base_args(P, L, shot0, ns);
@@ -332,7 +364,8 @@ esi_status_t do_normal_rupd(Plan* P, int shot0, int ns, const float* p, float* p
     const int64_t dl = data_len(P, shot0, ns);
     ESI_TRY(grow_t(&P->dscr, &P->dscr_cap, std::max<int64_t>(dl, 1), P->stream));
     ESI_TRY(ring_for(P, &P->ring, &P->ring_cap, ns));
-    ESI_TRY(loop_lists(P, (first ? F_SRC_DENSE : F_CG_FUSE) | F_GATHER | F_RUPD, F_INJ | F_NORMAL | F_RUPD));
+    ESI_TRY(loop_lists(P, (first ? F_SRC_DENSE : F_CG_FUSE) | F_GATHER | F_RUPD, F_INJ | F_NORMAL | F_RUPD,
+                       shot0, ns));
     P->part_stride = max_tiles(P);
     ESI_TRY(grow_t(&P->part, &P->part_cap, (int64_t)ns * std::max(P->part_stride, DATA_BLOCKS), P->stream));
     ESI_TRY(launch_fill_d(P, P->part, (int64_t)ns * P->part_stride));
@@ -481,7 +514,7 @@ std::vector<uintptr_t> cg_graph_key(Plan* P, const CgState& c) {
     return {(uintptr_t)c.shot0, (uintptr_t)c.ns, (uintptr_t)c.max_iter,
             (uintptr_t)std::llround(c.rtol * 1e18), (uintptr_t)c.L, (uintptr_t)c.x,
             (uintptr_t)c.r, (uintptr_t)c.hist, (uintptr_t)P->ring, (uintptr_t)P->dscr,
-            (uintptr_t)P->part, (uintptr_t)(P->tb_fwd * 8 + P->tb_adj), (uintptr_t)P->part_stride,
+            (uintptr_t)P->part, (uintptr_t)((P->tb_fwd * 8 + P->tb_adj) * 2 + P->small_tiles), (uintptr_t)P->part_stride,
             (uintptr_t)P->w_identity, beta_bits(P->beta), (uintptr_t)P->cg_rfuse};
 }
 
@@ -1037,7 +1070,7 @@ esi_status_t penalty_eval(Plan* P, int shot0, int ns, const float* q, const floa
     TileLists* L;
     ESI_TRY(lists_for(P, &L));
     const unsigned pfl = F_SRC_DENSE | F_PENALTY | F_GATHER | (bg ? F_SRC_POINT : 0u);
-    ESI_TRY(loop_lists(P, pfl, F_INJ));
+    ESI_TRY(loop_lists(P, pfl, F_INJ, shot0, ns));
     P->part_stride = max_tiles(P);
     ESI_TRY(grow_t(&P->part, &P->part_cap, (int64_t)ns * P->part_stride, P->stream));
     ESI_TRY(launch_fill_d(P, P->part, (int64_t)ns * P->part_stride));
@@ -1153,6 +1186,7 @@ extern "C" esi_status_t esi_plan_set_time_block(esi_plan_t plan, int32_t steps) 
     if (!plan) return fail(ESI_ERR_ARG, "null plan");
     if (steps != 1 && steps != 2) return fail(ESI_ERR_ARG, "time block must be 1 or 2");
     ((Plan*)plan)->tb_fwd = ((Plan*)plan)->tb_adj = steps == 1 ? LS_ONE : LS_T2_32;
+    ((Plan*)plan)->small_tiles = true;
     return ESI_OK;
 }
 
@@ -1237,6 +1271,7 @@ extern "C" esi_status_t esi_plan_autotune(esi_plan_t plan, int32_t shot0, int32_
             if (e.key == key) {
                 P->tb_fwd = e.fwd;
                 P->tb_adj = e.adj;
+                P->small_tiles = true;
                 P->tune_rows = e.rows;
                 if (choice) { choice[0] = e.fwd; choice[1] = e.adj; }
                 return ESI_OK;
@@ -1261,6 +1296,8 @@ extern "C" esi_status_t esi_plan_autotune(esi_plan_t plan, int32_t shot0, int32_
     pend.swap(P->prof_pending);
     tot.swap(P->prof_tot);
     const int tf0 = P->tb_fwd, ta0 = P->tb_adj;
+    const bool small0 = P->small_tiles;
+    P->small_tiles = false;   // each candidate as it is
     double best_f = 1e300, best_a = 1e300;
     int sf = LS_T2_32, sa = LS_T2_32;
     esi_status_t st = ESI_OK;
@@ -1291,10 +1328,12 @@ extern "C" esi_status_t esi_plan_autotune(esi_plan_t plan, int32_t shot0, int32_
     if (st != ESI_OK) {
         P->tb_fwd = tf0;
         P->tb_adj = ta0;
+        P->small_tiles = small0;
         return st;
     }
     P->tb_fwd = sf;
     P->tb_adj = sa;
+    P->small_tiles = true;
     P->tune_rows = rows;
     g_tune_cache.push_back({key, sf, sa, rows});
     if (choice) { choice[0] = sf; choice[1] = sa; }
@@ -1326,6 +1365,7 @@ extern "C" esi_status_t esi_plan_set_launch_shape(esi_plan_t plan, int32_t forwa
         return fail(ESI_ERR_ARG, "3D plans run shape 1 (one step per launch) or 2 (two steps)");
     P->tb_fwd = forward;
     P->tb_adj = adjoint;
+    P->small_tiles = false;
     return ESI_OK;
 }
 

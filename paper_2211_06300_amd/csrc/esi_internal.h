@@ -19,9 +19,10 @@ constexpr int XCDS = 8;          // MI355X: 8 accelerator complex dies, 32 CUs e
 
 // Launch shapes of 2D time loops (the autotuner's candidates): one step per
 // launch on 64 x 32 tiles, or two steps per launch on 56-column tiles of 32,
-// 24 or 40 rows.  3D loops use LS_ONE.
-enum : int { LS_ONE = 1, LS_T2_32 = 2, LS_T2_24 = 3, LS_T2_40 = 4 };
-constexpr int LS_COUNT = 4;
+// 24 or 40 rows.  3D loops use LS_ONE.  The 16- and 8-row tiles are the plan's
+// own choice, for launches too small to fill the GPU (loop_shape).
+enum : int { LS_ONE = 1, LS_T2_32 = 2, LS_T2_24 = 3, LS_T2_40 = 4, LS_T2_16 = 5, LS_T2_8 = 6 };
+constexpr int LS_COUNT = 4;      // shapes that callers can name
 
 
 // Thread-local error text.
@@ -72,6 +73,7 @@ struct TileLists {
     // window plus its absorbing layer, shot-major; work_ptr[gs] indexes it
     int32_t* work = nullptr;
     std::vector<int64_t> work_ptr;
+    int32_t* blob = nullptr;             // the device array all of the lists above live in
 };
 
 struct Plan {
@@ -171,6 +173,7 @@ struct Plan {
 
     std::vector<TileLists*> lists;       // one per tile shape used
     int tb_fwd = LS_T2_32, tb_adj = LS_T2_32;   // launch shape of forward / adjoint loops (2D)
+    bool small_tiles = true;             // two-step loops too small for the GPU take shorter tiles (2D)
     // the autotuner's last candidate table: shape, forward ms, adjoint ms
     struct TuneRow { int shape; double fwd_ms, adj_ms; };
     std::vector<TuneRow> tune_rows;
@@ -374,9 +377,10 @@ constexpr int RING = 4;
 // time-loop plumbing of the entry points (api.hip)
 esi_status_t check_shots(Plan* P, int shot0, int nshots);
 esi_status_t lists_for(Plan* P, TileLists** L);
-// launch shape a loop of `flags` runs with (the plan's choice, or 32-row
-// two-step tiles for variants without other heights), and its tiling
-int loop_shape(Plan* P, unsigned flags, bool adjoint);
+// launch shape a loop of `flags` over `nshots` shots runs with (the plan's
+// choice, shorter tiles where those fill the GPU better, or 32-row two-step
+// tiles for variants without other heights), and its tiling
+int loop_shape(Plan* P, unsigned flags, bool adjoint, int shot0, int nshots);
 esi_status_t shape_lists(Plan* P, int shape, TileLists** L);
 void shape_tile(Plan* P, int shape, int* tx, int* ty, int* tz);
 // the largest tile count of the plan's tilings (stride of per-tile partials)

@@ -287,29 +287,9 @@ esi_status_t get_lists(Plan* P, int tx, int tz, int ty, TileLists** out) {
         const int32_t* ps = &P->h_src[(size_t)s * nd];
         locate(ps[0] + P->nb, ps[1] + P->nb, nd == 3 ? ps[2] + P->nb : 0, &src_tile[s], &src_cell[s]);
     }
-    auto up = [&](std::vector<int32_t>& h, int32_t** d) -> esi_status_t {
-        size_t n = std::max<size_t>(h.size(), 1);
-        ESI_HIP_TRY(hipMalloc(d, n * sizeof(int32_t)));
-        if (!h.empty())
-            ESI_HIP_TRY(hipMemcpy(*d, h.data(), h.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-        return ESI_OK;
-    };
-    ESI_TRY(up(inj_ptr, &L->inj_ptr));
-    ESI_TRY(up(inj_cell, &L->inj_cell));
-    ESI_TRY(up(inj_rptr, &L->inj_rptr));
-    ESI_TRY(up(inj_rid, &L->inj_rid));
-    ESI_TRY(up(gat_ptr, &L->gat_ptr));
-    ESI_TRY(up(gat_cell, &L->gat_cell));
-    ESI_TRY(up(gat_rid, &L->gat_rid));
-    ESI_TRY(up(src_tile, &L->src_tile));
-    ESI_TRY(up(src_cell, &L->src_cell));
-    ESI_TRY(up(inj2_ptr, &L->inj2_ptr));
-    ESI_TRY(up(inj2_cell, &L->inj2_cell));
-    ESI_TRY(up(inj2_rptr, &L->inj2_rptr));
-    ESI_TRY(up(inj2_rid, &L->inj2_rid));
+    std::vector<int32_t> work;
     if (!P->h_win.empty()) {
         // the (shot, tile) items whose tile columns meet the shot's window plus layer
-        std::vector<int32_t> work;
         L->work_ptr.assign(P->nshots + 1, 0);
         for (int s = 0; s < P->nshots; ++s) {
             const int lo = P->h_win[2 * s], hi = P->h_win[2 * s + 1] + 2 * P->nb;   // padded [lo, hi)
@@ -320,7 +300,37 @@ esi_status_t get_lists(Plan* P, int tx, int tz, int ty, TileLists** out) {
             }
             L->work_ptr[s + 1] = (int64_t)work.size();
         }
-        ESI_TRY(up(work, &L->work));
+    }
+    // one device array holds all lists, each starting on a 256-byte boundary
+    struct Part { const std::vector<int32_t>* h; int32_t** d; };
+    std::vector<Part> parts = {{&inj_ptr, &L->inj_ptr}, {&inj_cell, &L->inj_cell}, {&inj_rptr, &L->inj_rptr},
+                               {&inj_rid, &L->inj_rid}, {&gat_ptr, &L->gat_ptr}, {&gat_cell, &L->gat_cell},
+                               {&gat_rid, &L->gat_rid}, {&src_tile, &L->src_tile}, {&src_cell, &L->src_cell},
+                               {&inj2_ptr, &L->inj2_ptr}, {&inj2_cell, &L->inj2_cell}, {&inj2_rptr, &L->inj2_rptr},
+                               {&inj2_rid, &L->inj2_rid}};
+    if (!P->h_win.empty()) parts.push_back({&work, &L->work});
+    size_t total = 0;
+    for (const Part& q : parts) total += (q.h->size() + 64) / 64 * 64;   // at least one element's room each
+    std::vector<int32_t> all(total, 0);
+    size_t at = 0;
+    for (const Part& q : parts) {
+        std::copy(q.h->begin(), q.h->end(), all.begin() + at);
+        at += (q.h->size() + 64) / 64 * 64;
+    }
+    if (hipMalloc(&L->blob, total * sizeof(int32_t)) != hipSuccess) {
+        delete L;
+        return fail(ESI_ERR_OOM, "hipMalloc of the tile lists failed");
+    }
+    const hipError_t ce = hipMemcpy(L->blob, all.data(), total * sizeof(int32_t), hipMemcpyHostToDevice);
+    if (ce != hipSuccess) {
+        hipFree(L->blob);
+        delete L;
+        return fail(ESI_ERR_HIP, std::string("tile lists: ") + hipGetErrorString(ce));
+    }
+    at = 0;
+    for (const Part& q : parts) {
+        *q.d = L->blob + at;
+        at += (q.h->size() + 64) / 64 * 64;
     }
     P->lists.push_back(L);
     *out = L;
@@ -328,11 +338,7 @@ esi_status_t get_lists(Plan* P, int tx, int tz, int ty, TileLists** out) {
 }
 
 static void free_lists(TileLists* L) {
-    hipFree(L->inj_ptr); hipFree(L->inj_cell); hipFree(L->inj_rptr); hipFree(L->inj_rid);
-    hipFree(L->gat_ptr); hipFree(L->gat_cell); hipFree(L->gat_rid);
-    hipFree(L->src_tile); hipFree(L->src_cell);
-    hipFree(L->inj2_ptr); hipFree(L->inj2_cell); hipFree(L->inj2_rptr); hipFree(L->inj2_rid);
-    if (L->work) hipFree(L->work);
+    hipFree(L->blob);
     delete L;
 }
 
@@ -478,7 +484,7 @@ extern "C" esi_status_t esi_plan_create(esi_plan_t* plan, const esi_grid_t* g, c
     {
         TileLists* L = nullptr;
         st = lists_for(P, &L);
-        if (st == ESI_OK) st = shape_lists(P, loop_shape(P, F_SRC_POINT | F_GATHER, false), &L);
+        if (st == ESI_OK) st = shape_lists(P, loop_shape(P, F_SRC_POINT | F_GATHER, false, 0, P->nshots), &L);
         if (st != ESI_OK) return cleanup(st);
     }
     noalloc_init_device(P->device);

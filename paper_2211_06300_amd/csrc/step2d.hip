@@ -1154,6 +1154,8 @@ esi_status_t launch_step2d(Plan* P, unsigned flags, const StepArgs& a, int shape
         case LS_T2_32: return dispatch2d<32>(P, flags, a);
         case LS_T2_24: return dispatch2d_tuned<24>(P, flags, a);
         case LS_T2_40: return dispatch2d_tuned<40>(P, flags, a);
+        case LS_T2_16: return dispatch2d_tuned<16>(P, flags, a);
+        case LS_T2_8: return dispatch2d_tuned<8>(P, flags, a);
         default: return fail(ESI_ERR_ARG, "internal: launch shape " + std::to_string(shape));
     }
 }
@@ -1171,6 +1173,8 @@ void step2d_shape_tile(int shape, int* tx, int* tz) {
         case LS_ONE: *tz = TZ; break;
         case LS_T2_24: *tz = 24; break;
         case LS_T2_40: *tz = 40; break;
+        case LS_T2_16: *tz = 16; break;
+        case LS_T2_8: *tz = 8; break;
         default: *tz = 32;
     }
 }

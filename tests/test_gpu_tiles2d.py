@@ -17,7 +17,9 @@ DEV = "cuda:0"
 # eight-row tiles (6.5 of 16, 4.3 of 24, 3.25 of 32, 2.6 of 40), and a grid of
 # one ragged tile column
 GRIDS = [(152, 88, 8), (153, 89, 8), (37, 70, 4)]
-SHAPES = [("set", 2), ("set", 3), ("set", 4)]
+# shapes callers can set, and the plan's own choice: 8-row tiles for few
+# shots, 16-row tiles for 60
+SHAPES = [("set", 2), ("set", 3), ("set", 4), ("few", 2), ("many", 2)]
 
 
 @pytest.fixture(scope="module")
