@@ -20,11 +20,12 @@
 // data gradient is the same kernel with taps reversed and weights transposed.
 // Transposed convolutions use the same instruction with operands loaded
 // straight from memory (each input pixel is read once); their data gradient
-// and the weight gradients use v_mfma_f32_16x16x16_bf16.  The weight gradient
-// is a GEMM over pixels (split into fixed chunks, partials summed in a fixed
-// order).
+// uses v_mfma_f32_16x16x16_bf16.  The weight gradients are GEMMs over pixels on
+// the K = 32 instruction, with NHWC tiles in LDS read pixel-major by transposing
+// loads (split into fixed chunks, partials summed in a fixed order).
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "esi_internal.h"
@@ -83,6 +84,10 @@ static uint16_t f2bf_host(float f) {
 // b, b + gridDim.x, ...  The global loads of the next step are issued
 // before the current step's MFMAs and land in registers, so memory latency
 // overlaps the arithmetic; a tile's outputs are stored after its last chunk.
+// With MASK, outputs where `act` (an activation laid out as Y, no halves) is not
+// positive are 0: the ReLU mask of a data gradient, in place of a pass of its
+// own.  (A template flag: a test of the pointer in the epilogue slowed the
+// forward pass by 19 %.)
 constexpr int frag_ck(int K) { return K % 32 == 0 ? 32 : 16; }
 constexpr int frag_nkb(int ck) { return ck == 32 ? 9 : 5; }
 
@@ -96,11 +101,11 @@ struct Conv3Tile {
     static constexpr int NWQ = NKB * CB * 64, NWL = (NWQ + NTW - 1) / NTW;  // and of a chunk's weights
 };
 
-template <int CB, int RPW, int CK, int NWV>
+template <int CB, int RPW, int CK, int NWV, bool MASK>
 __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3(
     const bf16_t* __restrict__ X, int sx, int64_t xhs, int xsplit, int K, const bf16_t* __restrict__ Af, int ncb,
     const float* __restrict__ bias, bf16_t* __restrict__ Y, int sy, int64_t yhs, int ysplit, int M, int H, int W,
-    int N, int relu) {
+    int N, int relu, const bf16_t* __restrict__ act) {
     using T = Conv3Tile<CB, RPW, CK, NWV>;
     __shared__ __align__(16) bf16_t xs[T::TR * T::TC * T::PS];
     __shared__ __align__(16) bf16_t ws[T::NWQ * 8];
@@ -210,12 +215,14 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
                 for (int c = 0; c < CB; ++c) {
                     const int co = (cbg * CB + c) * 16 + 4 * g;
                     if (yo < H && xo < W) {
-                        s4 o;
+                        s4 on = s4{0, 0, 0, 0}, o;
+                        if constexpr (MASK)
+                            on = *reinterpret_cast<const s4*>(act + ((int64_t)n * H * W + (int64_t)yo * W + xo) * sy + co);
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             float v = acc[r][p][c][e] + (bias ? bias[co + e] : 0.f);
                             if (relu) v = fmaxf(v, 0.f);
-                            o[e] = (short)f2bf(v);
+                            o[e] = !MASK || bf2f((bf16_t)on[e]) > 0.f ? (short)f2bf(v) : (short)0;
                         }
                         const int64_t hoff = co >= ysplit ? yhs - ysplit : 0;
                         *reinterpret_cast<s4*>(Yn + ((int64_t)yo * W + xo) * sy + hoff + co) = o;
@@ -227,87 +234,212 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) v
     }
 }
 
-// Weight gradient of a 3x3 convolution: part[chunk][tap][co][ci] =
-// sum over the chunk's rows of gy[p][co] x[p + tap][ci], and the bias partial
-// bpart[chunk][co] = sum gy[p][co] (written by the ci-block 0 waves).
-// One wave per (chunk, co block, ci block); rows of all images are chunked.
-__global__ __launch_bounds__(64) void k_conv3_wgrad(const bf16_t* __restrict__ GY, int sg, int Cout,
-                                                    const bf16_t* __restrict__ X, int sx, int64_t xhs, int xsplit,
-                                                    int Cin,
-                                                    int H, int W, int nrows, int rows_per_chunk,
-                                                    float* __restrict__ part, float* __restrict__ bpart) {
-    const int lane = threadIdx.x;
-    const int nci = Cin / 16;
-    const int blk = blockIdx.y;
-    const int co0 = (blk / nci) * 16, ci0 = (blk % nci) * 16;
-    const int chunk = blockIdx.x;
-    const int r0 = chunk * rows_per_chunk, r1 = min(nrows, r0 + rows_per_chunk);
-    const int jl = lane & 15, kq = (lane >> 4) * 4;
-    f4 acc[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.f;
-    for (int r = r0; r < r1; ++r) {
-        const int n = r / H, y = r % H;
-        const bf16_t* Gr = GY + (int64_t)r * W * sg;
-        const bf16_t* Xn = X + (int64_t)n * H * W * sx + (ci0 >= xsplit ? xhs - xsplit : 0);
-        for (int x0 = 0; x0 < W; x0 += 16) {
-            s4 a;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int xp = x0 + kq + e;
-                a[e] = xp < W ? (short)Gr[(int64_t)xp * sg + co0 + jl] : (short)0;
-                bsum += bf2f((bf16_t)a[e]);
-            }
-#pragma unroll
-            for (int tap = 0; tap < 9; ++tap) {
-                const int yy = y + tap / 3 - 1, dx = tap % 3 - 1;
-                s4 b;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int xp = x0 + kq + e, xx = xp + dx;
-                    b[e] = (xp < W && yy >= 0 && yy < H && xx >= 0 && xx < W)
-                               ? (short)Xn[((int64_t)yy * W + xx) * sx + ci0 + jl] : (short)0;
-                }
-                acc[tap] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[tap], 0, 0, 0);
-            }
-        }
-    }
-    // D[co][ci]: lane holds ci = ci0 + jl, co = co0 + kq + e
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            part[(((int64_t)chunk * 9 + tap) * Cout + co0 + kq + e) * Cin + ci0 + jl] = acc[tap][e];
-    if (ci0 == 0) {
-        // lanes jl, jl+16, jl+32, jl+48 hold partial sums of channel co0 + jl
-        bsum += __shfl_xor(bsum, 16, 64);
-        bsum += __shfl_xor(bsum, 32, 64);
-        if (lane < 16) bpart[(int64_t)chunk * Cout + co0 + lane] = bsum;
-    }
+// ---- weight gradients --------------------------------------------------------
+// A weight gradient is a GEMM over pixels: D[co][ci] = sum_p GY[p][co] X[p'][ci]
+// per tap, p' the tap's input pixel.  Both operands are wanted pixel-major (a
+// lane holds eight pixels of one channel) while the tensors are channel-major,
+// so tiles are staged in LDS as they are and read by the transposing loads of
+// gfx950: ds_read_tr16_b64 gives lane l = 16 g + i of a wave column i (a
+// channel) of the four rows (pixels) whose 32 bytes its group's lanes address,
+// lane i at row i / 4, columns 4 (i % 4).  A tap is then an offset in pixels.
+typedef __attribute__((address_space(3))) s4 lds_s4;
+
+// Eight pixels of channel l % 16 for lane l: pixels p, .., p + 3 at `lo` and at
+// `hi`, each lane passing the address of its pixel and channel quarter.
+__device__ __forceinline__ bf16x8 tr_operand(const bf16_t* lo, const bf16_t* hi) {
+    union { s4 h[2]; bf16x8 v; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(lo));
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(hi));
+    return u.v;
+}
+__device__ __forceinline__ bf16x8 bf_ones() {
+    union { s4 h[2]; bf16x8 v; } u;
+    u.h[0] = u.h[1] = s4{0x3F80, 0x3F80, 0x3F80, 0x3F80};
+    return u.v;
 }
 
-// Sum the chunk partials of a 3x3 layer into the flat gradient: weights in
-// [co][ci][3][3] for ci < cin_real, then the bias.  Threads walk the partials
-// in their own layout (ci fastest) so the reads over chunks are coalesced.
-__global__ void k_conv3_wgrad_reduce(const float* __restrict__ part, const float* __restrict__ bpart,
-                                     int nchunks, int Cout, int Cin, int cin_real,
-                                     float* __restrict__ gflat) {
-    const int64_t per = (int64_t)9 * Cout * Cin;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < per + Cout;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        float s = 0.f;
-        if (i < per) {
-            const int ci = (int)(i % Cin), co = (int)((i / Cin) % Cout), tap = (int)(i / ((int64_t)Cin * Cout));
-            if (ci >= cin_real) continue;
-            for (int c = 0; c < nchunks; ++c) s += part[(int64_t)c * per + i];
-            gflat[((int64_t)co * cin_real + ci) * 9 + tap] = s;
-        } else {
-            const int co = (int)(i - per);
-            for (int c = 0; c < nchunks; ++c) s += bpart[(int64_t)c * Cout + co];
-            gflat[(int64_t)Cout * cin_real * 9 + co] = s;
+// Sum the four waves' accumulators of a workgroup in a fixed order and write
+// them as part[tap][co][ci] of this chunk (TAPS x CO x CI of the layer's TAPS x
+// Cout x Cin, at co0, ci0), the bias sums (column 0 of bacc) after them.
+template <int TAPS, int CB, int IB>
+__device__ __forceinline__ void wgrad_out(const f4 (&acc)[TAPS][CB][IB], const f4 (&bacc)[CB], float* sm, int co0,
+                                          int ci0, int Cout, int Cin, float* __restrict__ part,
+                                          float* __restrict__ bpart) {
+    constexpr int CO = 16 * CB, CI = 16 * IB;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int jl = lane & 15, g = lane >> 4;
+    float* sb = sm + TAPS * CO * CI;
+    for (int w = 0; w < 4; ++w) {
+        __syncthreads();
+        if (wave != w) continue;
+#pragma unroll
+        for (int t = 0; t < TAPS; ++t)
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+#pragma unroll
+                for (int b = 0; b < IB; ++b)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        float* q = sm + (t * CO + 16 * c + 4 * g + e) * CI + 16 * b + jl;
+                        *q = w ? *q + acc[t][c][b][e] : acc[t][c][b][e];
+                    }
+        if (jl == 0)
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float* q = sb + 16 * c + 4 * g + e;
+                    *q = w ? *q + bacc[c][e] : bacc[c][e];
+                }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < TAPS * CO * CI; i += NT) {
+        const int ci = i % CI, co = (i / CI) % CO, t = i / (CI * CO);
+        part[((int64_t)t * Cout + co0 + co) * Cin + ci0 + ci] = sm[i];
+    }
+    if (ci0 == 0 && threadIdx.x < CO) bpart[co0 + threadIdx.x] = sb[threadIdx.x];
+}
+
+// Weight gradient of a 3x3 convolution, with the bias gradient sum_p GY[p][co]
+// (a product with ones).  Workgroup (chunk, channel tile): four waves, 16 CB
+// output x 16 IB input channels, all nine taps, over the chunk's tiles of
+// ROWS x 64 pixels (chunk, chunk + gridDim.x, ...); a tile's GY and its X with
+// a 1-pixel halo are staged in LDS while the next tile's loads are in flight,
+// and wave w takes rows w, w + 4, ...  Pixels off the image are 0.
+//
+// One wave per 16 x 16 channels fetching every operand element by itself (two
+// bytes a load) and a thread per output adding up to 1664 chunks took 183 and 143
+// us a layer on average on 16 images of 208 x 408.  Now 22 us at 16 x 16 channels
+// (87 MB read, 4 TB/s), 35 us at 32 x 32 and above, 6 us for the sum; the whole
+// training gradient went from 6.58 to 1.55 ms.
+template <int CB, int IB, int ROWS>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3_wgrad(
+    const bf16_t* __restrict__ GY, int sg, int Cout, const bf16_t* __restrict__ X, int sx, int64_t xhs, int xsplit,
+    int Cin, int H, int W, int N, float* __restrict__ part, float* __restrict__ bpart) {
+    constexpr int CO = 16 * CB, CI = 16 * IB, TW = 64, XW = TW + 2;
+    constexpr int NGQ = ROWS * TW * CO / 8, NXQ = (ROWS + 2) * XW * CI / 8;   // 16-byte pieces of a tile
+    constexpr int NG = (NGQ + NT - 1) / NT, NX = (NXQ + NT - 1) / NT;
+    constexpr int SM_TILE = (ROWS * TW * CO + (ROWS + 2) * XW * CI) * 2, SM_OUT = (9 * CO * CI + CO) * 4;
+    __shared__ __align__(16) char smem[SM_TILE > SM_OUT ? SM_TILE : SM_OUT];
+    bf16_t* gs = reinterpret_cast<bf16_t*>(smem);
+    bf16_t* xs = gs + ROWS * TW * CO;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nci = Cin / CI;
+    const int co0 = (int)(blockIdx.y / nci) * CO, ci0 = (int)(blockIdx.y % nci) * CI;
+    const int ntx = (W + TW - 1) / TW, nty = (H + ROWS - 1) / ROWS, ntiles = ntx * nty * N;
+    const bf16_t* Gc = GY + co0;
+    // this thread's channels of X, the same for each piece it stages; a channel
+    // tile may span the halves of a concatenation
+    const int xch = ci0 + (int)(threadIdx.x % (CI / 8)) * 8;
+    const bf16_t* Xc = X + xch + (xch >= xsplit ? xhs - xsplit : 0);
+    static_assert(NT % (CI / 8) == 0, "a thread stages the same channels throughout");
+
+    uint4 rg[NG], rx[NX];
+    auto fetch = [&](int t) {
+        const int x0 = (t % ntx) * TW, y0 = ((t / ntx) % nty) * ROWS, n = t / (ntx * nty);
+        const bf16_t* Gn = Gc + (int64_t)n * H * W * sg;
+        const bf16_t* Xn = Xc + (int64_t)n * H * W * sx;
+#pragma unroll
+        for (int l = 0; l < NG; ++l) {
+            const int q = threadIdx.x + l * NT, sub = q % (CO / 8), px = (q / (CO / 8)) % TW, row = q / (CO / 8 * TW);
+            rg[l] = uint4{0u, 0u, 0u, 0u};
+            if (q < NGQ && y0 + row < H && x0 + px < W)
+                rg[l] = *reinterpret_cast<const uint4*>(Gn + ((int64_t)(y0 + row) * W + x0 + px) * sg + sub * 8);
+        }
+#pragma unroll
+        for (int l = 0; l < NX; ++l) {
+            const int q = threadIdx.x + l * NT, px = (q / (CI / 8)) % XW, row = q / (CI / 8 * XW);
+            const int yy = y0 - 1 + row, xx = x0 - 1 + px;
+            rx[l] = uint4{0u, 0u, 0u, 0u};
+            if (q < NXQ && yy >= 0 && yy < H && xx >= 0 && xx < W)
+                rx[l] = *reinterpret_cast<const uint4*>(Xn + ((int64_t)yy * W + xx) * sx);
+        }
+    };
+    f4 acc[9][CB][IB], bacc[CB];
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+        bacc[c] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int b = 0; b < IB; ++b) acc[t][c][b] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+    // this lane's pixel and channel quarter in a group of 16 pixels
+    const int pl = 4 * (lane >> 4) + ((lane & 15) >> 2), cq = 4 * (lane & 3);
+    if ((int)blockIdx.x < ntiles) fetch(blockIdx.x);
+    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        __syncthreads();   // every wave is done with the previous tile
+#pragma unroll
+        for (int l = 0; l < NG; ++l)
+            if (threadIdx.x + l * NT < NGQ) *reinterpret_cast<uint4*>(gs + (threadIdx.x + l * NT) * 8) = rg[l];
+#pragma unroll
+        for (int l = 0; l < NX; ++l)
+            if (threadIdx.x + l * NT < NXQ) *reinterpret_cast<uint4*>(xs + (threadIdx.x + l * NT) * 8) = rx[l];
+        __syncthreads();
+        if (t + (int)gridDim.x < ntiles) fetch(t + gridDim.x);
+#pragma unroll
+        for (int r0 = 0; r0 < ROWS; r0 += 4) {
+            const int row = r0 + wave;
+#pragma unroll
+            for (int k0 = 0; k0 < TW; k0 += 32) {
+                bf16x8 a[CB];
+                const bf16_t* gp = gs + (row * TW + k0 + pl) * CO + cq;
+#pragma unroll
+                for (int c = 0; c < CB; ++c) {
+                    a[c] = tr_operand(gp + 16 * c, gp + 16 * CO + 16 * c);
+                    bacc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], bf_ones(), bacc[c], 0, 0, 0);
+                }
+#pragma unroll
+                for (int tap = 0; tap < 9; ++tap) {
+                    const bf16_t* xp = xs + ((row + tap / 3) * XW + k0 + pl + tap % 3) * CI + cq;
+#pragma unroll
+                    for (int b = 0; b < IB; ++b) {
+                        const bf16x8 bv = tr_operand(xp + 16 * b, xp + 16 * CI + 16 * b);
+#pragma unroll
+                        for (int c = 0; c < CB; ++c)
+                            acc[tap][c][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], bv, acc[tap][c][b], 0, 0, 0);
+                    }
+                }
+            }
         }
     }
+    const int64_t per = (int64_t)9 * Cout * Cin;
+    wgrad_out<9, CB, IB>(acc, bacc, reinterpret_cast<float*>(smem), co0, ci0, Cout, Cin, part + blockIdx.x * per,
+                         bpart + (int64_t)blockIdx.x * Cout);
+}
+
+// Sum the chunk partials [chunk][tap][co][ci] (and [chunk][nbias] of the bias) of
+// a layer into its flat gradient: weights [co][ci][taps] (3x3 convolutions, ci <
+// cin_real) or [ci][co][taps] (T: transposed ones), then the bias.  A workgroup
+// takes 64 outputs, 16 threads each over every 16th chunk, in float64.
+template <bool T>
+__global__ __launch_bounds__(1024) void k_wgrad_reduce(const float* __restrict__ part, const float* __restrict__ bpart,
+                                                       int nchunks, int taps, int Cout, int Cin, int cin_real,
+                                                       int nbias, float* __restrict__ gflat) {
+    __shared__ double sm[16][64];
+    const int64_t per = (int64_t)taps * Cout * Cin;
+    const int64_t i = blockIdx.x * (int64_t)64 + (threadIdx.x & 63);
+    const int slice = threadIdx.x >> 6;
+    double s = 0.0;
+    if (i < per + nbias) {
+        const float* p = i < per ? part + i : bpart + (i - per);
+        const int64_t stride = i < per ? per : nbias;
+#pragma unroll 4
+        for (int c = slice; c < nchunks; c += 16) s += p[c * stride];
+    }
+    sm[slice][threadIdx.x & 63] = s;
+    __syncthreads();
+    if (slice || i >= per + nbias) return;
+    s = 0.0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) s += sm[k][threadIdx.x];
+    if (i >= per) {
+        gflat[(int64_t)Cout * cin_real * taps + (i - per)] = (float)s;
+        return;
+    }
+    const int ci = (int)(i % Cin), co = (int)((i / Cin) % Cout), tap = (int)(i / ((int64_t)Cin * Cout));
+    if (T) gflat[((int64_t)ci * Cout + co) * taps + tap] = (float)s;
+    else if (ci < cin_real) gflat[((int64_t)co * cin_real + ci) * taps + tap] = (float)s;
 }
 
 // 2x2 average pool: out[n][i][j][c] = bf16(mean of the 2x2 block).
@@ -337,29 +469,28 @@ __global__ void k_pool(const bf16_t* __restrict__ X, int sx, bf16_t* __restrict_
 }
 
 // Gradient into an encoder output: g[n][y][x][c] = bf16(gp[n][y/2][x/2][c] / 4
-// + gskip[n][y][x][c]), then the ReLU mask of that output.
-__global__ void k_pool_back(const bf16_t* __restrict__ GP, int sp, const bf16_t* __restrict__ GS, int ss,
-                            const bf16_t* __restrict__ Yact, int sa, bf16_t* __restrict__ G, int sg,
-                            int C, int N, int H, int W) {
-    const int64_t total = (int64_t)N * H * W * C;
+// + gskip[n][y][x][c]), then the ReLU mask of that output.  One thread per 8
+// channels of a pixel (16-byte loads and store: 18 us a level on average on 16
+// images of 208 x 408, two bytes at a time 51).
+__global__ void k_pool_back(const bf16_t* __restrict__ GP, const bf16_t* GS, const bf16_t* __restrict__ Yact,
+                            bf16_t* G, int C, int N, int H, int W) {   // GS may be G
+    const int C8 = C / 8;
+    const int64_t total = (int64_t)N * H * W * C8;
     for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < total; i += (int64_t)gridDim.x * NT) {
-        const int c = (int)(i % C);
-        const int64_t pix = i / C;
+        const int c = (int)(i % C8) * 8;
+        const int64_t pix = i / C8;
         const int x = (int)(pix % W), y = (int)((pix / W) % H), n = (int)(pix / ((int64_t)W * H));
         const int64_t pp = ((int64_t)n * (H / 2) + y / 2) * (W / 2) + x / 2;
-        const float v = 0.25f * bf2f(GP[pp * sp + c]) + bf2f(GS[pix * ss + c]);
-        G[pix * sg + c] = bf2f(Yact[pix * sa + c]) > 0.f ? f2bf(v) : (bf16_t)0;
-    }
-}
-
-// g *= (y > 0), in place.
-__global__ void k_relu_mask(bf16_t* __restrict__ G, int sg, const bf16_t* __restrict__ Yact, int sa,
-                            int C, int64_t npix) {
-    const int64_t total = npix * C;
-    for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < total; i += (int64_t)gridDim.x * NT) {
-        const int c = (int)(i % C);
-        const int64_t pix = i / C;
-        if (!(bf2f(Yact[pix * sa + c]) > 0.f)) G[pix * sg + c] = 0;
+        bf8u gp, gsk, ya, o;
+        gp.u = *reinterpret_cast<const uint4*>(GP + pp * C + c);
+        gsk.u = *reinterpret_cast<const uint4*>(GS + pix * C + c);
+        ya.u = *reinterpret_cast<const uint4*>(Yact + pix * C + c);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float v = 0.25f * bf2f(gp.h[e]) + bf2f(gsk.h[e]);
+            o.h[e] = bf2f(ya.h[e]) > 0.f ? f2bf(v) : (bf16_t)0;
+        }
+        *reinterpret_cast<uint4*>(G + pix * C + c) = o.u;
     }
 }
 
@@ -427,11 +558,13 @@ __global__ __launch_bounds__(NT) void k_convT_mfma(const bf16_t* __restrict__ X,
 
 // Data gradient of the transposed convolution: D[ci][pixel] = sum over
 // (a d, co) of WT[ci][(a d) Cout + co] GY[(2i + a, 2j + d)][co]; WT is
-// [Cin][4 Cout] bf16.  Same workgroup shape as k_convT_mfma.
+// [Cin][4 Cout] bf16.  Outputs where the activation `act` (laid out as GX) is
+// not positive are 0.  Same workgroup shape as k_convT_mfma.
 template <int CB>
 __global__ __launch_bounds__(NT) void k_convT_dgrad_mfma(const bf16_t* __restrict__ GY, int sg, int Cout,
                                                          const bf16_t* __restrict__ WT, bf16_t* __restrict__ GX,
-                                                         int sx, int Cin, int Hi, int Wi) {
+                                                         int sx, int Cin, int Hi, int Wi,
+                                                         const bf16_t* __restrict__ act) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ncog = Cin / (16 * CB);
     const int n = blockIdx.z / ncog;
@@ -463,104 +596,108 @@ __global__ __launch_bounds__(NT) void k_convT_dgrad_mfma(const bf16_t* __restric
                 acc[p][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, b[p], acc[p][c], 0, 0, 0);
         }
     }
-    bf16_t* Gxr = GX + ((int64_t)n * Hi + y) * Wi * sx;
+    const int64_t row = ((int64_t)n * Hi + y) * Wi * sx;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         const int xx = x0 + p * 16 + jl;
         if (xx >= Wi) continue;
 #pragma unroll
         for (int c = 0; c < CB; ++c) {
+            const int64_t at = row + (int64_t)xx * sx + c0 + c * 16 + kq;
+            const s4 on = *reinterpret_cast<const s4*>(act + at);
             s4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (short)f2bf(acc[p][c][e]);
-            *reinterpret_cast<s4*>(Gxr + (int64_t)xx * sx + c0 + c * 16 + kq) = o;
+            for (int e = 0; e < 4; ++e) o[e] = bf2f((bf16_t)on[e]) > 0.f ? (short)f2bf(acc[p][c][e]) : (short)0;
+            *reinterpret_cast<s4*>(GX + at) = o;
         }
     }
 }
 
-// Weight gradient of the transposed convolution: part[chunk][ad][co][ci] =
-// sum over the chunk's input rows of GY[(2i + a, 2j + d)][co] X[(i, j)][ci]
-// (a GEMM over pixels per sub-position ad), and bpart[chunk][co] = the sum of
-// GY over the chunk's output pixels (ci-block 0 waves).  One wave per (chunk,
-// co block, ci block).
-__global__ __launch_bounds__(64) void k_convT_wgrad_mfma(const bf16_t* __restrict__ X, int sx, int Cin,
-                                                         const bf16_t* __restrict__ GY, int sg, int Cout, int Hi,
-                                                         int Wi, int nrows, int rows_per_chunk,
-                                                         float* __restrict__ part, float* __restrict__ bpart) {
-    const int lane = threadIdx.x;
-    const int nci = Cin / 16;
-    const int co0 = (blockIdx.y / nci) * 16, ci0 = (blockIdx.y % nci) * 16;
-    const int chunk = blockIdx.x;
-    const int r0 = chunk * rows_per_chunk, r1 = min(nrows, r0 + rows_per_chunk);
-    const int jl = lane & 15, kq = (lane >> 4) * 4;
-    const int Wo = 2 * Wi;
-    f4 acc[4];
+// Weight gradient of the transposed convolution: part[chunk][ad][co][ci] = sum
+// over the chunk's input pixels of GY[(2i + a, 2j + d)][co] X[(i, j)][ci], and
+// the bias partials sum GY.  As k_conv3_wgrad, on tiles of 2 x 64 input pixels
+// (4 x 128 of GY, whose pixels a tap reads at a stride of two); wave w takes
+// row w / 2, columns 32 (w % 2) on.
+template <int CB, int IB>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_convT_wgrad(
+    const bf16_t* __restrict__ X, int sx, int Cin, const bf16_t* __restrict__ GY, int sg, int Cout, int Hi, int Wi,
+    int N, float* __restrict__ part, float* __restrict__ bpart) {
+    constexpr int CO = 16 * CB, CI = 16 * IB, TW = 64, ROWS = 2;
+    constexpr int NGQ = 4 * ROWS * TW * CO / 8, NXQ = ROWS * TW * CI / 8;
+    constexpr int NG = (NGQ + NT - 1) / NT, NX = (NXQ + NT - 1) / NT;
+    constexpr int SM_TILE = (4 * ROWS * TW * CO + ROWS * TW * CI) * 2, SM_OUT = (4 * CO * CI + CO) * 4;
+    __shared__ __align__(16) char smem[SM_TILE > SM_OUT ? SM_TILE : SM_OUT];
+    bf16_t* gs = reinterpret_cast<bf16_t*>(smem);
+    bf16_t* xs = gs + 4 * ROWS * TW * CO;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nci = Cin / CI;
+    const int co0 = (int)(blockIdx.y / nci) * CO, ci0 = (int)(blockIdx.y % nci) * CI;
+    const int ntx = (Wi + TW - 1) / TW, nty = (Hi + ROWS - 1) / ROWS, ntiles = ntx * nty * N;
+    const int Wo = 2 * Wi, Ho = 2 * Hi;
+
+    uint4 rg[NG], rx[NX];
+    auto fetch = [&](int t) {
+        const int x0 = (t % ntx) * TW, y0 = ((t / ntx) % nty) * ROWS, n = t / (ntx * nty);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.f;
-    for (int r = r0; r < r1; ++r) {                       // r = n Hi + i
-        const int n = r / Hi, i = r - n * Hi;
-        const bf16_t* Xr = X + (int64_t)r * Wi * sx;
-        for (int x0 = 0; x0 < Wi; x0 += 16) {
-            s4 b;
+        for (int l = 0; l < NG; ++l) {
+            const int q = threadIdx.x + l * NT, sub = q % (CO / 8), px = (q / (CO / 8)) % (2 * TW),
+                      row = q / (CO / 8 * 2 * TW);
+            rg[l] = uint4{0u, 0u, 0u, 0u};
+            if (q < NGQ && 2 * y0 + row < Ho && 2 * x0 + px < Wo)
+                rg[l] = *reinterpret_cast<const uint4*>(
+                    GY + (((int64_t)n * Ho + 2 * y0 + row) * Wo + 2 * x0 + px) * sg + co0 + sub * 8);
+        }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int xp = x0 + kq + e;
-                b[e] = xp < Wi ? (short)Xr[(int64_t)xp * sx + ci0 + jl] : (short)0;
-            }
+        for (int l = 0; l < NX; ++l) {
+            const int q = threadIdx.x + l * NT, sub = q % (CI / 8), px = (q / (CI / 8)) % TW, row = q / (CI / 8 * TW);
+            rx[l] = uint4{0u, 0u, 0u, 0u};
+            if (q < NXQ && y0 + row < Hi && x0 + px < Wi)
+                rx[l] = *reinterpret_cast<const uint4*>(X + (((int64_t)n * Hi + y0 + row) * Wi + x0 + px) * sx + ci0 +
+                                                        sub * 8);
+        }
+    };
+    f4 acc[4][CB][IB], bacc[CB];
 #pragma unroll
-            for (int ad = 0; ad < 4; ++ad) {
-                const bf16_t* Gr = GY + (((int64_t)n * 2 * Hi + 2 * i + (ad >> 1)) * Wo + (ad & 1)) * sg + co0 + jl;
-                s4 av;
+    for (int c = 0; c < CB; ++c) {
+        bacc[c] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int xp = x0 + kq + e;
-                    av[e] = xp < Wi ? (short)Gr[(int64_t)2 * xp * sg] : (short)0;
-                    bsum += bf2f((bf16_t)av[e]);
-                }
-                acc[ad] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, b, acc[ad], 0, 0, 0);
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int b = 0; b < IB; ++b) acc[t][c][b] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int pl = 4 * (lane >> 4) + ((lane & 15) >> 2), cq = 4 * (lane & 3);
+    const int row = wave >> 1, k0 = 32 * (wave & 1);
+    if ((int)blockIdx.x < ntiles) fetch(blockIdx.x);
+    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        __syncthreads();   // every wave is done with the previous tile
+#pragma unroll
+        for (int l = 0; l < NG; ++l)
+            if (threadIdx.x + l * NT < NGQ) *reinterpret_cast<uint4*>(gs + (threadIdx.x + l * NT) * 8) = rg[l];
+#pragma unroll
+        for (int l = 0; l < NX; ++l)
+            if (threadIdx.x + l * NT < NXQ) *reinterpret_cast<uint4*>(xs + (threadIdx.x + l * NT) * 8) = rx[l];
+        __syncthreads();
+        if (t + (int)gridDim.x < ntiles) fetch(t + gridDim.x);
+        bf16x8 bv[IB];
+        const bf16_t* xp = xs + (row * TW + k0 + pl) * CI + cq;
+#pragma unroll
+        for (int b = 0; b < IB; ++b) bv[b] = tr_operand(xp + 16 * b, xp + 16 * CI + 16 * b);
+#pragma unroll
+        for (int ad = 0; ad < 4; ++ad) {
+            const bf16_t* gp = gs + ((2 * row + (ad >> 1)) * 2 * TW + 2 * (k0 + pl) + (ad & 1)) * CO + cq;
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                const bf16x8 a = tr_operand(gp + 16 * c, gp + 32 * CO + 16 * c);
+                bacc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bf_ones(), bacc[c], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < IB; ++b)
+                    acc[ad][c][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bv[b], acc[ad][c][b], 0, 0, 0);
             }
         }
     }
-    // D[co][ci]: lane holds ci = ci0 + jl, co = co0 + kq + e
-#pragma unroll
-    for (int ad = 0; ad < 4; ++ad)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            part[(((int64_t)chunk * 4 + ad) * Cout + co0 + kq + e) * Cin + ci0 + jl] = acc[ad][e];
-    if (ci0 == 0) {
-        bsum += __shfl_xor(bsum, 16, 64);
-        bsum += __shfl_xor(bsum, 32, 64);
-        if (lane < 16) bpart[(int64_t)chunk * Cout + co0 + lane] = bsum;
-    }
-}
-
-// Transposed-convolution partials into the flat gradient [ci][co][a][d] + bias.
-__global__ void k_convT_wgrad_reduce(const float* __restrict__ part, const float* __restrict__ bpart, int nchunks,
-                                     int Cout, int Cin, float* __restrict__ gflat) {
     const int64_t per = (int64_t)4 * Cout * Cin;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < per + Cout;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        float s = 0.f;
-        if (i < per) {
-            const int ci = (int)(i % Cin), co = (int)((i / Cin) % Cout), ad = (int)(i / ((int64_t)Cin * Cout));
-            for (int c = 0; c < nchunks; ++c) s += part[(int64_t)c * per + i];
-            gflat[((int64_t)ci * Cout + co) * 4 + ad] = s;
-        } else {
-            const int co = (int)(i - per);
-            for (int c = 0; c < nchunks; ++c) s += bpart[(int64_t)c * Cout + co];
-            gflat[per + co] = s;
-        }
-    }
-}
-
-// Sum per-chunk partials laid out [chunk][n] into out[n].
-__global__ void k_sum_chunks(const float* __restrict__ part, int nchunks, int64_t n, float* __restrict__ out) {
-    for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * NT) {
-        float s = 0.f;
-        for (int c = 0; c < nchunks; ++c) s += part[(int64_t)c * n + i];
-        out[i] = s;
-    }
+    wgrad_out<4, CB, IB>(acc, bacc, reinterpret_cast<float*>(smem), co0, ci0, Cout, Cin, part + blockIdx.x * per,
+                         bpart + (int64_t)blockIdx.x * Cout);
 }
 
 // Output layer (1x1, 16 -> 1): o[p] = b + sum_c w[c] x[p][c], float32.
@@ -590,12 +727,17 @@ __global__ void k_out_back(const float* __restrict__ go, const bf16_t* __restric
     for (int c = 0; c < 17; ++c) acc[c] = 0.f;
     for (int64_t p = p0 + threadIdx.x; p < p1; p += NT) {
         const float g = go[p];
+        bf8u xv[2], gv[2];
+        xv[0].u = *reinterpret_cast<const uint4*>(X + p * sx);
+        xv[1].u = *reinterpret_cast<const uint4*>(X + p * sx + 8);
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
-            const float xv = bf2f(X[p * sx + c]);
-            acc[c] += g * xv;
-            G[p * sg + c] = xv > 0.f ? f2bf(bf2f(w[c]) * g) : (bf16_t)0;
+            const float xc = bf2f(xv[c >> 3].h[c & 7]);
+            acc[c] += g * xc;
+            gv[c >> 3].h[c & 7] = xc > 0.f ? f2bf(bf2f(w[c]) * g) : (bf16_t)0;
         }
+        *reinterpret_cast<uint4*>(G + p * sg) = gv[0].u;
+        *reinterpret_cast<uint4*>(G + p * sg + 8) = gv[1].u;
         acc[16] += g;
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -642,50 +784,79 @@ __global__ __launch_bounds__(NT) void k_loss_weights(const float* __restrict__ a
 
 // Scaling loss per sample s: L_s = w_s sum_x (a e^{2o} - 2 c e^{o}) and
 // go = w_s (2 a e^{2o} - 2 c e^{o}) / nbatch, with w from `weight` or the
-// default sum_x a / (sum_x c)^2 of the image.  One workgroup per sample;
-// loss[s] in float64.
+// default sum_x a / (sum_x c)^2 of the image.  LOSS_BLOCKS workgroups per sample
+// (grid LOSS_BLOCKS x nbatch) leave float64 partials, summed in a fixed order:
+// k_loss_sums those of a and c, k_scaling_loss the loss's, k_loss_finish adds
+// them up.  (One workgroup per sample took 266 us for 16 images of 208 x 408.)
+constexpr int LOSS_BLOCKS = 32;
+
+__device__ __forceinline__ double nt_block_sum(double v, double* red) {   // valid in every thread
+    for (int k = 32; k > 0; k >>= 1) v += __shfl_xor(v, k, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double t = 0.0;
+    for (int k = 0; k < NT / 64; ++k) t += red[k];
+    return t;
+}
+
+// part[s][b][2]: partial sums of a and c
+__global__ __launch_bounds__(NT) void k_loss_sums(const float* __restrict__ a, const float* __restrict__ c,
+                                                  int64_t npix, double* __restrict__ part) {
+    __shared__ double red[NT / 64];
+    const int s = blockIdx.y;
+    double suma = 0.0, sumc = 0.0;
+    for (int64_t p = blockIdx.x * (int64_t)NT + threadIdx.x; p < npix; p += (int64_t)LOSS_BLOCKS * NT) {
+        suma += a[(int64_t)s * npix + p];
+        sumc += c[(int64_t)s * npix + p];
+    }
+    suma = nt_block_sum(suma, red);
+    sumc = nt_block_sum(sumc, red);
+    if (threadIdx.x == 0) {
+        part[((int64_t)s * LOSS_BLOCKS + blockIdx.x) * 2] = suma;
+        part[((int64_t)s * LOSS_BLOCKS + blockIdx.x) * 2 + 1] = sumc;
+    }
+}
+
+// sums: k_loss_sums' partials (weight null); lpart[s][b]: partial of the weighted loss
 __global__ __launch_bounds__(NT) void k_scaling_loss(const float* __restrict__ o, const float* __restrict__ a,
                                                      const float* __restrict__ c, const float* __restrict__ weight,
-                                                     int64_t npix, int nbatch, float* __restrict__ go,
-                                                     double* __restrict__ loss) {
+                                                     const double* __restrict__ sums, int64_t npix, int nbatch,
+                                                     float* __restrict__ go, double* __restrict__ lpart) {
     __shared__ double red[NT / 64];
-    const int s = blockIdx.x;
+    const int s = blockIdx.y;
     const float* os = o + (int64_t)s * npix;
     const float* as = a + (int64_t)s * npix;
     const float* cs = c + (int64_t)s * npix;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    auto block_sum = [&](double v) -> double {
-        for (int k = 32; k > 0; k >>= 1) v += __shfl_xor(v, k, 64);
-        __syncthreads();
-        if (lane == 0) red[wv] = v;
-        __syncthreads();
-        double t = 0.0;
-        for (int k = 0; k < NT / 64; ++k) t += red[k];
-        return t;
-    };
     double wt;
     if (weight) {
         wt = weight[s];
     } else {
         double suma = 0.0, sumc = 0.0;
-        for (int64_t p = threadIdx.x; p < npix; p += NT) {
-            suma += as[p];
-            sumc += cs[p];
+        for (int b = 0; b < LOSS_BLOCKS; ++b) {
+            suma += sums[((int64_t)s * LOSS_BLOCKS + b) * 2];
+            sumc += sums[((int64_t)s * LOSS_BLOCKS + b) * 2 + 1];
         }
-        suma = block_sum(suma);
-        sumc = block_sum(sumc);
         wt = (sumc > 0.0 && suma > 0.0) ? (double)(float)(suma / (sumc * sumc)) : 0.0;
     }
     const float inv = (float)wt;
     double sl = 0.0;
-    for (int64_t p = threadIdx.x; p < npix; p += NT) {
+    for (int64_t p = blockIdx.x * (int64_t)NT + threadIdx.x; p < npix; p += (int64_t)LOSS_BLOCKS * NT) {
         const float e = expf(os[p]);
         const float ae = as[p] * e, ce = cs[p];
         sl += (double)(ae * e - 2.f * ce * e);
         go[(int64_t)s * npix + p] = (2.f * ae * e - 2.f * ce * e) * inv / (float)nbatch;
     }
-    sl = block_sum(sl);
-    if (threadIdx.x == 0) loss[s] = sl * wt;
+    sl = nt_block_sum(sl, red);
+    if (threadIdx.x == 0) lpart[(int64_t)s * LOSS_BLOCKS + blockIdx.x] = sl * wt;
+}
+
+__global__ void k_loss_finish(const double* __restrict__ lpart, int nbatch, double* __restrict__ loss) {
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= nbatch) return;
+    double t = 0.0;
+    for (int b = 0; b < LOSS_BLOCKS; ++b) t += lpart[(int64_t)s * LOSS_BLOCKS + b];
+    loss[s] = t;
 }
 
 // Squared gradient norm: partials per block, summed by k_norm_finish.
@@ -830,7 +1001,7 @@ struct Unet {
     float* go = nullptr;         // dL/do [maxb][H][W]
     float* part = nullptr;       // reduction partials
     int64_t part_cap = 0;
-    double* dloss = nullptr;     // per-sample loss
+    double* dloss = nullptr;     // per-sample loss [maxb], then partials [maxb][LOSS_BLOCKS] x 3
     // activation views (element offsets into act / grad, per-image strides)
     // C channels per pixel at pixel stride `stride`; a concatenation buffer
     // holds its two halves of C / 2 channels as planar tensors hs apart
@@ -896,28 +1067,31 @@ struct Ctx {
 // per workgroup, feed twice the MFMAs of a four-wave workgroup (0.68 against
 // 0.70 ms for the network forward on 8 images of 408 x 808; two rows per wave
 // or sixteen waves were slower, the latter spilling).
-template <int CB, int RPW, int CK, int NWV = 8>
+template <int CB, int CK, bool MASK>
 void launch_conv3(const Ctx& c, const Tv& X, int K, const bf16_t* Af, const float* bias, const Tv& Y, int M, int H,
-                  int W, bool relu) {
+                  int W, bool relu, const bf16_t* act) {
+    constexpr int RPW = 1, NWV = 8;
     // persistent grid: as many workgroups as the device holds at once
     static int resident = 0;
     if (!resident) {
         int per_cu = 0, cus = 0, dev = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_conv3<CB, RPW, CK, NWV>, 64 * NWV, 0) != hipSuccess)
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_conv3<CB, RPW, CK, NWV, MASK>, 64 * NWV, 0) != hipSuccess)
             per_cu = 1, cus = 256;
         resident = std::max(1, per_cu) * std::max(1, cus);
     }
     const int rows = NWV * RPW;
     const int64_t ntiles = (int64_t)((W + 63) / 64) * ((H + rows - 1) / rows) * c.N * (M / (16 * CB));
     const int grid = (int)std::min<int64_t>(ntiles, resident);
-    hipLaunchKernelGGL((k_conv3<CB, RPW, CK, NWV>), dim3(grid), dim3(64 * NWV), 0, c.U->stream, X.p, X.s, X.hs, X.split, K, Af,
-                       (M + 15) / 16, bias, Y.p, Y.s, Y.hs, Y.split, M, H, W, c.N, relu ? 1 : 0);
+    hipLaunchKernelGGL((k_conv3<CB, RPW, CK, NWV, MASK>), dim3(grid), dim3(64 * NWV), 0, c.U->stream, X.p, X.s, X.hs, X.split, K, Af,
+                       (M + 15) / 16, bias, Y.p, Y.s, Y.hs, Y.split, M, H, W, c.N, relu ? 1 : 0, act);
 }
 
-// K input channels (Cin, or Cout for the data gradient) to M outputs
-esi_status_t conv3(const Ctx& c, const Tv& X, int K, int layer, bool bwd, const Tv& Y, int M, int lvl, bool relu) {
+// K input channels (Cin, or Cout for the data gradient) to M outputs; act: the
+// activation whose ReLU a data gradient passes (nullptr: none)
+esi_status_t conv3(const Ctx& c, const Tv& X, int K, int layer, bool bwd, const Tv& Y, int M, int lvl, bool relu,
+                   const bf16_t* act = nullptr) {
     Unet* U = c.U;
     const Layer& Ly = U->L[layer];
     const bf16_t* Af = bwd ? Ly.wb : Ly.wf;
@@ -925,15 +1099,20 @@ esi_status_t conv3(const Ctx& c, const Tv& X, int K, int layer, bool bwd, const 
     const int H = c.h(lvl), W = c.w(lvl);
     if (K % 16 || M % 16) return fail(ESI_ERR_SHAPE, "3x3 convolution channels must be multiples of 16");
     const int cb = M >= 64 ? 4 : M / 16;
-    if (frag_ck(K) == 32) {
-        if (cb == 4) launch_conv3<4, 1, 32>(c, X, K, Af, bias, Y, M, H, W, relu);
-        else if (cb == 2) launch_conv3<2, 1, 32>(c, X, K, Af, bias, Y, M, H, W, relu);
-        else launch_conv3<1, 1, 32>(c, X, K, Af, bias, Y, M, H, W, relu);
-    } else {
-        if (cb == 4) launch_conv3<4, 1, 16>(c, X, K, Af, bias, Y, M, H, W, relu);
-        else if (cb == 2) launch_conv3<2, 1, 16>(c, X, K, Af, bias, Y, M, H, W, relu);
-        else launch_conv3<1, 1, 16>(c, X, K, Af, bias, Y, M, H, W, relu);
-    }
+    auto launch = [&](auto mask) {
+        constexpr bool MASK = decltype(mask)::value;
+        if (frag_ck(K) == 32) {
+            if (cb == 4) launch_conv3<4, 32, MASK>(c, X, K, Af, bias, Y, M, H, W, relu, act);
+            else if (cb == 2) launch_conv3<2, 32, MASK>(c, X, K, Af, bias, Y, M, H, W, relu, act);
+            else launch_conv3<1, 32, MASK>(c, X, K, Af, bias, Y, M, H, W, relu, act);
+        } else {
+            if (cb == 4) launch_conv3<4, 16, MASK>(c, X, K, Af, bias, Y, M, H, W, relu, act);
+            else if (cb == 2) launch_conv3<2, 16, MASK>(c, X, K, Af, bias, Y, M, H, W, relu, act);
+            else launch_conv3<1, 16, MASK>(c, X, K, Af, bias, Y, M, H, W, relu, act);
+        }
+    };
+    if (act) launch(std::true_type{});
+    else launch(std::false_type{});
     ESI_HIP_TRY(hipGetLastError());
     return ESI_OK;
 }
@@ -942,27 +1121,44 @@ esi_status_t need_part(Unet* U, int64_t n) {
     return grow_t(&U->part, &U->part_cap, n, U->stream);
 }
 
-// weight + bias gradient of a 3x3 layer into gflat
-esi_status_t conv3_wgrad(const Ctx& c, const Tv& GY, int Cout, const Tv& X, int Cin, int cin_real, int lvl,
-                         float* gflat) {
+// Chunks of a weight gradient: as many workgroups as two per CU over the
+// channel tiles, each with the same number of pixel tiles (but the last).
+int wgrad_chunks(int ntiles, int channel_tiles) {
+    const int want = std::max(1, std::min(ntiles, 512 / channel_tiles));
+    const int each = (ntiles + want - 1) / want;
+    return (ntiles + each - 1) / each;
+}
+
+template <int CB, int IB, int ROWS>
+esi_status_t launch_conv3_wgrad(const Ctx& c, const Tv& GY, int Cout, const Tv& X, int Cin, int cin_real, int H, int W,
+                                float* gflat) {
     Unet* U = c.U;
-    const int H = c.h(lvl), W = c.w(lvl);
-    const int nrows = c.N * H;
-    const int nblocks = (Cout / 16) * (Cin / 16);
-    const int want = std::max(1, std::min(nrows, 2048 / nblocks));
-    const int rpc = (nrows + want - 1) / want;
-    const int nchunks = (nrows + rpc - 1) / rpc;
-    const int64_t np = (int64_t)nchunks * 9 * Cout * Cin;
-    ESI_TRY(need_part(U, np + (int64_t)nchunks * Cout));
+    const int ct = (Cout / (16 * CB)) * (Cin / (16 * IB));
+    const int nchunks = wgrad_chunks(((W + 63) / 64) * ((H + ROWS - 1) / ROWS) * c.N, ct);
+    const int64_t per = (int64_t)9 * Cout * Cin;
+    ESI_TRY(need_part(U, nchunks * (per + Cout)));
     float* part = U->part;
-    float* bpart = U->part + np;
-    hipLaunchKernelGGL(k_conv3_wgrad, dim3(nchunks, nblocks), dim3(64), 0, U->stream, GY.p, GY.s, Cout, X.p, X.s,
-                       X.hs, X.split, Cin, H, W, nrows, rpc, part, bpart);
-    const int64_t nout = (int64_t)9 * Cout * Cin + Cout;
-    hipLaunchKernelGGL(k_conv3_wgrad_reduce, dim3(grid_for(nout)), dim3(NT), 0, U->stream, part, bpart, nchunks,
-                       Cout, Cin, cin_real, gflat);
+    float* bpart = U->part + nchunks * per;
+    hipLaunchKernelGGL((k_conv3_wgrad<CB, IB, ROWS>), dim3(nchunks, ct), dim3(NT), 0, U->stream, GY.p, GY.s, Cout, X.p,
+                       X.s, X.hs, X.split, Cin, H, W, c.N, part, bpart);
+    hipLaunchKernelGGL(k_wgrad_reduce<false>, dim3((int)((per + Cout + 63) / 64)), dim3(1024), 0, U->stream, part,
+                       bpart, nchunks, 9, Cout, Cin, cin_real, Cout, gflat);
     ESI_HIP_TRY(hipGetLastError());
     return ESI_OK;
+}
+
+// weight + bias gradient of a 3x3 layer into gflat: channel tiles of 32 x 32,
+// or 16 where a side has no more (16 x 16 is bound by memory: taller tiles
+// stage less halo)
+esi_status_t conv3_wgrad(const Ctx& c, const Tv& GY, int Cout, const Tv& X, int Cin, int cin_real, int lvl,
+                         float* gflat) {
+    const int H = c.h(lvl), W = c.w(lvl);
+    if (Cout % 16 || Cin % 16 || (Cout > 16 && Cout % 32) || (Cin > 16 && Cin % 32) || X.split % 8)
+        return fail(ESI_ERR_SHAPE, "weight-gradient channels outside the supported set");
+    if (Cout == 16 && Cin == 16) return launch_conv3_wgrad<1, 1, 8>(c, GY, Cout, X, Cin, cin_real, H, W, gflat);
+    if (Cout == 16) return launch_conv3_wgrad<1, 2, 4>(c, GY, Cout, X, Cin, cin_real, H, W, gflat);
+    if (Cin == 16) return launch_conv3_wgrad<2, 1, 4>(c, GY, Cout, X, Cin, cin_real, H, W, gflat);
+    return launch_conv3_wgrad<2, 2, 4>(c, GY, Cout, X, Cin, cin_real, H, W, gflat);
 }
 
 template <int CB, int NKC>
@@ -988,8 +1184,28 @@ esi_status_t convT_fwd(const Ctx& c, int layer, const bf16_t* X, int sx, bf16_t*
     return ESI_OK;
 }
 
+template <int CB, int IB>
+esi_status_t launch_convT_wgrad(const Ctx& c, const Layer& Ly, const bf16_t* X, int sx, const bf16_t* GY, int sg,
+                                int Hi, int Wi, float* gflat) {
+    Unet* U = c.U;
+    const int ct = (Ly.cout / (16 * CB)) * (Ly.cin / (16 * IB));
+    const int nchunks = wgrad_chunks(((Wi + 63) / 64) * ((Hi + 1) / 2) * c.N, ct);
+    const int64_t per = (int64_t)4 * Ly.cout * Ly.cin;
+    ESI_TRY(need_part(U, nchunks * (per + Ly.cout)));
+    float* part = U->part;
+    float* bpart = U->part + nchunks * per;
+    hipLaunchKernelGGL((k_convT_wgrad<CB, IB>), dim3(nchunks, ct), dim3(NT), 0, U->stream, X, sx, Ly.cin, GY, sg,
+                       Ly.cout, Hi, Wi, c.N, part, bpart);
+    hipLaunchKernelGGL(k_wgrad_reduce<true>, dim3((int)((per + Ly.cout + 63) / 64)), dim3(1024), 0, U->stream, part,
+                       bpart, nchunks, 4, Ly.cout, Ly.cin, Ly.cin, Ly.cout, gflat);
+    ESI_HIP_TRY(hipGetLastError());
+    return ESI_OK;
+}
+
+// weight + bias gradient of a transposed convolution and the gradient of its
+// input, masked by that activation's ReLU (act)
 esi_status_t convT_back(const Ctx& c, int layer, const bf16_t* X, int sx, const bf16_t* GY, int sg,
-                        bf16_t* GX, int sgx, int lvl_in, float* gflat) {
+                        bf16_t* GX, int sgx, int lvl_in, const bf16_t* act, float* gflat) {
     Unet* U = c.U;
     const Layer& Ly = U->L[layer];
     const int Hi = c.h(lvl_in), Wi = c.w(lvl_in);
@@ -998,39 +1214,21 @@ esi_status_t convT_back(const Ctx& c, int layer, const bf16_t* X, int sx, const 
         dim3 grid((Wi + 63) / 64, (Hi + 3) / 4, c.N * (Ly.cin / (16 * cb)));
         if (cb == 4)
             hipLaunchKernelGGL(k_convT_dgrad_mfma<4>, grid, dim3(NT), 0, U->stream, GY, sg, Ly.cout, Ly.wb, GX,
-                               sgx, Ly.cin, Hi, Wi);
+                               sgx, Ly.cin, Hi, Wi, act);
         else
             hipLaunchKernelGGL(k_convT_dgrad_mfma<2>, grid, dim3(NT), 0, U->stream, GY, sg, Ly.cout, Ly.wb, GX,
-                               sgx, Ly.cin, Hi, Wi);
+                               sgx, Ly.cin, Hi, Wi, act);
     }
-    const int nrows = c.N * Hi;
-    const int nblocks = (Ly.cout / 16) * (Ly.cin / 16);
-    const int want = std::max(1, std::min(nrows, 2048 / nblocks));
-    const int rpc = (nrows + want - 1) / want;
-    const int nchunks = (nrows + rpc - 1) / rpc;
-    const int64_t per = (int64_t)4 * Ly.cout * Ly.cin;
-    ESI_TRY(need_part(U, nchunks * per + (int64_t)nchunks * Ly.cout));
-    float* part = U->part;
-    float* bpart = U->part + nchunks * per;
-    hipLaunchKernelGGL(k_convT_wgrad_mfma, dim3(nchunks, nblocks), dim3(64), 0, U->stream, X, sx, Ly.cin, GY, sg,
-                       Ly.cout, Hi, Wi, nrows, rpc, part, bpart);
-    hipLaunchKernelGGL(k_convT_wgrad_reduce, dim3(grid_for(per + Ly.cout)), dim3(NT), 0, U->stream, part, bpart,
-                       nchunks, Ly.cout, Ly.cin, gflat + Ly.off);
-    ESI_HIP_TRY(hipGetLastError());
-    return ESI_OK;
+    if (Ly.cin % 32 || Ly.cout % 16 || (Ly.cout > 16 && Ly.cout % 32))
+        return fail(ESI_ERR_SHAPE, "transposed convolution channels outside the supported set");
+    if (Ly.cout == 16) return launch_convT_wgrad<1, 2>(c, Ly, X, sx, GY, sg, Hi, Wi, gflat + Ly.off);
+    return launch_convT_wgrad<2, 2>(c, Ly, X, sx, GY, sg, Hi, Wi, gflat + Ly.off);
 }
 
 esi_status_t pool(const Ctx& c, const bf16_t* X, int sx, bf16_t* Y, int sy, int C, int lvl_in) {
     const int64_t n = c.pix(lvl_in + 1) * (C / 8);
     hipLaunchKernelGGL(k_pool, dim3(grid_for(n)), dim3(NT), 0, c.U->stream, X, sx, Y, sy, C, c.N,
                        c.h(lvl_in + 1), c.w(lvl_in + 1));
-    ESI_HIP_TRY(hipGetLastError());
-    return ESI_OK;
-}
-
-esi_status_t mask(const Ctx& c, bf16_t* G, int sg, const bf16_t* Y, int sa, int C, int lvl) {
-    const int64_t n = c.pix(lvl) * C;
-    hipLaunchKernelGGL(k_relu_mask, dim3(grid_for(n)), dim3(NT), 0, c.U->stream, G, sg, Y, sa, C, c.pix(lvl));
     ESI_HIP_TRY(hipGetLastError());
     return ESI_OK;
 }
@@ -1077,46 +1275,41 @@ esi_status_t backward(const Ctx& c, float* gflat) {
     // output layer: g_d1b = bf16(w go) masked by d1b > 0; weight / bias sums
     {
         const int64_t npx = c.pix(0);
-        const int nchunks = (int)std::max<int64_t>(1, std::min<int64_t>(1024, npx / 4096));
+        const int nchunks = (int)std::max<int64_t>(1, std::min<int64_t>(1024, npx / 1024));
         const int64_t ppc = (npx + nchunks - 1) / nchunks;
         ESI_TRY(need_part(U, (int64_t)nchunks * 17));
         const Layer& Lo = U->L[OUT];
         hipLaunchKernelGGL(k_out_back, dim3(nchunks), dim3(NT), 0, U->stream, U->go, c.a(A_D1B), 16, Lo.wf,
                            c.g(A_D1B), 16, npx, ppc, U->part);
-        hipLaunchKernelGGL(k_sum_chunks, dim3(1), dim3(NT), 0, U->stream, U->part, nchunks, (int64_t)17,
-                           gflat + Lo.off);
+        // 16 weights and the bias: as a 1-tap layer of 17 input channels
+        hipLaunchKernelGGL(k_wgrad_reduce<true>, dim3(1), dim3(1024), 0, U->stream, U->part, U->part, nchunks, 1, 1, 17,
+                           17, 0, gflat + Lo.off);
         ESI_HIP_TRY(hipGetLastError());
     }
     // weight gradient of a 3x3 layer from its output gradient GY and input X,
-    // then (GX.p non-null) the gradient of its input
-    auto conv_back = [&](int layer, const Tv& GY, int Cout, const Tv& X, int Cin, int lvl,
-                         const Tv& GX) -> esi_status_t {
+    // then (GX.p non-null) the gradient of its input, masked by the ReLU of act
+    // (the input itself, when that is another layer's output)
+    auto conv_back = [&](int layer, const Tv& GY, int Cout, const Tv& X, int Cin, int lvl, const Tv& GX,
+                         const bf16_t* act = nullptr) -> esi_status_t {
         const Layer& Ly = U->L[layer];
         ESI_TRY(conv3_wgrad(c, GY, Cout, X, Cin, Ly.cin, lvl, gflat + Ly.off));
-        if (GX.p) ESI_TRY(conv3(c, GY, Cout, layer, true, GX, Cin, lvl, false));
+        if (GX.p) ESI_TRY(conv3(c, GY, Cout, layer, true, GX, Cin, lvl, false, act));
         return ESI_OK;
     };
     // level 1 decoder: d1b, d1a (d1b's gradient is already masked)
-    ESI_TRY(conv_back(D1B, c.gt(A_D1B), 16, c.at(A_D1A), 16, 0, c.gt(A_D1A)));
-    ESI_TRY(mask(c, c.g(A_D1A), 16, c.a(A_D1A), 16, 16, 0));
+    ESI_TRY(conv_back(D1B, c.gt(A_D1B), 16, c.at(A_D1A), 16, 0, c.gt(A_D1A), c.a(A_D1A)));
     ESI_TRY(conv_back(D1A, c.gt(A_D1A), 16, c.at(A_CAT1), 32, 0, c.gt(A_CAT1)));
-    ESI_TRY(convT_back(c, U1, c.a(A_D2B), 32, c.gh(A_CAT1, 0), 16, c.g(A_D2B), 32, 1, gflat));
+    ESI_TRY(convT_back(c, U1, c.a(A_D2B), 32, c.gh(A_CAT1, 0), 16, c.g(A_D2B), 32, 1, c.a(A_D2B), gflat));
     // level 2 decoder
-    ESI_TRY(mask(c, c.g(A_D2B), 32, c.a(A_D2B), 32, 32, 1));
-    ESI_TRY(conv_back(D2B, c.gt(A_D2B), 32, c.at(A_D2A), 32, 1, c.gt(A_D2A)));
-    ESI_TRY(mask(c, c.g(A_D2A), 32, c.a(A_D2A), 32, 32, 1));
+    ESI_TRY(conv_back(D2B, c.gt(A_D2B), 32, c.at(A_D2A), 32, 1, c.gt(A_D2A), c.a(A_D2A)));
     ESI_TRY(conv_back(D2A, c.gt(A_D2A), 32, c.at(A_CAT2), 64, 1, c.gt(A_CAT2)));
-    ESI_TRY(convT_back(c, U2, c.a(A_D3B), 64, c.gh(A_CAT2, 0), 32, c.g(A_D3B), 64, 2, gflat));
+    ESI_TRY(convT_back(c, U2, c.a(A_D3B), 64, c.gh(A_CAT2, 0), 32, c.g(A_D3B), 64, 2, c.a(A_D3B), gflat));
     // level 3 decoder
-    ESI_TRY(mask(c, c.g(A_D3B), 64, c.a(A_D3B), 64, 64, 2));
-    ESI_TRY(conv_back(D3B, c.gt(A_D3B), 64, c.at(A_D3A), 64, 2, c.gt(A_D3A)));
-    ESI_TRY(mask(c, c.g(A_D3A), 64, c.a(A_D3A), 64, 64, 2));
+    ESI_TRY(conv_back(D3B, c.gt(A_D3B), 64, c.at(A_D3A), 64, 2, c.gt(A_D3A), c.a(A_D3A)));
     ESI_TRY(conv_back(D3A, c.gt(A_D3A), 64, c.at(A_CAT3), 128, 2, c.gt(A_CAT3)));
-    ESI_TRY(convT_back(c, U3, c.a(A_B4), 128, c.gh(A_CAT3, 0), 64, c.g(A_B4), 128, 3, gflat));
+    ESI_TRY(convT_back(c, U3, c.a(A_B4), 128, c.gh(A_CAT3, 0), 64, c.g(A_B4), 128, 3, c.a(A_B4), gflat));
     // bottleneck
-    ESI_TRY(mask(c, c.g(A_B4), 128, c.a(A_B4), 128, 128, 3));
-    ESI_TRY(conv_back(C4B, c.gt(A_B4), 128, c.at(A_A4), 128, 3, c.gt(A_A4)));
-    ESI_TRY(mask(c, c.g(A_A4), 128, c.a(A_A4), 128, 128, 3));
+    ESI_TRY(conv_back(C4B, c.gt(A_B4), 128, c.at(A_A4), 128, 3, c.gt(A_A4), c.a(A_A4)));
     ESI_TRY(conv_back(C4A, c.gt(A_A4), 128, c.at(A_P3), 64, 3, c.gt(A_P3)));
     // encoder levels: gradient into e_l = pool path + skip, masked by e_l > 0;
     // the e_l gradient goes into the skip half of the concat gradient buffer
@@ -1125,14 +1318,12 @@ esi_status_t backward(const Ctx& c, float* gflat) {
                         {1, 32, A_CAT2, A_P2, A_A2, C2B, C2A, A_P1},
                         {0, 16, A_CAT1, A_P1, A_A1, C1B, C1A, A_X}};
     for (const Enc& e : enc) {
-        const int64_t n = c.pix(e.lvl) * e.ch;
-        hipLaunchKernelGGL(k_pool_back, dim3(grid_for(n)), dim3(NT), 0, U->stream, c.g(e.p), e.ch,
-                           c.gh(e.cat, 1), e.ch, c.ah(e.cat, 1), e.ch, c.gh(e.cat, 1), e.ch,
-                           e.ch, c.N, c.h(e.lvl), c.w(e.lvl));
+        const int64_t n = c.pix(e.lvl) * (e.ch / 8);
+        hipLaunchKernelGGL(k_pool_back, dim3(grid_for(n)), dim3(NT), 0, U->stream, c.g(e.p), c.gh(e.cat, 1),
+                           c.ah(e.cat, 1), c.gh(e.cat, 1), e.ch, c.N, c.h(e.lvl), c.w(e.lvl));
         ESI_HIP_TRY(hipGetLastError());
         const int cin_a = e.lvl == 0 ? 16 : e.ch / 2;
-        ESI_TRY(conv_back(e.cb, T(c.gh(e.cat, 1), e.ch), e.ch, c.at(e.a), e.ch, e.lvl, c.gt(e.a)));
-        ESI_TRY(mask(c, c.g(e.a), e.ch, c.a(e.a), e.ch, e.ch, e.lvl));
+        ESI_TRY(conv_back(e.cb, T(c.gh(e.cat, 1), e.ch), e.ch, c.at(e.a), e.ch, e.lvl, c.gt(e.a), c.a(e.a)));
         ESI_TRY(conv_back(e.ca, c.gt(e.a), e.ch, c.at(e.pin), cin_a, e.lvl,
                           e.lvl == 0 ? Tv{nullptr, 0} : c.gt(e.pin)));
     }
@@ -1228,7 +1419,7 @@ extern "C" esi_status_t esi_unet_create(esi_unet_t* out, int32_t H, int32_t W, i
         hipMalloc(&U->v, U->P * 4) != hipSuccess || hipMalloc(&U->act, aoff * 2) != hipSuccess ||
         hipMalloc(&U->grad, aoff * 2) != hipSuccess ||
         hipMalloc(&U->go, (int64_t)max_batch * H * W * 4) != hipSuccess ||
-        hipMalloc(&U->dloss, (int64_t)max_batch * 8) != hipSuccess)
+        hipMalloc(&U->dloss, (int64_t)max_batch * (1 + 3 * LOSS_BLOCKS) * 8) != hipSuccess)
         return fail_oom();
     for (Layer& Ly : U->L) {
         const int cpad = Ly.cin < 16 ? 16 : Ly.cin;
@@ -1312,8 +1503,13 @@ extern "C" esi_status_t esi_unet_loss_grad(esi_unet_t u, const float* x, const f
     ESI_TRY(grow_t(&U->part, &U->part_cap, (int64_t)batch * npix, U->stream));   // o scratch
     float* o = U->part;
     ESI_TRY(forward(c, x, o));
-    hipLaunchKernelGGL(k_scaling_loss, dim3(batch), dim3(NT), 0, U->stream, o, a, cc, weight, npix, batch, U->go,
-                       U->dloss);
+    double* sums = U->dloss + U->maxb;                     // [batch][LOSS_BLOCKS][2], then the loss partials
+    double* lpart = sums + (int64_t)U->maxb * LOSS_BLOCKS * 2;
+    if (!weight)
+        hipLaunchKernelGGL(k_loss_sums, dim3(LOSS_BLOCKS, batch), dim3(NT), 0, U->stream, a, cc, npix, sums);
+    hipLaunchKernelGGL(k_scaling_loss, dim3(LOSS_BLOCKS, batch), dim3(NT), 0, U->stream, o, a, cc, weight, sums, npix,
+                       batch, U->go, lpart);
+    hipLaunchKernelGGL(k_loss_finish, dim3((batch + 63) / 64), dim3(64), 0, U->stream, lpart, batch, U->dloss);
     ESI_HIP_TRY(hipGetLastError());
     ESI_TRY(backward(c, grad));
     if (loss) {
