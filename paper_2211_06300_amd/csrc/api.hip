@@ -11,7 +11,6 @@ namespace esi {
 
 esi_status_t launch_step2d(Plan* P, unsigned flags, const StepArgs& a, int shape);
 int step2d_loop_shape(unsigned flags, int shape, int64_t fsize);
-void step2d_tile_shape(int* tx, int* tz);
 void step2d_shape_tile(int shape, int* tx, int* tz);
 esi_status_t launch_step3d(Plan* P, unsigned flags, const StepArgs& a);
 esi_status_t launch_step3d_t2(Plan* P, unsigned flags, const StepArgs& a);
@@ -31,10 +30,7 @@ esi_status_t check_shots(Plan* P, int shot0, int nshots) {
 }
 
 esi_status_t lists_for(Plan* P, TileLists** L) {
-    int tx, ty = 1, tz;
-    if (P->ndim == 2) step2d_tile_shape(&tx, &tz);
-    else step3d_tile_shape(&tx, &ty, &tz);
-    return get_lists(P, tx, tz, ty, L);
+    return shape_lists(P, LS_ONE, L);
 }
 
 esi_status_t launch_step(Plan* P, unsigned flags, const StepArgs& a, int shape) {
@@ -85,14 +81,17 @@ int loop_shape(Plan* P, unsigned flags, bool adjoint, int shot0, int nshots) {
 void shape_tile(Plan* P, int shape, int* tx, int* ty, int* tz) {
     *ty = 1;
     if (P->ndim == 2) step2d_shape_tile(shape, tx, tz);
-    else if (shape == LS_ONE) step3d_tile_shape(tx, ty, tz);
+    else if (shape == LS_ONE) {
+        step3d_tile_shape(tx, ty, tz);
+        *tz = P->chunk3d;
+    }
     else step3d_t2_tile_shape(tx, ty, tz);
 }
 
 esi_status_t shape_lists(Plan* P, int shape, TileLists** L) {
     int tx, ty, tz;
     shape_tile(P, shape, &tx, &ty, &tz);
-    return get_lists(P, tx, tz, ty, L);
+    return get_lists(P, tx, tz, ty, shape != LS_ONE, L);
 }
 
 int max_tiles(Plan* P) {
@@ -115,6 +114,7 @@ esi_status_t loop_lists(Plan* P, unsigned fflags, unsigned aflags, int shot0, in
 // Point the tile fields and sparse lists of `a` at the tiling `L`.
 void apply_lists(StepArgs& a, const TileLists* L) {
     a.tiles_x = L->tiles_x; a.tiles_y = L->tiles_y; a.tiles_z = L->tiles_z; a.tiles = L->tiles;
+    a.chunk = L->tz;
     a.inj_ptr = L->inj_ptr; a.inj_cell = L->inj_cell; a.inj_rptr = L->inj_rptr; a.inj_rid = L->inj_rid;
     a.gat_ptr = L->gat_ptr; a.gat_cell = L->gat_cell; a.gat_rid = L->gat_rid;
     a.src_tile = L->src_tile; a.src_cell = L->src_cell;

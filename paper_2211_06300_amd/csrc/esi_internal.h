@@ -103,6 +103,7 @@ struct Plan {
     int nzp = 0, nyp = 1, nxp = 0;       // padded grid
     int ZS = 0, YS = 1, XS = 0;          // storage grid (padded + zero ghost halo)
     int64_t fsize = 0;                   // floats per stored field (one shot)
+    int chunk3d = 0;                     // planes per chunk of the one-step 3D kernel
     int64_t nphys = 0;                   // physical cells
     hipStream_t stream = nullptr;
     int device = 0;
@@ -201,8 +202,9 @@ esi_status_t grow_t(T** p, int64_t* cap_elems, int64_t need_elems, hipStream_t s
     return s;
 }
 
-// Lists for a tile shape (built on first use).
-esi_status_t get_lists(Plan* P, int tx, int tz, int ty, TileLists** out);
+// Lists for a tile shape (built on first use); grown: with the injection cells
+// of the grown tile, which two-step launches read.
+esi_status_t get_lists(Plan* P, int tx, int tz, int ty, bool grown, TileLists** out);
 
 // Look up the no-allocation scratch array of `device` (current) once per
 // process; called when a plan is created (noalloc.hip).
@@ -234,6 +236,7 @@ struct StepArgs {
     int step;                // n (forward) or j (adjoint)
     int nt;
     int tiles_x, tiles_y, tiles_z, tiles;   // per shot
+    int chunk;               // planes (3D) or rows (2D) of a tile
     int nshots;
     int shot0;               // global index of the first shot
     const int32_t* src_pos;  // [global shots][3]

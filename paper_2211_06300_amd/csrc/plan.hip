@@ -13,6 +13,7 @@
 namespace esi {
 
 void step3d_tile_shape(int* tx, int* ty, int* tz);   // step3d.hip
+int step3d_chunk(int nxp, int nyp, int nzp, int64_t plane, int nshots);
 
 static thread_local std::string g_err;
 
@@ -187,8 +188,8 @@ static esi_status_t set_model(Plan* P, const float* vel, bool first, double eta_
 }
 
 // ---- per-tile lists -------------------------------------------------------------
-esi_status_t get_lists(Plan* P, int tx, int tz, int ty, TileLists** out) {
-    for (TileLists* L : P->lists)
+esi_status_t get_lists(Plan* P, int tx, int tz, int ty, bool grown, TileLists** out) {
+    for (TileLists* L : P->lists)   // (one- and two-step tiles differ in width)
         if (L->tx == tx && L->tz == tz && L->ty == ty) { *out = L; return ESI_OK; }
     TileLists* L = new (std::nothrow) TileLists();
     if (!L) return fail(ESI_ERR_OOM, "host allocation failed");
@@ -213,7 +214,7 @@ esi_status_t get_lists(Plan* P, int tx, int tz, int ty, TileLists** out) {
     // grown-tile injection lists: a receiver belongs to every tile whose region
     // grown by one stencil radius, [x0-4, x0+tx+4) x [z0-4, z0+tz+4)
     // (x [y0-4, y0+ty+4) in 3D), holds it; cells are indexed on the grown tile
-    std::vector<int32_t> inj2_ptr((size_t)S * (T + 1)), inj2_cell, inj2_rptr{0}, inj2_rid;
+    std::vector<int32_t> inj2_ptr(grown ? (size_t)S * (T + 1) : 0), inj2_cell, inj2_rptr{0}, inj2_rid;
     const int gw = tx + 2 * HALO, gh = tz + 2 * HALO, gy3 = ty + 2 * HALO;
     for (int s = 0; s < S; ++s) {
         int64_t r0 = P->h_rec_ptr[s], r1 = P->h_rec_ptr[s + 1];
@@ -248,7 +249,7 @@ esi_status_t get_lists(Plan* P, int tx, int tz, int ty, TileLists** out) {
         }
         ip[T] = (int32_t)inj_cell.size();
         gp[T] = (int32_t)gat_cell.size();
-        {
+        if (grown) {
             // (tile, grown cell, rid) for every tile region holding each receiver
             std::vector<std::array<int32_t, 3>> g2;
             for (int64_t r = r0; r < r1; ++r) {
@@ -445,6 +446,7 @@ extern "C" esi_status_t esi_plan_create(esi_plan_t* plan, const esi_grid_t* g, c
     lap_weights(w);
     for (int k = 0; k < 5; ++k) P->lap_w[k] = (float)w[k];
     P->nshots = geo->nshots;
+    if (nd == 3) P->chunk3d = step3d_chunk(P->nxp, P->nyp, P->nzp, (int64_t)P->XS * P->YS, P->nshots);
     P->h_src.assign(geo->src, geo->src + (size_t)geo->nshots * nd);
     P->h_rec_ptr.assign(geo->rec_ptr, geo->rec_ptr + geo->nshots + 1);
     if (geo->window) P->h_win.assign(geo->window, geo->window + 2 * (size_t)geo->nshots);

@@ -1166,7 +1166,6 @@ int step2d_loop_shape(unsigned flags, int shape, int64_t fsize) {
     return shape != LS_ONE && !tuned_variant(flags) ? LS_T2_32 : shape;
 }
 
-void step2d_tile_shape(int* tx, int* tz) { *tx = TX; *tz = TZ; }
 void step2d_shape_tile(int shape, int* tx, int* tz) {
     *tx = shape == LS_ONE ? TX : T2W;
     switch (shape) {
