@@ -17,6 +17,7 @@
 // the step kernel, so both ways give the same bits.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "esi_internal.h"
@@ -42,10 +43,14 @@ __device__ __forceinline__ double block_sum(double v, double* sm) {
 }
 
 // out = acc + beta W (F G) p per cell, and part[s][b] = block sums of p . out.
-__global__ __launch_bounds__(NT) void k_dtft_finish(const float2* __restrict__ acc, const float2* __restrict__ p,
+// NFC frequencies at most: a cell's slices stay in registers (indexed by a
+// runtime count they went through scratch memory: with 20 workgroups a shot, 338
+// us on 4 shots of 401 x 201 and 8 frequencies, now 18).
+template <int NFC>
+__global__ __launch_bounds__(NT) void k_dtft_finish(const float2* acc, const float2* __restrict__ p,
                                                     const double* __restrict__ C, int nf, int nz, int ny, int nx,
                                                     const int32_t* __restrict__ src, int shot0, double beta,
-                                                    double b_eps, int w_identity, float2* __restrict__ out,
+                                                    double b_eps, int w_identity, float2* out,   // may be acc
                                                     double* __restrict__ part) {
     __shared__ double sm[NT / 64];
     const int s = blockIdx.y, b = blockIdx.x, bps = gridDim.x;
@@ -62,61 +67,109 @@ __global__ __launch_bounds__(NT) void k_dtft_finish(const float2* __restrict__ a
             const double bb = sqrt(dx * dx + dz * dz + dy * dy) + b_eps;
             w = beta * bb * bb;
         }
-        double pv[2 * MAX_NF];
-        for (int m = 0; m < nf; ++m) {
-            const float2 v = p[base + m * n + c];
-            pv[2 * m] = v.x;
-            pv[2 * m + 1] = v.y;
-        }
+        float2 pv[NFC];
+#pragma unroll
+        for (int m = 0; m < NFC; ++m) pv[m] = m < nf ? p[base + m * n + c] : make_float2(0.f, 0.f);
         for (int k = 0; k < nf; ++k) {
             double cr = 0.0, ci = 0.0;
-            for (int j = 0; j < 2 * nf; ++j) {
-                cr += C[(2 * k) * (2 * nf) + j] * pv[j];
-                ci += C[(2 * k + 1) * (2 * nf) + j] * pv[j];
+#pragma unroll
+            for (int m = 0; m < NFC; ++m) {
+                if (m >= nf) break;   // uniform
+                cr += C[(2 * k) * (2 * nf) + 2 * m] * (double)pv[m].x;
+                cr += C[(2 * k) * (2 * nf) + 2 * m + 1] * (double)pv[m].y;
+                ci += C[(2 * k + 1) * (2 * nf) + 2 * m] * (double)pv[m].x;
+                ci += C[(2 * k + 1) * (2 * nf) + 2 * m + 1] * (double)pv[m].y;
             }
-            const float2 a = acc[base + k * n + c];
+            const float2 a = acc[base + k * n + c], pk = p[base + k * n + c];
             float2 o;
             o.x = (float)((double)a.x + w * cr);
             o.y = (float)((double)a.y + w * ci);
             out[base + k * n + c] = o;
-            dot += pv[2 * k] * (double)o.x + pv[2 * k + 1] * (double)o.y;
+            dot += (double)pk.x * (double)o.x + (double)pk.y * (double)o.y;
         }
     }
     const double t = block_sum(dot, sm);
     if (threadIdx.x == 0) part[(int64_t)s * bps + b] = t;
 }
 
-// d_out = G F d_in per receiver trace (the data represented through the
-// inverse DTFT of their DTFT); one thread per receiver of the call's shots.
-__global__ void k_data_band(const float* __restrict__ din, float* __restrict__ dout,
-                            const int64_t* __restrict__ rec_ptr, int shot0, int nshots, int nt,
-                            const float2* __restrict__ tw, int nf, double inv_nt) {
+// d_out = G F d_in per receiver trace (the data represented through the inverse
+// DTFT of their DTFT), in two kernels over the receivers of the call's shots (64
+// a workgroup, one a lane): the DTFT F[receiver][m] = (re, im) in float64, its
+// sums over 16 interleaved slices of the time axis added in order, then the
+// series.  (One thread per receiver for both took 1.47 ms on 804 receivers of
+// 600 steps, now 98 us.)
+struct Trace {
+    int64_t off;      // of its first sample
+    int64_t stride;   // of the following ones
+};
+__device__ __forceinline__ Trace trace_of(const int64_t* __restrict__ rec_ptr, int shot0, int nt, int64_t r) {
     const int64_t base = rec_ptr[shot0];
-    const int64_t nr = rec_ptr[shot0 + nshots] - base;
-    for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < nr; r += (int64_t)gridDim.x * blockDim.x) {
-        int s = 0;
-        while (rec_ptr[shot0 + s + 1] <= base + r) ++s;
-        const int64_t nrs = rec_ptr[shot0 + s + 1] - rec_ptr[shot0 + s];
-        const int64_t col = base + r - rec_ptr[shot0 + s];
-        const int64_t off = (int64_t)nt * (rec_ptr[shot0 + s] - base) + col;
-        double fr[MAX_NF], fi[MAX_NF];
-        for (int m = 0; m < nf; ++m) fr[m] = fi[m] = 0.0;
-        for (int t = 0; t < nt; ++t) {
-            const double v = din[off + (int64_t)t * nrs];
-            for (int m = 0; m < nf; ++m) {
-                const float2 w = tw[(int64_t)t * nf + m];
-                fr[m] += v * (double)w.x;
-                fi[m] += v * (double)w.y;
+    int s = 0;
+    while (rec_ptr[shot0 + s + 1] <= base + r) ++s;
+    const int64_t col = base + r - rec_ptr[shot0 + s];
+    return {(int64_t)nt * (rec_ptr[shot0 + s] - base) + col, rec_ptr[shot0 + s + 1] - rec_ptr[shot0 + s]};
+}
+
+constexpr int BAND_F = 8, BAND_W = 16;   // frequencies a launch row takes, slices of the time axis
+
+__global__ __launch_bounds__(64 * BAND_W) void k_data_dtft(const float* __restrict__ din,
+                                                           const int64_t* __restrict__ rec_ptr, int shot0, int64_t nr,
+                                                           int nt, const float2* __restrict__ tw, int nf,
+                                                           double2* __restrict__ F) {
+    __shared__ double2 sm[BAND_W / 2][BAND_F][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, m0 = blockIdx.y * BAND_F;
+    const int64_t r = blockIdx.x * (int64_t)64 + lane;
+    double2 f[BAND_F];
+#pragma unroll
+    for (int m = 0; m < BAND_F; ++m) f[m] = make_double2(0.0, 0.0);
+    if (r < nr) {
+        const Trace tr = trace_of(rec_ptr, shot0, nt, r);
+#pragma unroll 4
+        for (int t = wv; t < nt; t += BAND_W) {
+            const double v = din[tr.off + (int64_t)t * tr.stride];
+#pragma unroll
+            for (int m = 0; m < BAND_F; ++m) {
+                if (m0 + m < nf) {
+                    const float2 w = tw[(int64_t)t * nf + m0 + m];
+                    f[m].x += v * (double)w.x;
+                    f[m].y += v * (double)w.y;
+                }
             }
         }
-        for (int t = 0; t < nt; ++t) {
-            double q = 0.0;
-            for (int m = 0; m < nf; ++m) {
-                const float2 w = tw[(int64_t)t * nf + m];
-                q += fr[m] * (double)w.x + fi[m] * (double)w.y;
+    }
+    for (int h = BAND_W / 2; h > 0; h >>= 1) {   // slices w and w + h
+        __syncthreads();
+        if (wv >= h && wv < 2 * h)
+#pragma unroll
+            for (int m = 0; m < BAND_F; ++m) sm[wv - h][m][lane] = f[m];
+        __syncthreads();
+        if (wv < h)
+#pragma unroll
+            for (int m = 0; m < BAND_F; ++m) {
+                f[m].x += sm[wv][m][lane].x;
+                f[m].y += sm[wv][m][lane].y;
             }
-            dout[off + (int64_t)t * nrs] = (float)(q * inv_nt);
+    }
+    if (wv == 0 && r < nr)
+#pragma unroll
+        for (int m = 0; m < BAND_F; ++m)
+            if (m0 + m < nf) F[r * nf + m0 + m] = f[m];
+}
+
+__global__ __launch_bounds__(64) void k_data_series(const double2* __restrict__ F, float* __restrict__ dout,
+                                                    const int64_t* __restrict__ rec_ptr, int shot0, int64_t nr, int nt,
+                                                    const float2* __restrict__ tw, int nf, double inv_nt) {
+    const int64_t r = blockIdx.x * (int64_t)64 + threadIdx.x;
+    if (r >= nr) return;
+    const Trace tr = trace_of(rec_ptr, shot0, nt, r);
+    for (int t = blockIdx.y; t < nt; t += gridDim.y) {
+        double q = 0.0;
+        for (int m = 0; m < nf; ++m) {
+            const float2 w = tw[(int64_t)t * nf + m];
+            const double2 f = F[r * nf + m];
+            q += f.x * (double)w.x + f.y * (double)w.y;
         }
+        dout[tr.off + (int64_t)t * tr.stride] = (float)(q * inv_nt);
     }
 }
 
@@ -163,9 +216,10 @@ __global__ __launch_bounds__(NT) void k_dtft_qgen(const float2* __restrict__ xb,
             for (int m = 0; m < NFC; ++m)
                 v[j][m] = (on[j] && m < nf) ? xb[((int64_t)s * nf + m) * n + c0 + 64 * j] : make_float2(0.f, 0.f);
         }
-        for (int t = n0; t < n1; ++t) {
+        float* __restrict__ qt = q + (int64_t)s * K * n + c0;   // slot 0: n0 is a multiple of K
+#pragma unroll 4
+        for (int t = n0; t < n1; ++t, qt += n) {
             const float2* __restrict__ w = tw + (int64_t)t * nf;
-            float* __restrict__ qt = q + ((int64_t)s * K + t % K) * n + c0;
 #pragma unroll
             for (int j = 0; j < CPT; ++j) {
                 float acc = 0.f;
@@ -185,7 +239,7 @@ template <int NFC, int CPT>
 __global__ __launch_bounds__(NT) void k_dtft_bacc(float2* __restrict__ acc, const float* __restrict__ mu,
                                                   const float2* __restrict__ tw, int nf, int j0, int j1, int K,
                                                   int64_t n, const int* __restrict__ active) {
-    constexpr int U = 4;
+    constexpr int U = CPT == 1 ? 8 : 4;
     const int s = blockIdx.y;
     if (active && !active[s]) return;   // uniform over the block
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -205,7 +259,7 @@ __global__ __launch_bounds__(NT) void k_dtft_bacc(float2* __restrict__ acc, cons
 #pragma unroll
             for (int k = 0; k < U; ++k) {
                 const int jj = jt - k;
-                const float* __restrict__ mt = mu + ((int64_t)s * K + (jj >= j0 ? jj % K : 0)) * n + c0;
+                const float* __restrict__ mt = mu + ((int64_t)s * K + max(jj - j0, 0)) * n + c0;   // j0 is a multiple of K
 #pragma unroll
                 for (int j = 0; j < CPT; ++j) u[k][j] = (on[j] && jj >= j0) ? mt[64 * j] : 0.f;
             }
@@ -269,33 +323,44 @@ dim3 cell_grid(Plan* P, int ns) {
     return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((P->nphys + per - 1) / per, 1024)), (unsigned)ns);
 }
 
+// f(NFC) with the register count of frequencies for nf of them: 8, 16 or 32
+template <class F>
+void by_freqs(int nf, F f) {
+    if (nf <= 8) f(std::integral_constant<int, 8>{});
+    else if (nf <= 16) f(std::integral_constant<int, 16>{});
+    else f(std::integral_constant<int, MAX_NF>{});
+}
+
+// f(NFC, CPT): cells per thread of the block kernels, so that a thread's slices
+// fit its registers; one cell where more would leave fewer than 2048 workgroups
+// (64-step blocks of 4 shots of 401 x 201 at 8 frequencies, sources / fields: 90
+// and 88 us at 4 cells a thread, 36 and 40 at one).
+template <class F>
+void by_block(Plan* P, int ns, F f) {
+    const int64_t cells = (int64_t)ns * P->nphys;
+    by_freqs((int)P->dft_freqs.size(), [&](auto nfc) {
+        constexpr int CPT = 32 / decltype(nfc)::value;
+        if (cells < (int64_t)2048 * NT * CPT) f(nfc, std::integral_constant<int, 1>{});
+        else f(nfc, std::integral_constant<int, CPT>{});
+    });
+}
+
 esi_status_t launch_qgen(Plan* P, const float2* xb, int n0, int n1, int K, int ns, const int* active, float* q) {
-    const int nf = (int)P->dft_freqs.size();
-    const float inv_nt = (float)(1.0 / P->nt);
-    if (nf <= 8)
-        hipLaunchKernelGGL((k_dtft_qgen<8, 4>), cell_grid<4>(P, ns), dim3(NT), 0, P->stream, xb, P->dft_tw, nf, n0,
-                           n1, K, P->nphys, active, inv_nt, q);
-    else if (nf <= 16)
-        hipLaunchKernelGGL((k_dtft_qgen<16, 2>), cell_grid<2>(P, ns), dim3(NT), 0, P->stream, xb, P->dft_tw, nf, n0,
-                           n1, K, P->nphys, active, inv_nt, q);
-    else
-        hipLaunchKernelGGL((k_dtft_qgen<MAX_NF, 1>), cell_grid<1>(P, ns), dim3(NT), 0, P->stream, xb, P->dft_tw, nf,
-                           n0, n1, K, P->nphys, active, inv_nt, q);
+    by_block(P, ns, [&](auto nfc, auto cpt) {
+        constexpr int CPT = decltype(cpt)::value;
+        hipLaunchKernelGGL((k_dtft_qgen<decltype(nfc)::value, CPT>), cell_grid<CPT>(P, ns), dim3(NT), 0, P->stream, xb,
+                           P->dft_tw, (int)P->dft_freqs.size(), n0, n1, K, P->nphys, active, (float)(1.0 / P->nt), q);
+    });
     ESI_HIP_TRY(hipGetLastError());
     return ESI_OK;
 }
 
 esi_status_t launch_bacc(Plan* P, float2* acc, const float* mu, int j0, int j1, int K, int ns, const int* active) {
-    const int nf = (int)P->dft_freqs.size();
-    if (nf <= 8)
-        hipLaunchKernelGGL((k_dtft_bacc<8, 4>), cell_grid<4>(P, ns), dim3(NT), 0, P->stream, acc, mu, P->dft_tw, nf,
-                           j0, j1, K, P->nphys, active);
-    else if (nf <= 16)
-        hipLaunchKernelGGL((k_dtft_bacc<16, 2>), cell_grid<2>(P, ns), dim3(NT), 0, P->stream, acc, mu, P->dft_tw, nf,
-                           j0, j1, K, P->nphys, active);
-    else
-        hipLaunchKernelGGL((k_dtft_bacc<MAX_NF, 1>), cell_grid<1>(P, ns), dim3(NT), 0, P->stream, acc, mu, P->dft_tw,
-                           nf, j0, j1, K, P->nphys, active);
+    by_block(P, ns, [&](auto nfc, auto cpt) {
+        constexpr int CPT = decltype(cpt)::value;
+        hipLaunchKernelGGL((k_dtft_bacc<decltype(nfc)::value, CPT>), cell_grid<CPT>(P, ns), dim3(NT), 0, P->stream, acc,
+                           mu, P->dft_tw, (int)P->dft_freqs.size(), j0, j1, K, P->nphys, active);
+    });
     ESI_HIP_TRY(hipGetLastError());
     return ESI_OK;
 }
@@ -369,10 +434,12 @@ esi_status_t dtft_normal(Plan* P, int shot0, int ns, const float2* p, float2* Mp
     b.active = active;
     b.inj_data = P->dscr;
     ESI_TRY(dtft_adjoint(P, b, Mp, ns));
-    const int bps = (int)std::max<int64_t>(1, std::min<int64_t>(64, (P->nphys + 4095) / 4096));
+    const int bps = (int)std::max<int64_t>(1, std::min<int64_t>(1024, (P->nphys + NT - 1) / NT));
     ESI_TRY(grow_t(&P->part, &P->part_cap, (int64_t)bps * ns, P->stream));
-    hipLaunchKernelGGL(k_dtft_finish, dim3(bps, ns), dim3(NT), 0, P->stream, Mp, p, P->dft_C, nf, P->nz, P->ny, P->nx,
-                       P->d_src, shot0, P->beta, P->b_eps, P->w_identity, Mp, P->part);
+    by_freqs(nf, [&](auto nfc) {
+        hipLaunchKernelGGL(k_dtft_finish<decltype(nfc)::value>, dim3(bps, ns), dim3(NT), 0, P->stream, Mp, p, P->dft_C,
+                           nf, P->nz, P->ny, P->nx, P->d_src, shot0, P->beta, P->b_eps, P->w_identity, Mp, P->part);
+    });
     ESI_HIP_TRY(hipGetLastError());
     return pMp ? launch_reduce_parts(P, P->part, bps, ns, pMp) : ESI_OK;
 }
@@ -386,8 +453,13 @@ esi_status_t dtft_rhs(Plan* P, int shot0, int ns, const float* d_obs, float2* b)
     ESI_TRY(grow_t(&P->dscr, &P->dscr_cap, std::max<int64_t>(dl, 1), P->stream));
     if (dl > 0) {
         const int64_t nr = P->h_rec_ptr[shot0 + ns] - P->h_rec_ptr[shot0];
-        hipLaunchKernelGGL(k_data_band, dim3((int)std::min<int64_t>((nr + 63) / 64, 4096)), dim3(64), 0, P->stream,
-                           d_obs, P->dscr, P->d_rec_ptr, shot0, ns, P->nt, P->dft_tw, nf, 1.0 / P->nt);
+        ESI_TRY(grow_t(&P->part, &P->part_cap, 2 * nr * nf, P->stream));
+        double2* F = reinterpret_cast<double2*>(P->part);
+        const unsigned groups = (unsigned)((nr + 63) / 64);
+        hipLaunchKernelGGL(k_data_dtft, dim3(groups, (nf + BAND_F - 1) / BAND_F), dim3(64 * BAND_W), 0, P->stream, d_obs,
+                           P->d_rec_ptr, shot0, nr, P->nt, P->dft_tw, nf, F);
+        hipLaunchKernelGGL(k_data_series, dim3(groups, std::min(P->nt, 128)), dim3(64), 0, P->stream, F, P->dscr,
+                           P->d_rec_ptr, shot0, nr, P->nt, P->dft_tw, nf, 1.0 / P->nt);
         ESI_HIP_TRY(hipGetLastError());
     }
     ESI_TRY(launch_fill(P, (float*)b, (int64_t)ns * nf * P->nphys * 2, 0.f));

@@ -212,7 +212,7 @@ __global__ void k_scale_vec(float* __restrict__ p, const float* __restrict__ r, 
 // constant in time).  part[s][b] = block sums of r^2.  A thread owns CPT cells
 // 64 apart, so that a wave reads and writes 64 * CPT consecutive floats of a
 // time step (1 KB runs of each vector instead of 256 B ones).
-constexpr int CPT = 4;
+template <int CPT>
 __global__ __launch_bounds__(NT) void k_r_update_cells(float* __restrict__ r, const float* __restrict__ Np,
                                                        const double* __restrict__ alpha,
                                                        const int* __restrict__ active, int nt, int64_t nphys,
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(NT) void k_r_update_cells(float* __restrict__ r, co
         on[j] = c0 + 64 * j < nphys;
     }
     // U steps at a time: every load of the chunk is issued before its stores
-    constexpr int U = 4;
+    constexpr int U = CPT == 1 ? 8 : 4;
     for (int t0 = 0; t0 < nt; t0 += U) {
         float rv[U][CPT], av[U][CPT];
 #pragma unroll
@@ -415,10 +415,13 @@ esi_status_t launch_scale_vec(Plan* P, float* p, const float* r, const float* S,
 
 esi_status_t launch_r_update_cells(Plan* P, float* r, const float* Np, const double* alpha, const int* active,
                                    int ns, float* en, double* rnp, double* rr_out) {
-    const int bps = (int)((P->nphys + NT * CPT - 1) / (NT * CPT));
+    // one cell a thread where four would leave fewer than 1024 workgroups (a pass
+    // over 4 shots of 401 x 201 x 700: 637 us at four, 540 at one)
+    const int cpt = (int64_t)ns * P->nphys < (int64_t)1024 * NT * 4 ? 1 : 4;
+    const int bps = (int)((P->nphys + NT * cpt - 1) / (NT * cpt));
     ESI_TRY(grow_t(&P->part, &P->part_cap, (int64_t)bps * ns, P->stream));
-    hipLaunchKernelGGL(k_r_update_cells, dim3(bps, ns), dim3(NT), 0, P->stream, r, Np, alpha, active, P->nt,
-                       P->nphys, en, rnp, P->part);
+    hipLaunchKernelGGL(cpt == 1 ? k_r_update_cells<1> : k_r_update_cells<4>, dim3(bps, ns), dim3(NT), 0, P->stream, r,
+                       Np, alpha, active, P->nt, P->nphys, en, rnp, P->part);
     ESI_HIP_TRY(hipGetLastError());
     return launch_reduce_parts(P, P->part, bps, ns, rr_out);
 }
