@@ -73,161 +73,458 @@ static uint16_t f2bf_host(float f) {
 // l / 16, for row (A) or pixel (B) l % 16; A is packed in that order by
 // k_pack_frag, so a lane's weights are one coalesced 16-byte load.
 //
-// Workgroup: NWV waves, RPW output rows each, 64 pixels (4 groups of 16) x
-// 16 CB output channels.  Per chunk of CK input channels the (NWV RPW + 2) x 66
-// input tile and the chunk's weight operands are staged in LDS once; every
-// tap then reads its shifted operands from there.  (Padding the pixel stride
-// by 8 or 16 elements measured 1.5-4 % slower: the smaller tile keeps more
-// workgroups resident.)
+// Workgroup (x, y): NWV waves, each RPW output rows of PG groups of 16 of the tile's
+// 64 pixels, the 16 CB output channels of group y.  Per chunk of CK input channels
+// the (rows + 2) x 66 input tile is staged in LDS once and every tap reads its
+// shifted operands from there: at two rows a wave and CK = 32 an operand read
+// serves the taps of both rows.  The weights stay in registers for the whole
+// launch where a layer has one chunk and they fit (RES), else they are staged in
+// LDS with the chunk.
 //
-// The grid is persistent: workgroup b takes the (tile, chunk) steps of tiles
-// b, b + gridDim.x, ...  The global loads of the next step are issued
-// before the current step's MFMAs and land in registers, so memory latency
-// overlaps the arithmetic; a tile's outputs are stored after its last chunk.
-// With MASK, outputs where `act` (an activation laid out as Y, no halves) is not
-// positive are 0: the ReLU mask of a data gradient, in place of a pass of its
-// own.  (A template flag: a test of the pointer in the epilogue slowed the
-// forward pass by 19 %.)
+// The grid is persistent: workgroup x takes tiles x, x + gridDim.x, ...  The
+// global loads of the next (tile, chunk) are issued before the current one's
+// MFMAs and land in registers, so memory latency overlaps the arithmetic; a
+// tile's outputs are stored after its last chunk.
+//
+// Around the MFMAs it is the vector instructions that cost (a 64-wide one takes
+// as long as a quarter of an MFMA), so there are few: tiles are walked by scalar
+// additions, loads and stores are raw buffers with a per-lane offset that is
+// fixed but for the image's edges and a scalar one per row, and outputs are
+// rounded two at a time by the instruction.  Stores are 16 bytes a lane (8 bytes
+// left four partial writes in a line: 467 us for the pass below against 428).
+// The layers of 16 channels are bound by memory (38 us for 189 MB, 5 TB/s), the
+// others by the last wave of tiles and what it leaves exposed: 64 channels on 8
+// images of 102 x 202 have 416 tiles for 256 CUs (28 us, of which 8 MFMAs).
+// The forward pass on 8 images of 408 x 808 takes 428 us; with 1369 vector
+// instructions for 144 MFMAs (now 513), pooling and first and last layer as
+// kernels of their own, it took 652.
 constexpr int frag_ck(int K) { return K % 32 == 0 ? 32 : 16; }
 constexpr int frag_nkb(int ck) { return ck == 32 ? 9 : 5; }
 
-template <int CB, int RPW, int CK, int NWV>
-struct Conv3Tile {
-    static constexpr int NTW = 64 * NWV;                  // threads of a workgroup
-    static constexpr int ROWS = NWV * RPW;                // output rows of a tile
-    static constexpr int NKB = frag_nkb(CK);
-    static constexpr int TR = ROWS + 2, TC = 66, PS = CK, SUB = CK / 8;
-    static constexpr int NQ = TR * TC * SUB, NL = (NQ + NTW - 1) / NTW;   // 16-byte pieces of a tile, per thread
-    static constexpr int NWQ = NKB * CB * 64, NWL = (NWQ + NTW - 1) / NTW;  // and of a chunk's weights
+enum Epi {
+    E_FWD,    // bias, ReLU
+    E_POOL,   // and the 2x2 average of the outputs (of their bf16 values) into `pool`
+    E_OUT,    // and the 1x1 output layer (16 -> 1) of the outputs into `o`; Y only if given
+    E_GRAD,   // data gradient: as it is
+    E_MASK    // outputs where `act` (laid out as Y, no halves) is not positive are 0
 };
 
-template <int CB, int RPW, int CK, int NWV, bool MASK>
-__global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3(
-    const bf16_t* __restrict__ X, int sx, int64_t xhs, int xsplit, int K, const bf16_t* __restrict__ Af, int ncb,
-    const float* __restrict__ bias, bf16_t* __restrict__ Y, int sy, int64_t yhs, int ysplit, int M, int H, int W,
-    int N, int relu, const bf16_t* __restrict__ act) {
-    using T = Conv3Tile<CB, RPW, CK, NWV>;
-    __shared__ __align__(16) bf16_t xs[T::TR * T::TC * T::PS];
-    __shared__ __align__(16) bf16_t ws[T::NWQ * 8];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+constexpr uint32_t OOB = 0x80000000u;   // byte offset beyond every buffer: loads 0, stores nothing
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)OOB, 0x00027000);
+}
+// two floats to bf16, round to nearest even
+__device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
+    union { bf16x2 v; uint32_t u; } r;
+    r.v = bf16x2{(__bf16)a, (__bf16)b};
+    return r.u;
+}
+__device__ __forceinline__ float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
+__device__ __forceinline__ float bf_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
+// the value of lane l ^ 1
+__device__ __forceinline__ uint32_t lane_pair(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);
+}
+
+// Lane 16 g + j of u and v holds outputs 4 g .. 4 g + 3 (8 bytes) of pixel j of a
+// block of 16 outputs each; now 8 consecutive outputs of one: g = 0 and 2 the
+// halves of u, g = 1 and 3 those of v.
+__device__ __forceinline__ u32x4 merge_blocks(u32x2 u, u32x2 v) {
+    const auto x = __builtin_amdgcn_permlane16_swap(u.x, v.x, false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(u.y, v.y, false, false);
+    return u32x4{x[0], y[0], x[1], y[1]};
+}
+
+// 16-byte buffer stores go without a scalar offset: with one, the compiler puts
+// no wait between the store and the next write of its data registers, and the
+// first dword of half the lanes was then stored with that next value.
+__device__ __forceinline__ void store16(u32x4 v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, 0);
+}
+// the inverse of merge_blocks
+__device__ __forceinline__ void split_blocks(u32x4 m, u32x2& u, u32x2& v) {
+    const auto x = __builtin_amdgcn_permlane16_swap(m.x, m.z, false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(m.y, m.w, false, false);
+    u = u32x2{x[0], y[0]};
+    v = u32x2{x[1], y[1]};
+}
+
+struct ConvArgs {
+    const bf16_t* X;
+    int sx;
+    int64_t xhs;
+    int xsplit, K;
+    const bf16_t* Af;
+    int ncb;                // 16-row blocks of A
+    const float* bias;
+    bf16_t* Y;
+    int sy;
+    int64_t yhs;
+    int ysplit, H, W, N;
+    const bf16_t* act;      // E_MASK
+    bf16_t* pool;           // E_POOL: [N][H/2][W/2][sy]
+    const bf16_t* wo;       // E_OUT: weights, bias, output [N][H][W]
+    const float* bo;
+    float* o;
+    const float* xin;       // IN: the network's input [N][3][H][W] in place of X
+};
+
+template <int CB, int CK, int PG>
+struct Conv3Tile {
+    static constexpr int RPW = 2, ROWS = 8;               // output rows of a wave and of a tile
+    static constexpr int NWV = 4 * ROWS / (RPW * PG);     // waves: 4 groups of pixels a row, PG a wave
+    static constexpr int NTW = 64 * NWV;                  // threads of a workgroup
+    static constexpr int NKB = frag_nkb(CK);
+    static constexpr int TR = ROWS + 2, TC = 66, SUB = CK / 8;
+    static constexpr int RPL = NTW / (64 * SUB);          // tile rows per load, but for the last two columns
+    static constexpr int NL = (TR + RPL - 1) / RPL;
+    static constexpr int NWL = (NKB * CB + NWV - 1) / NWV;   // weight blocks a wave stages
+};
+
+template <int CB, int CK, int PG, int EPI, bool RES, bool IN>
+__global__ __launch_bounds__(64 * (16 / PG)) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3(const ConvArgs A) {
+    using T = Conv3Tile<CB, CK, PG>;
+    constexpr int RPW = T::RPW, NWV = T::NWV;
+    constexpr int TC = T::TC, TR = T::TR, SUB = T::SUB, NKB = T::NKB;
+    static_assert(T::RPL >= 1 && TR * 2 * SUB <= T::NTW, "tile staging");
+    static_assert(EPI != E_OUT || (CB == 1 && PG == 4), "the output layer reads 16 channels");
+    static_assert(!IN || CK == 16, "the input is padded to 16 channels");
+    __shared__ __align__(16) bf16_t xs[TR * TC * CK];
+    __shared__ __align__(16) bf16_t ws[RES ? 8 : NKB * CB * 512];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int jl = lane & 15, g = lane >> 4;
-    const int ncog = M / (16 * CB), nchunk = K / CK;
+    const int wy = wave / (4 / PG) * RPW, wx = wave % (4 / PG) * (PG * 16);   // the wave's first row and pixel
+    const int H = A.H, W = A.W, nchunk = RES ? 1 : A.K / CK, cb0 = blockIdx.y * CB;
     const int ntx = (W + 63) / 64, nty = (H + T::ROWS - 1) / T::ROWS;
-    const int ntiles = ntx * nty * N * ncog;
-    // tiles b, b + gridDim.x, ... of this workgroup b
-    const int nmine = blockIdx.x < ntiles ? (ntiles - 1 - (int)blockIdx.x) / (int)gridDim.x + 1 : 0;
-    const int nsteps = nmine * nchunk;
+    const int nmine = (ntx * nty * A.N - 1 - (int)blockIdx.x) / (int)gridDim.x + 1;   // gridDim.x <= tiles
 
-    // step -> tile origin, image, output-channel group, chunk
-    auto decode = [&](int step, int& x0, int& y0, int& n, int& cbg, int& chunk) {
-        const int t = (int)blockIdx.x + (step / nchunk) * (int)gridDim.x;
-        chunk = step % nchunk;
-        x0 = (t % ntx) * 64;
-        y0 = ((t / ntx) % nty) * T::ROWS;
-        const int z = t / (ntx * nty);
-        n = z / ncog;
-        cbg = z % ncog;
-    };
-    uint4 st[T::NL], sw[T::NWL];
-    auto fetch = [&](int step) {
-        int x0, y0, n, cbg, chunk;
-        decode(step, x0, y0, n, cbg, chunk);
-        const bf16_t* Xn = X + (int64_t)n * H * W * sx;
-#pragma unroll
-        for (int l = 0; l < T::NL; ++l) {
-            const int q = threadIdx.x + l * T::NTW;
-            const int sub = q % T::SUB, px = (q / T::SUB) % T::TC, row = q / (T::SUB * T::TC);
-            const int yy = y0 - 1 + row, xx = x0 - 1 + px;
-            const int ch = chunk * CK + sub * 8;             // channels at or past xsplit: second half
-            const int64_t hoff = ch >= xsplit ? xhs - xsplit : 0;
-            st[l] = uint4{0u, 0u, 0u, 0u};
-            if (q < T::NQ && yy >= 0 && yy < H && xx >= 0 && xx < W)
-                st[l] = *reinterpret_cast<const uint4*>(Xn + ((int64_t)yy * W + xx) * sx + hoff + ch);
-        }
-        // the workgroup's weight operands of the chunk: [kb][c][lane][8]
-#pragma unroll
-        for (int l = 0; l < T::NWL; ++l) {
-            const int q = threadIdx.x + l * T::NTW;
-            const int kbc = q / 64, kb = kbc / CB, c = kbc % CB;
-            sw[l] = uint4{0u, 0u, 0u, 0u};
-            if (q < T::NWQ)
-                sw[l] = *reinterpret_cast<const uint4*>(
-                    Af + (((int64_t)chunk * T::NKB + kb) * ncb + cbg * CB + c) * 512 + (q % 64) * 8);
-        }
-    };
+    // tile walk: this workgroup's tile and the stride gridDim.x, as (x, y, image)
+    int tx = blockIdx.x % ntx, ty = (blockIdx.x / ntx) % nty, tn = blockIdx.x / (ntx * nty);
+    const int gx = gridDim.x % ntx, gy = (gridDim.x / ntx) % nty, gn = gridDim.x / (ntx * nty);
 
-    f4 acc[RPW][4][CB];
+    // ---- staging: thread -> (row of a load, column, 16-byte piece); one more
+    // load for the tile's last two columns
+    uint4 st[T::NL + 1], sw[T::NWL];
+    float fi[T::NL + 1][3];
+    constexpr int IL = (TR + NWV - 1) / NWV;
+    const int wrow = IN ? wave : wave / SUB;
+    const int mpx = IN ? lane : (tid % (64 * SUB)) / SUB, msub = IN ? 0 : tid % SUB;
+    const int hrow = IN ? tid >> 1 : tid / (2 * SUB);
+    const int hpx = IN ? 64 + (tid & 1) : 64 + (tid % (2 * SUB)) / SUB;
+    uint32_t moff, hoff;
+    if constexpr (IN) {
+        moff = 4 * mpx;
+        hoff = 4 * (hrow * W + hpx);
+    } else {
+        // channels at or past xsplit inside the only chunk: second half
+        const uint32_t sec = A.xsplit < CK && msub * 8 >= A.xsplit ? (uint32_t)(2 * (A.xhs - A.xsplit)) : 0u;
+        moff = 2 * (mpx * A.sx + msub * 8) + sec;
+        hoff = 2 * ((hrow * W + hpx) * A.sx + msub * 8) + sec;
+    }
+    const bool hin = hrow < TR;
+    const __amdgpu_buffer_rsrc_t ra = rsrc(A.Af);
+    // (unconditional, with every lane out of bounds when there is nothing to load:
+    // registers loaded on one path only are copied, and waited for, at the join)
+    auto fetch = [&](int x, int y, int n, int chunk, bool any) {
+        const int x0 = x * 64, y0 = y * T::ROWS;
+        const uint32_t mo = any && (uint32_t)(x0 - 1 + mpx) < (uint32_t)W ? moff : OOB;
+        const uint32_t ho = any && hin && (uint32_t)(y0 - 1 + hrow) < (uint32_t)H && x0 - 1 + hpx < W ? hoff : OOB;
+        if constexpr (IN) {
 #pragma unroll
-    for (int r = 0; r < RPW; ++r)
+            for (int c = 0; c < 3; ++c) {
+                const __amdgpu_buffer_rsrc_t rx = rsrc(A.xin + ((int64_t)n * 3 + c) * H * W - 1 - W);
 #pragma unroll
-        for (int p = 0; p < 4; ++p)
-#pragma unroll
-            for (int c = 0; c < CB; ++c) acc[r][p][c] = f4{0.f, 0.f, 0.f, 0.f};
-
-    if (nsteps > 0) fetch(0);
-    for (int step = 0; step < nsteps; ++step) {
-        if (step) __syncthreads();   // every wave is done reading the previous step's LDS
-#pragma unroll
-        for (int l = 0; l < T::NL; ++l) {
-            const int q = threadIdx.x + l * T::NTW;
-            const int sub = q % T::SUB, px = (q / T::SUB) % T::TC, row = q / (T::SUB * T::TC);
-            if (q < T::NQ) *reinterpret_cast<uint4*>(xs + (row * T::TC + px) * T::PS + sub * 8) = st[l];
-        }
-#pragma unroll
-        for (int l = 0; l < T::NWL; ++l) {
-            const int q = threadIdx.x + l * T::NTW;
-            if (q < T::NWQ) *reinterpret_cast<uint4*>(ws + q * 8) = sw[l];
-        }
-        __syncthreads();
-        if (step + 1 < nsteps) fetch(step + 1);   // lands while this step computes
-#pragma unroll
-        for (int kb = 0; kb < T::NKB; ++kb) {
-            const int tap = CK == 32 ? kb : min(2 * kb + (g >> 1), 8);
-            const int koff = CK == 32 ? 8 * g : 8 * (g & 1);
-            const int dy = tap / 3, dx = tap % 3;
-            bf16x8 a[CB];
-#pragma unroll
-            for (int c = 0; c < CB; ++c)
-                a[c] = *reinterpret_cast<const bf16x8*>(ws + ((kb * CB + c) * 64 + lane) * 8);
-#pragma unroll
-            for (int r = 0; r < RPW; ++r)
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    const bf16x8 b = *reinterpret_cast<const bf16x8*>(
-                        xs + ((wave * RPW + r + dy) * T::TC + p * 16 + jl + dx) * T::PS + koff);
-#pragma unroll
-                    for (int c = 0; c < CB; ++c)
-                        acc[r][p][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], b, acc[r][p][c], 0, 0, 0);
+                for (int l = 0; l < IL; ++l) {
+                    const int row = l * NWV + wave, yy = y0 - 1 + row;
+                    const bool ok = (uint32_t)yy < (uint32_t)H && row < TR;
+                    fi[l][c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                        rx, (int)(ok ? mo : OOB), 4 * ((yy + 1) * W + x0), 0));
                 }
+                fi[IL][c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, (int)ho, 4 * (y0 * W + x0), 0));
+            }
+        } else {
+            const int ch = chunk * CK;
+            // from one pixel and one row before the tile's first: offsets stay positive
+            const __amdgpu_buffer_rsrc_t rx =
+                rsrc(A.X + ((int64_t)n * H * W - 1 - W) * A.sx + ch + (ch >= A.xsplit ? A.xhs - A.xsplit : 0));
+#pragma unroll
+            for (int l = 0; l < T::NL; ++l) {
+                const int row = l * T::RPL + wrow, yy = y0 - 1 + row;
+                const bool ok = (uint32_t)yy < (uint32_t)H && row < TR;
+                const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(ok ? mo : OOB),
+                                                                     2 * ((yy + 1) * W + x0) * A.sx, 0);
+                st[l] = uint4{v.x, v.y, v.z, v.w};
+            }
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)ho, 2 * (y0 * W + x0) * A.sx, 0);
+            st[T::NL] = uint4{v.x, v.y, v.z, v.w};
         }
-        if (step % nchunk != nchunk - 1) continue;
-        // the tile's last chunk: bias, ReLU, bf16, store; clear the sums
-        int x0, y0, n, cbg, chunk;
-        decode(step, x0, y0, n, cbg, chunk);
-        bf16_t* Yn = Y + (int64_t)n * H * W * sy;
+    };
+    // the workgroup's weight blocks of a chunk: [kb][c][lane][8]
+    auto wblock = [&](int chunk, int f, int off) -> uint4 {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(
+            ra, off, (((chunk * NKB + f / CB) * A.ncb + cb0 + f % CB) * 1024), 0);
+        return uint4{v.x, v.y, v.z, v.w};
+    };
+    auto wfetch = [&](int chunk, bool any) {
+        const int off = any ? lane * 16 : (int)OOB;
+#pragma unroll
+        for (int l = 0; l < T::NWL; ++l) sw[l] = wblock(chunk, min(l * NWV + wave, NKB * CB - 1), off);
+    };
+    auto put = [&]() {
+        if constexpr (IN) {
+#pragma unroll
+            for (int l = 0; l <= IL; ++l) {
+                const int row = l < IL ? l * NWV + wave : hrow, px = l < IL ? mpx : hpx;
+                if ((l < IL && (l + 1) * NWV <= TR) || row < TR)
+                    *reinterpret_cast<u32x2*>(xs + (row * TC + px) * CK) =
+                        u32x2{pk_bf16(fi[l][0], fi[l][1]), pk_bf16(fi[l][2], 0.f)};
+            }
+        } else {
+#pragma unroll
+            for (int l = 0; l < T::NL; ++l) {
+                const int row = l * T::RPL + wrow;
+                if ((l + 1) * T::RPL <= TR || row < TR) *reinterpret_cast<uint4*>(xs + (row * TC + mpx) * CK + msub * 8) = st[l];
+            }
+            if (hin) *reinterpret_cast<uint4*>(xs + (hrow * TC + hpx) * CK + msub * 8) = st[T::NL];
+        }
+        if constexpr (!RES)
+#pragma unroll
+            for (int l = 0; l < T::NWL; ++l) {
+                const int f = l * NWV + wave;
+                if ((l + 1) * NWV <= NKB * CB || f < NKB * CB) *reinterpret_cast<uint4*>(ws + f * 512 + lane * 8) = sw[l];
+            }
+    };
+
+    union { uint4 u; bf16x8 v; } wr[RES ? NKB * CB : 1];
+    if constexpr (RES) {
+#pragma unroll
+        for (int f = 0; f < NKB * CB; ++f) wr[f].u = wblock(0, f, lane * 16);
+    }
+    auto weight = [&](int kb, int c) -> bf16x8 {
+        if constexpr (RES) return wr[kb * CB + c].v;
+        else return *reinterpret_cast<const bf16x8*>(ws + ((kb * CB + c) * 64 + lane) * 8);
+    };
+    f4 bias[CB];
+#pragma unroll
+    for (int c = 0; c < CB; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bias[c][e] = EPI <= E_OUT ? A.bias[(cb0 + c) * 16 + 4 * g + e] : 0.f;
+    float wo[16], bo = 0.f;
+    if constexpr (EPI == E_OUT) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) wo[c] = bf2f(A.wo[c]);
+        bo = A.bo[0];
+    }
+    if constexpr (IN) {   // channels 3 to 15 of the input stay 0
+        for (int q = tid; q < TR * TC * 2; q += T::NTW) *reinterpret_cast<uint4*>(xs + q * 8) = uint4{0u, 0u, 0u, 0u};
+        __syncthreads();
+    }
+
+    // this lane's operand in the tile; CK = 16: the offset of the lane's tap of each block
+    const bf16_t* bp = xs + (wy * TC + wx + jl) * CK + (CK == 32 ? 8 * g : 8 * (g & 1));
+    int toff[NKB];
+    if constexpr (CK == 16)
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+            const int t0 = 2 * kb, t1 = kb == 4 ? 8 : 2 * kb + 1;
+            toff[kb] = ((g >> 1) ? (t1 / 3) * TC + t1 % 3 : (t0 / 3) * TC + t0 % 3) * CK;
+        }
+
+    f4 acc[RPW][PG][CB];
+    fetch(tx, ty, tn, 0, true);
+    if (!RES) wfetch(0, true);
+    for (int i = 0; i < nmine; ++i) {
+        const int x0 = tx * 64, y0 = ty * T::ROWS, n = tn;
+#pragma unroll
+        for (int r = 0; r < RPW; ++r)
+#pragma unroll
+            for (int p = 0; p < PG; ++p)
+#pragma unroll
+                for (int c = 0; c < CB; ++c) acc[r][p][c] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int chunk = 0; chunk < nchunk; ++chunk) {
+            __syncthreads();   // every wave is done reading the previous step's LDS
+            put();
+            __syncthreads();
+            // the next step's loads land while this one computes
+            const bool last = chunk + 1 == nchunk, any = !last || i + 1 < nmine;
+            if (last) {
+                tx += gx;
+                if (tx >= ntx) tx -= ntx, ++ty;
+                ty += gy;
+                if (ty >= nty) ty -= nty, ++tn;
+                tn += gn;
+            }
+            const int next = last ? 0 : chunk + 1;
+            fetch(tx, ty, tn, next, any);
+            if (!RES) wfetch(next, any);
+            __builtin_amdgcn_sched_barrier(0);   // issued here, not where registers are free
+            if constexpr (CK == 16) {
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb) {
+                    bf16x8 a[CB];
+#pragma unroll
+                    for (int c = 0; c < CB; ++c) a[c] = weight(kb, c);
+                    const bf16_t* q = bp + toff[kb];
+#pragma unroll
+                    for (int r = 0; r < RPW; ++r)
+#pragma unroll
+                        for (int p = 0; p < PG; ++p) {
+                            const bf16x8 b = *reinterpret_cast<const bf16x8*>(q + (r * TC + p * 16) * CK);
+#pragma unroll
+                            for (int c = 0; c < CB; ++c)
+                                acc[r][p][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], b, acc[r][p][c], 0, 0, 0);
+                        }
+                }
+            } else {
+                // tile row t of the wave's RPW + 2 serves tap row t of its first
+                // output row and t - 1 of its second: every sum runs over the taps in order
+                bf16x8 a[2][3][CB];
+#pragma unroll
+                for (int t = 0; t < RPW + 2; ++t)
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx) {
+#pragma unroll
+                        for (int c = 0; c < CB; ++c) {
+                            if (t) a[1][dx][c] = a[0][dx][c];
+                            if (t < 3) a[0][dx][c] = weight(t * 3 + dx, c);
+                        }
+#pragma unroll
+                        for (int p = 0; p < PG; ++p) {
+                            const bf16x8 b = *reinterpret_cast<const bf16x8*>(bp + (t * TC + p * 16 + dx) * CK);
+#pragma unroll
+                            for (int r = 0; r < RPW; ++r)
+                                if (t - r >= 0 && t - r < 3)
+#pragma unroll
+                                    for (int c = 0; c < CB; ++c)
+                                        acc[r][p][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r][dx][c], b, acc[r][p][c], 0, 0, 0);
+                        }
+                    }
+            }
+        }
+        // ---- the tile's outputs
+        uint32_t po[PG];   // byte offsets of the lane's 8 channels of a pixel
+#pragma unroll
+        for (int p = 0; p < PG; ++p) {
+            const int px = wx + (CB == 1 ? 2 * p + (g & 1) : p) * 16 + jl;
+            po[p] = x0 + px < W ? 2 * (px * A.sy + (CB == 1 ? 0 : 16 * (g & 1)) + 8 * (g >> 1)) : OOB;
+        }
+        const int64_t img = (int64_t)n * H * W;
+        const __amdgpu_buffer_rsrc_t ry = rsrc(A.Y + img * A.sy), rm = rsrc(EPI == E_MASK ? A.act + img * A.sy : nullptr);
+        auto cbase = [&](int c, int yo) -> int {   // byte offset of row yo's first pixel, channel block c
+            const int co = (cb0 + c) * 16;
+            return 2 * (int)((yo * W + x0) * A.sy + co + (co >= A.ysplit ? A.yhs - A.ysplit : 0));
+        };
+        u32x2 on[RPW][PG][CB], out[RPW][PG][CB];
+        if constexpr (EPI == E_MASK)
+#pragma unroll
+            for (int r = 0; r < RPW; ++r) {
+                const int yo = y0 + wy + r;
+#pragma unroll
+                for (int p = 0; p < PG; p += CB == 1 ? 2 : 1)
+#pragma unroll
+                    for (int c = 0; c < CB; c += 2)
+                        split_blocks(__builtin_amdgcn_raw_buffer_load_b128(
+                                         rm, (int)(yo < H ? po[CB == 1 ? p >> 1 : p] : OOB), cbase(c, yo), 0),
+                                     on[r][p][c], CB == 1 ? on[r][p + 1][c] : on[r][p][c + 1]);
+            }
 #pragma unroll
         for (int r = 0; r < RPW; ++r) {
-            const int yo = y0 + wave * RPW + r;
+            const int yo = y0 + wy + r;
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const int xo = x0 + p * 16 + jl;
+            for (int p = 0; p < PG; ++p)
 #pragma unroll
                 for (int c = 0; c < CB; ++c) {
-                    const int co = (cbg * CB + c) * 16 + 4 * g;
-                    if (yo < H && xo < W) {
-                        s4 on = s4{0, 0, 0, 0}, o;
-                        if constexpr (MASK)
-                            on = *reinterpret_cast<const s4*>(act + ((int64_t)n * H * W + (int64_t)yo * W + xo) * sy + co);
+                    f4 v = acc[r][p][c];
+                    if constexpr (EPI <= E_OUT)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e] + bias[c][e], 0.f);
+                    if constexpr (EPI == E_MASK) {
+                        const u32x2 m = on[r][p][c];
+                        v[0] = bf_lo(m.x) > 0.f ? v[0] : 0.f;
+                        v[1] = bf_hi(m.x) > 0.f ? v[1] : 0.f;
+                        v[2] = bf_lo(m.y) > 0.f ? v[2] : 0.f;
+                        v[3] = bf_hi(m.y) > 0.f ? v[3] : 0.f;
+                    }
+                    out[r][p][c] = u32x2{pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3])};
+                }
+            // 16 bytes a lane, of two channel blocks or (CB = 1) of two pixel groups.
+            // No branches: the count of stores after the next step's loads is fixed
+            const bool in = yo < H, yes = in && (EPI != E_OUT || A.Y);
+            if constexpr (CB == 1) {
+#pragma unroll
+                for (int p = 0; p < PG; p += 2)
+                    store16(merge_blocks(out[r][p][0], out[r][p + 1][0]), ry, (yes ? po[p >> 1] : OOB) + cbase(0, yo));
+            } else {
+#pragma unroll
+                for (int p = 0; p < PG; ++p)
+#pragma unroll
+                    for (int c = 0; c < CB; c += 2) {
+                        const int hop = A.ysplit == (cb0 + c + 1) * 16 ? 2 * (int)(A.yhs - A.ysplit) : 0;
+                        const uint32_t vo = po[p] + (g & 1 ? hop : 0);
+                        store16(merge_blocks(out[r][p][c], out[r][p][c + 1]), ry, (yes ? vo : OOB) + cbase(c, yo));
+                    }
+            }
+            if constexpr (EPI == E_OUT) {
+                // transpose over the four 16-lane rows: lane 16 g + j gets the 16
+                // channels of pixel j of group g
+                uint32_t ch[4][2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    auto v = [&](int p) { return h ? out[r][p][0].y : out[r][p][0].x; };
+                    const auto s0 = __builtin_amdgcn_permlane32_swap(v(0), v(2), false, false);
+                    const auto s1 = __builtin_amdgcn_permlane32_swap(v(1), v(3), false, false);
+                    const auto t0 = __builtin_amdgcn_permlane16_swap(s0[0], s1[0], false, false);
+                    const auto t1 = __builtin_amdgcn_permlane16_swap(s0[1], s1[1], false, false);
+                    ch[0][h] = t0[0]; ch[1][h] = t0[1]; ch[2][h] = t1[0]; ch[3][h] = t1[1];
+                }
+                float s = bo;
+#pragma unroll
+                for (int c = 0; c < 16; ++c) {
+                    const uint32_t w2 = ch[c >> 2][(c >> 1) & 1];
+                    s += wo[c] * (c & 1 ? bf_hi(w2) : bf_lo(w2));
+                }
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s), rsrc(A.o + img),
+                                                      (int)(in && x0 + lane < W ? 4 * lane : OOB), 4 * (yo * W + x0), 0);
+            }
+        }
+        if constexpr (EPI == E_POOL) {
+            // a lane pair holds two columns of pixel groups p and p + 1: the even lane
+            // averages its pair's block of group p, the odd lane that of p + 1
+            const int yo = y0 + wy;
+            {
+                const bool odd = lane & 1;
+                const __amdgpu_buffer_rsrc_t rp = rsrc(A.pool + (img >> 2) * A.sy);
+#pragma unroll
+                for (int p = 0; p < PG; p += 2) {
+                    const int px = wx + (p + (odd ? 1 : 0)) * 16 + jl;
+                    const uint32_t vo = yo < H && x0 + px < W ? 2 * ((px >> 1) * A.sy + 4 * g) : OOB;
+#pragma unroll
+                    for (int c = 0; c < CB; ++c) {
+                        uint32_t v[4][2];   // rows x columns, packed channels
+#pragma unroll
+                        for (int r = 0; r < 2; ++r)
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) {
+                                const uint32_t u0 = h ? out[r][p][c].y : out[r][p][c].x;
+                                const uint32_t u1 = h ? out[r][p + 1][c].y : out[r][p + 1][c].x;
+                                const uint32_t mine = odd ? u1 : u0, theirs = lane_pair(odd ? u0 : u1);
+                                v[2 * r][h] = odd ? theirs : mine;
+                                v[2 * r + 1][h] = odd ? mine : theirs;
+                            }
+                        float m[4];
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            float v = acc[r][p][c][e] + (bias ? bias[co + e] : 0.f);
-                            if (relu) v = fmaxf(v, 0.f);
-                            o[e] = !MASK || bf2f((bf16_t)on[e]) > 0.f ? (short)f2bf(v) : (short)0;
+                            auto f = [&](int k) { return e & 1 ? bf_hi(v[k][e >> 1]) : bf_lo(v[k][e >> 1]); };
+                            m[e] = 0.25f * (f(0) + f(1) + f(2) + f(3));
                         }
-                        const int64_t hoff = co >= ysplit ? yhs - ysplit : 0;
-                        *reinterpret_cast<s4*>(Yn + ((int64_t)yo * W + xo) * sy + hoff + co) = o;
+                        __builtin_amdgcn_raw_buffer_store_b64(
+                            u32x2{pk_bf16(m[0], m[1]), pk_bf16(m[2], m[3])}, rp, (int)vo,
+                            2 * (((yo >> 1) * (W >> 1) + (x0 >> 1)) * A.sy + (cb0 + c) * 16), 0);
                     }
-                    acc[r][p][c] = f4{0.f, 0.f, 0.f, 0.f};
                 }
             }
         }
@@ -442,32 +739,6 @@ __global__ __launch_bounds__(1024) void k_wgrad_reduce(const float* __restrict__
     else if (ci < cin_real) gflat[((int64_t)co * cin_real + ci) * taps + tap] = (float)s;
 }
 
-// 2x2 average pool: out[n][i][j][c] = bf16(mean of the 2x2 block).
-__global__ void k_pool(const bf16_t* __restrict__ X, int sx, bf16_t* __restrict__ Y, int sy, int C,
-                       int N, int H2, int W2) {
-    // one thread per 8 channels of an output pixel (16-byte loads and store)
-    const int C8 = C / 8;
-    const int64_t total = (int64_t)N * H2 * W2 * C8;
-    for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < total; i += (int64_t)gridDim.x * NT) {
-        const int c = (int)(i % C8) * 8;
-        const int64_t pix = i / C8;
-        const int j = (int)(pix % W2), ii = (int)((pix / W2) % H2), n = (int)(pix / ((int64_t)W2 * H2));
-        const int64_t base = ((int64_t)n * 2 * H2 + 2 * ii) * (2 * W2) + 2 * j;
-        bf8u v[4];
-        v[0].u = *reinterpret_cast<const uint4*>(X + base * sx + c);
-        v[1].u = *reinterpret_cast<const uint4*>(X + (base + 1) * sx + c);
-        v[2].u = *reinterpret_cast<const uint4*>(X + (base + 2 * W2) * sx + c);
-        v[3].u = *reinterpret_cast<const uint4*>(X + (base + 2 * W2 + 1) * sx + c);
-        bf8u o;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float s = bf2f(v[0].h[e]) + bf2f(v[1].h[e]) + bf2f(v[2].h[e]) + bf2f(v[3].h[e]);
-            o.h[e] = f2bf(0.25f * s);
-        }
-        *reinterpret_cast<uint4*>(Y + pix * sy + c) = o.u;
-    }
-}
-
 // Gradient into an encoder output: g[n][y][x][c] = bf16(gp[n][y/2][x/2][c] / 4
 // + gskip[n][y][x][c]), then the ReLU mask of that output.  One thread per 8
 // channels of a pixel (16-byte loads and store: 18 us a level on average on 16
@@ -505,7 +776,8 @@ template <int CB, int NKC>
 __global__ __launch_bounds__(NT) void k_convT_mfma(const bf16_t* __restrict__ X, int sx,
                                                    const bf16_t* __restrict__ Af, const float* __restrict__ bias,
                                                    bf16_t* __restrict__ Y, int sy, int Cout, int Hi, int Wi) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    static_assert(CB % 2 == 0, "blocks of 16 outputs are stored in pairs");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int jl = lane & 15, g = lane >> 4;
     const int M = 4 * Cout, nmb = M / 16;
     const int ncog = M / (16 * CB);
@@ -514,19 +786,31 @@ __global__ __launch_bounds__(NT) void k_convT_mfma(const bf16_t* __restrict__ X,
     const int y = blockIdx.y * 4 + wave;
     if (y >= Hi) return;
     const int x0 = blockIdx.x * 64;
-    const bf16_t* Xr = X + ((int64_t)n * Hi + y) * Wi * sx;
+    const __amdgpu_buffer_rsrc_t rx = rsrc(X + (((int64_t)n * Hi + y) * Wi + x0) * sx), ra = rsrc(Af);
     bf16x8 b[NKC][4], a[NKC][CB];
+    auto load = [](__amdgpu_buffer_rsrc_t r, uint32_t v, int o) {
+        union { u32x4 u; bf16x8 h; } q;
+        q.u = __builtin_amdgcn_raw_buffer_load_b128(r, (int)v, o, 0);
+        return q.h;
+    };
+    uint32_t po[4];
 #pragma unroll
-    for (int kc = 0; kc < NKC; ++kc) {
+    for (int p = 0; p < 4; ++p) {
+        const bool in = x0 + p * 16 + jl < Wi;
+        const uint32_t vo = in ? 2 * ((p * 16 + jl) * sx + 8 * g) : OOB;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const int xx = x0 + p * 16 + jl;
-            b[kc][p] = bf16x8{};
-            if (xx < Wi) b[kc][p] = *reinterpret_cast<const bf16x8*>(Xr + (int64_t)xx * sx + kc * 32 + 8 * g);
-        }
+        for (int kc = 0; kc < NKC; ++kc) b[kc][p] = load(rx, vo, kc * 64);
+        // 8 outputs of a pair of blocks: two neighbouring outputs pixels are 2 Cout
+        // consecutive channels
+        po[p] = in ? 2 * (2 * (p * 16 + jl) * sy + 16 * (g & 1) + 8 * (g >> 1)) : OOB;
+    }
+    f4 bs[CB];
 #pragma unroll
-        for (int c = 0; c < CB; ++c)
-            a[kc][c] = *reinterpret_cast<const bf16x8*>(Af + (((int64_t)kc * nmb + mb0 + c) * 64 + lane) * 8);
+    for (int c = 0; c < CB; ++c) {
+#pragma unroll
+        for (int kc = 0; kc < NKC; ++kc) a[kc][c] = load(ra, lane * 16, (kc * nmb + mb0 + c) * 1024);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bs[c][e] = bias[((mb0 + c) * 16) % Cout + 4 * g + e];
     }
     f4 acc[4][CB];
 #pragma unroll
@@ -540,18 +824,20 @@ __global__ __launch_bounds__(NT) void k_convT_mfma(const bf16_t* __restrict__ X,
         }
     const int Wo = 2 * Wi;
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const int xx = x0 + p * 16 + jl;
-        if (xx >= Wi) continue;
+    for (int c = 0; c < CB; c += 2) {
+        const int m = (mb0 + c) * 16, ra2 = m / (2 * Cout);   // output row of the pair's four, and the channel in it
+        const __amdgpu_buffer_rsrc_t ry = rsrc(Y + (((int64_t)n * 2 * Hi + 2 * y + ra2) * Wo + 2 * x0) * sy);
 #pragma unroll
-        for (int c = 0; c < CB; ++c) {
-            const int mrow = (mb0 + c) * 16 + 4 * g;     // four consecutive rows: same (a, d)
-            const int ad = mrow / Cout, co = mrow - ad * Cout;
-            const int yo = 2 * y + (ad >> 1), xo = 2 * xx + (ad & 1);
-            s4 o;
+        for (int p = 0; p < 4; ++p) {
+            u32x2 o[2];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (short)f2bf(acc[p][c][e] + bias[co + e]);
-            *reinterpret_cast<s4*>(Y + (((int64_t)n * 2 * Hi + yo) * Wo + xo) * sy + co) = o;
+            for (int h = 0; h < 2; ++h) {
+                f4 v = acc[p][c + h];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] += bs[c + h][e];
+                o[h] = u32x2{pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3])};
+            }
+            store16(merge_blocks(o[0], o[1]), ry, po[p] + 2 * (m - ra2 * 2 * Cout));
         }
     }
 }
@@ -698,20 +984,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
     const int64_t per = (int64_t)4 * Cout * Cin;
     wgrad_out<4, CB, IB>(acc, bacc, reinterpret_cast<float*>(smem), co0, ci0, Cout, Cin, part + blockIdx.x * per,
                          bpart + (int64_t)blockIdx.x * Cout);
-}
-
-// Output layer (1x1, 16 -> 1): o[p] = b + sum_c w[c] x[p][c], float32.
-__global__ void k_out(const bf16_t* __restrict__ X, int sx, const bf16_t* __restrict__ w, const float* bias,
-                      float* __restrict__ o, int64_t npix) {
-    for (int64_t p = blockIdx.x * (int64_t)NT + threadIdx.x; p < npix; p += (int64_t)gridDim.x * NT) {
-        bf8u x[2];
-        x[0].u = *reinterpret_cast<const uint4*>(X + p * sx);
-        x[1].u = *reinterpret_cast<const uint4*>(X + p * sx + 8);
-        float s = bias[0];
-#pragma unroll
-        for (int c = 0; c < 16; ++c) s += bf2f(w[c]) * bf2f(x[c >> 3].h[c & 7]);
-        o[p] = s;
-    }
 }
 
 // Back through the output layer: g[p][c] = bf16(w[c] go[p]) masked by the
@@ -1063,56 +1335,61 @@ struct Ctx {
     int w(int lvl) const { return U->W >> lvl; }
 };
 
-// Eight waves of one output row each: a chunk's weight operands, staged once
-// per workgroup, feed twice the MFMAs of a four-wave workgroup (0.68 against
-// 0.70 ms for the network forward on 8 images of 408 x 808; two rows per wave
-// or sixteen waves were slower, the latter spilling).
-template <int CB, int CK, bool MASK>
-void launch_conv3(const Ctx& c, const Tv& X, int K, const bf16_t* Af, const float* bias, const Tv& Y, int M, int H,
-                  int W, bool relu, const bf16_t* act) {
-    constexpr int RPW = 1, NWV = 8;
+template <int CB, int CK, int EPI, bool RES, bool IN>
+void launch_conv3(const Ctx& c, const ConvArgs& A, int M) {
+    // Waves of all 64 pixels, so that a weight operand serves 8 sums; with 64 outputs
+    // the sums of half a row fill the registers.
+    constexpr int PG = CB == 4 ? 2 : 4;
+    using T = Conv3Tile<CB, CK, PG>;
     // persistent grid: as many workgroups as the device holds at once
     static int resident = 0;
     if (!resident) {
         int per_cu = 0, cus = 0, dev = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_conv3<CB, RPW, CK, NWV, MASK>, 64 * NWV, 0) != hipSuccess)
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_conv3<CB, CK, PG, EPI, RES, IN>, T::NTW, 0) != hipSuccess)
             per_cu = 1, cus = 256;
         resident = std::max(1, per_cu) * std::max(1, cus);
     }
-    const int rows = NWV * RPW;
-    const int64_t ntiles = (int64_t)((W + 63) / 64) * ((H + rows - 1) / rows) * c.N * (M / (16 * CB));
-    const int grid = (int)std::min<int64_t>(ntiles, resident);
-    hipLaunchKernelGGL((k_conv3<CB, RPW, CK, NWV, MASK>), dim3(grid), dim3(64 * NWV), 0, c.U->stream, X.p, X.s, X.hs, X.split, K, Af,
-                       (M + 15) / 16, bias, Y.p, Y.s, Y.hs, Y.split, M, H, W, c.N, relu ? 1 : 0, act);
+    const int ncog = M / (16 * CB);
+    const int ntiles = ((A.W + 63) / 64) * ((A.H + T::ROWS - 1) / T::ROWS) * A.N;
+    const int grid = std::min(ntiles, std::max(1, resident / ncog));
+    hipLaunchKernelGGL((k_conv3<CB, CK, PG, EPI, RES, IN>), dim3(grid, ncog), dim3(T::NTW), 0, c.U->stream, A);
 }
 
-// K input channels (Cin, or Cout for the data gradient) to M outputs; act: the
-// activation whose ReLU a data gradient passes (nullptr: none)
-esi_status_t conv3(const Ctx& c, const Tv& X, int K, int layer, bool bwd, const Tv& Y, int M, int lvl, bool relu,
-                   const bf16_t* act = nullptr) {
+// K input channels (Cin, or Cout for a data gradient) to M outputs at level
+// lvl; A brings what the epilogue needs.
+template <int EPI, bool IN = false>
+esi_status_t conv3(const Ctx& c, const Tv& X, int K, int layer, const Tv& Y, int M, int lvl, ConvArgs A = {}) {
+    constexpr bool BWD = EPI == E_GRAD || EPI == E_MASK;
     Unet* U = c.U;
     const Layer& Ly = U->L[layer];
-    const bf16_t* Af = bwd ? Ly.wb : Ly.wf;
-    const float* bias = bwd ? nullptr : U->theta + Ly.off + Ly.nw;
-    const int H = c.h(lvl), W = c.w(lvl);
-    if (K % 16 || M % 16) return fail(ESI_ERR_SHAPE, "3x3 convolution channels must be multiples of 16");
-    const int cb = M >= 64 ? 4 : M / 16;
-    auto launch = [&](auto mask) {
-        constexpr bool MASK = decltype(mask)::value;
-        if (frag_ck(K) == 32) {
-            if (cb == 4) launch_conv3<4, 32, MASK>(c, X, K, Af, bias, Y, M, H, W, relu, act);
-            else if (cb == 2) launch_conv3<2, 32, MASK>(c, X, K, Af, bias, Y, M, H, W, relu, act);
-            else launch_conv3<1, 32, MASK>(c, X, K, Af, bias, Y, M, H, W, relu, act);
-        } else {
-            if (cb == 4) launch_conv3<4, 16, MASK>(c, X, K, Af, bias, Y, M, H, W, relu, act);
-            else if (cb == 2) launch_conv3<2, 16, MASK>(c, X, K, Af, bias, Y, M, H, W, relu, act);
-            else launch_conv3<1, 16, MASK>(c, X, K, Af, bias, Y, M, H, W, relu, act);
-        }
-    };
-    if (act) launch(std::true_type{});
-    else launch(std::false_type{});
+    A.X = X.p; A.sx = X.s; A.xhs = X.hs; A.xsplit = X.split; A.K = K;
+    A.Af = BWD ? Ly.wb : Ly.wf;
+    A.ncb = (M + 15) / 16;
+    A.bias = BWD ? nullptr : U->theta + Ly.off + Ly.nw;
+    A.Y = Y.p; A.sy = Y.s; A.yhs = Y.hs; A.ysplit = Y.split;
+    A.H = c.h(lvl); A.W = c.w(lvl); A.N = c.N;
+    const int ck = frag_ck(K);
+    if (K % 16 || M % 16 || (K > 16 && K % 32) || (M > 32 && M % 64))
+        return fail(ESI_ERR_SHAPE, "3x3 convolution channels outside the supported set");
+    if (X.split < K && X.split % ck && K != ck) return fail(ESI_ERR_SHAPE, "a chunk of channels spans two tensors");
+    // weights in registers: one chunk and at most 20 blocks of 4 registers
+    if constexpr (EPI == E_OUT || IN) {
+        if (K != 16 || M != 16) return fail(ESI_ERR_SHAPE, "fused first and last convolutions have 16 channels");
+        launch_conv3<1, 16, EPI, true, IN>(c, A, M);
+    } else if (ck == 16) {
+        if (M == 16) launch_conv3<1, 16, EPI, true, false>(c, A, M);
+        else launch_conv3<2, 16, EPI, true, false>(c, A, M);
+    } else if (M >= 64) {
+        launch_conv3<4, 32, EPI, false, false>(c, A, M);
+    } else if (M == 32) {
+        if (K == 32) launch_conv3<2, 32, EPI, true, false>(c, A, M);
+        else launch_conv3<2, 32, EPI, false, false>(c, A, M);
+    } else {
+        if (K == 32) launch_conv3<1, 32, EPI, true, false>(c, A, M);
+        else launch_conv3<1, 32, EPI, false, false>(c, A, M);
+    }
     ESI_HIP_TRY(hipGetLastError());
     return ESI_OK;
 }
@@ -1175,7 +1452,7 @@ esi_status_t convT_fwd(const Ctx& c, int layer, const bf16_t* X, int sx, bf16_t*
     const int Hi = c.h(lvl_in), Wi = c.w(lvl_in);
     const float* bias = U->theta + Ly.off + Ly.nw;
     // 4 Cout rows of D in blocks of 64; Cin in blocks of 32 (32, 64 or 128)
-    if (Ly.cout % 16 || (Ly.cin != 32 && Ly.cin != 64 && Ly.cin != 128))
+    if (Ly.cout % 16 || sy != Ly.cout || (Ly.cin != 32 && Ly.cin != 64 && Ly.cin != 128))
         return fail(ESI_ERR_SHAPE, "transposed convolution channels outside the supported set");
     if (Ly.cin == 32) launch_convT<4, 1>(c, Ly, X, sx, bias, Y, sy, Hi, Wi);
     else if (Ly.cin == 64) launch_convT<4, 2>(c, Ly, X, sx, bias, Y, sy, Hi, Wi);
@@ -1225,47 +1502,46 @@ esi_status_t convT_back(const Ctx& c, int layer, const bf16_t* X, int sx, const 
     return launch_convT_wgrad<2, 2>(c, Ly, X, sx, GY, sg, Hi, Wi, gflat + Ly.off);
 }
 
-esi_status_t pool(const Ctx& c, const bf16_t* X, int sx, bf16_t* Y, int sy, int C, int lvl_in) {
-    const int64_t n = c.pix(lvl_in + 1) * (C / 8);
-    hipLaunchKernelGGL(k_pool, dim3(grid_for(n)), dim3(NT), 0, c.U->stream, X, sx, Y, sy, C, c.N,
-                       c.h(lvl_in + 1), c.w(lvl_in + 1));
-    ESI_HIP_TRY(hipGetLastError());
-    return ESI_OK;
-}
-
-esi_status_t forward(const Ctx& c, const float* x, float* o) {
+// Forward pass.  Activations of every layer are left for a backward pass if
+// `train`; else the padded input and the last convolution's output are not
+// formed (168 MB of 8 images of 408 x 808 written and read).
+esi_status_t forward(const Ctx& c, const float* x, float* o, bool train) {
     Unet* U = c.U;
     const int64_t HW = (int64_t)U->H * U->W;
     auto T = [](bf16_t* p, int s) { return Tv{p, s}; };
-    hipLaunchKernelGGL(k_input, dim3(grid_for(c.N * HW)), dim3(NT), 0, U->stream, x, c.a(A_X), c.N, HW);
     // encoder: each level's second convolution writes the skip half of the
-    // decoder's concatenation buffer, which the pooling reads
-    ESI_TRY(conv3(c, c.at(A_X), 16, C1A, false, c.at(A_A1), 16, 0, true));
-    ESI_TRY(conv3(c, c.at(A_A1), 16, C1B, false, T(c.ah(A_CAT1, 1), 16), 16, 0, true));
-    ESI_TRY(pool(c, c.ah(A_CAT1, 1), 16, c.a(A_P1), 16, 16, 0));
-    ESI_TRY(conv3(c, c.at(A_P1), 16, C2A, false, c.at(A_A2), 32, 1, true));
-    ESI_TRY(conv3(c, c.at(A_A2), 32, C2B, false, T(c.ah(A_CAT2, 1), 32), 32, 1, true));
-    ESI_TRY(pool(c, c.ah(A_CAT2, 1), 32, c.a(A_P2), 32, 32, 1));
-    ESI_TRY(conv3(c, c.at(A_P2), 32, C3A, false, c.at(A_A3), 64, 2, true));
-    ESI_TRY(conv3(c, c.at(A_A3), 64, C3B, false, T(c.ah(A_CAT3, 1), 64), 64, 2, true));
-    ESI_TRY(pool(c, c.ah(A_CAT3, 1), 64, c.a(A_P3), 64, 64, 2));
-    ESI_TRY(conv3(c, c.at(A_P3), 64, C4A, false, c.at(A_A4), 128, 3, true));
-    ESI_TRY(conv3(c, c.at(A_A4), 128, C4B, false, c.at(A_B4), 128, 3, true));
+    // decoder's concatenation buffer and the next level's pooled input
+    auto pooled = [](bf16_t* p) { ConvArgs A = {}; A.pool = p; return A; };
+    if (train) {
+        hipLaunchKernelGGL(k_input, dim3(grid_for(c.N * HW)), dim3(NT), 0, U->stream, x, c.a(A_X), c.N, HW);
+        ESI_TRY(conv3<E_FWD>(c, c.at(A_X), 16, C1A, c.at(A_A1), 16, 0));
+    } else {
+        ConvArgs A = {};
+        A.xin = x;
+        ESI_TRY((conv3<E_FWD, true>(c, c.at(A_X), 16, C1A, c.at(A_A1), 16, 0, A)));
+    }
+    ESI_TRY(conv3<E_POOL>(c, c.at(A_A1), 16, C1B, T(c.ah(A_CAT1, 1), 16), 16, 0, pooled(c.a(A_P1))));
+    ESI_TRY(conv3<E_FWD>(c, c.at(A_P1), 16, C2A, c.at(A_A2), 32, 1));
+    ESI_TRY(conv3<E_POOL>(c, c.at(A_A2), 32, C2B, T(c.ah(A_CAT2, 1), 32), 32, 1, pooled(c.a(A_P2))));
+    ESI_TRY(conv3<E_FWD>(c, c.at(A_P2), 32, C3A, c.at(A_A3), 64, 2));
+    ESI_TRY(conv3<E_POOL>(c, c.at(A_A3), 64, C3B, T(c.ah(A_CAT3, 1), 64), 64, 2, pooled(c.a(A_P3))));
+    ESI_TRY(conv3<E_FWD>(c, c.at(A_P3), 64, C4A, c.at(A_A4), 128, 3));
+    ESI_TRY(conv3<E_FWD>(c, c.at(A_A4), 128, C4B, c.at(A_B4), 128, 3));
     // decoder: the transposed convolution writes the first half
     ESI_TRY(convT_fwd(c, U3, c.a(A_B4), 128, c.ah(A_CAT3, 0), 64, 3));
-    ESI_TRY(conv3(c, c.at(A_CAT3), 128, D3A, false, c.at(A_D3A), 64, 2, true));
-    ESI_TRY(conv3(c, c.at(A_D3A), 64, D3B, false, c.at(A_D3B), 64, 2, true));
+    ESI_TRY(conv3<E_FWD>(c, c.at(A_CAT3), 128, D3A, c.at(A_D3A), 64, 2));
+    ESI_TRY(conv3<E_FWD>(c, c.at(A_D3A), 64, D3B, c.at(A_D3B), 64, 2));
     ESI_TRY(convT_fwd(c, U2, c.a(A_D3B), 64, c.ah(A_CAT2, 0), 32, 2));
-    ESI_TRY(conv3(c, c.at(A_CAT2), 64, D2A, false, c.at(A_D2A), 32, 1, true));
-    ESI_TRY(conv3(c, c.at(A_D2A), 32, D2B, false, c.at(A_D2B), 32, 1, true));
+    ESI_TRY(conv3<E_FWD>(c, c.at(A_CAT2), 64, D2A, c.at(A_D2A), 32, 1));
+    ESI_TRY(conv3<E_FWD>(c, c.at(A_D2A), 32, D2B, c.at(A_D2B), 32, 1));
     ESI_TRY(convT_fwd(c, U1, c.a(A_D2B), 32, c.ah(A_CAT1, 0), 16, 1));
-    ESI_TRY(conv3(c, c.at(A_CAT1), 32, D1A, false, c.at(A_D1A), 16, 0, true));
-    ESI_TRY(conv3(c, c.at(A_D1A), 16, D1B, false, c.at(A_D1B), 16, 0, true));
+    ESI_TRY(conv3<E_FWD>(c, c.at(A_CAT1), 32, D1A, c.at(A_D1A), 16, 0));
     const Layer& Lo = U->L[OUT];
-    hipLaunchKernelGGL(k_out, dim3(grid_for(c.pix(0))), dim3(NT), 0, U->stream, c.a(A_D1B), 16, Lo.wf,
-                       U->theta + Lo.off + Lo.nw, o, c.pix(0));
-    ESI_HIP_TRY(hipGetLastError());
-    return ESI_OK;
+    ConvArgs A = {};
+    A.wo = Lo.wf;
+    A.bo = U->theta + Lo.off + Lo.nw;
+    A.o = o;
+    return conv3<E_OUT>(c, c.at(A_D1A), 16, D1B, train ? c.at(A_D1B) : T(nullptr, 16), 16, 0, A);
 }
 
 // Backward pass from U->go into the flat gradient gflat (after forward()).
@@ -1293,8 +1569,10 @@ esi_status_t backward(const Ctx& c, float* gflat) {
                          const bf16_t* act = nullptr) -> esi_status_t {
         const Layer& Ly = U->L[layer];
         ESI_TRY(conv3_wgrad(c, GY, Cout, X, Cin, Ly.cin, lvl, gflat + Ly.off));
-        if (GX.p) ESI_TRY(conv3(c, GY, Cout, layer, true, GX, Cin, lvl, false, act));
-        return ESI_OK;
+        if (!GX.p) return ESI_OK;
+        ConvArgs A = {};
+        A.act = act;
+        return act ? conv3<E_MASK>(c, GY, Cout, layer, GX, Cin, lvl, A) : conv3<E_GRAD>(c, GY, Cout, layer, GX, Cin, lvl);
     };
     // level 1 decoder: d1b, d1a (d1b's gradient is already masked)
     ESI_TRY(conv_back(D1B, c.gt(A_D1B), 16, c.at(A_D1A), 16, 0, c.gt(A_D1A), c.a(A_D1A)));
@@ -1479,7 +1757,7 @@ extern "C" esi_status_t esi_unet_forward(esi_unet_t u, const float* x, float* o,
     Unet* U = as_unet(u);
     if (batch < 1 || batch > U->maxb) return fail(ESI_ERR_ARG, "batch outside [1, max_batch]");
     Ctx c{U, batch};
-    return forward(c, x, o);
+    return forward(c, x, o, false);
 }
 
 extern "C" esi_status_t esi_unet_loss_weights(const float* a, const float* c, int32_t batch, int64_t npix,
@@ -1502,7 +1780,7 @@ extern "C" esi_status_t esi_unet_loss_grad(esi_unet_t u, const float* x, const f
     const int64_t npix = (int64_t)U->H * U->W;
     ESI_TRY(grow_t(&U->part, &U->part_cap, (int64_t)batch * npix, U->stream));   // o scratch
     float* o = U->part;
-    ESI_TRY(forward(c, x, o));
+    ESI_TRY(forward(c, x, o, true));
     double* sums = U->dloss + U->maxb;                     // [batch][LOSS_BLOCKS][2], then the loss partials
     double* lpart = sums + (int64_t)U->maxb * LOSS_BLOCKS * 2;
     if (!weight)
@@ -1562,7 +1840,7 @@ esi_status_t unet_forward_on(esi_unet_t u, hipStream_t stream, const float* x, f
     hipStream_t own = U->stream;
     U->stream = stream;
     Ctx c{U, batch};
-    esi_status_t st = forward(c, x, o);
+    esi_status_t st = forward(c, x, o, false);
     U->stream = own;
     return st;
 }
