@@ -54,16 +54,19 @@ static int64_t launch_tiles(Plan* P, int tx, int tz, int shot0, int nshots) {
 // A launch of few tiles lasts as long as one workgroup takes, four waves that
 // issue the instructions of their rows one after another: there two-step loops
 // take the shortest tiles that keep the launch within about four workgroups per
-// CU.  Microseconds per launch, CG (forward pass and adjoint, averaged) on
-// grids of 10 m cells, 32 / 24 / 16 / 8 rows:
-//   201 x 201, 1 shot:   10.15 /  9.11 /  7.96 /  6.91  (8 rows: 155 workgroups)
-//   401 x 201, 4 shots:  12.23 / 11.71 / 10.70 / 10.42  (992)
-//   401 x 201, 8 shots:  15.13 / 14.69 / 14.20 / 16.03  (16 rows: 1024)
-//   801 x 401, 2 shots:  15.09 / 14.49 / 13.98 / 15.10  (16 rows: 896)
-//   801 x 401, 4 shots:  21.41 / 21.01 / 21.67 / 23.96  (24 rows: 1216)
+// CU (three of 8 rows, whose rings cost most).  Microseconds per launch, CG
+// (forward pass and adjoint, averaged) on grids of 10 m cells, 32 / 24 / 16 / 8 rows:
+//   201 x 201, 1 shot:    9.56 /  8.57 /  7.09 /  6.25  (8 rows: 155 workgroups)
+//   401 x 201, 3 shots:  10.94 / 10.21 /  9.18 /  8.69  (8 rows: 744)
+//   401 x 201, 4 shots:  11.48 / 10.78 /  9.59 /  9.73  (8 rows: 992)
+//   401 x 201, 8 shots:  14.15 / 13.83 / 13.16 / 14.78  (16 rows: 1024)
+//   801 x 401, 2 shots:  14.10 / 13.77 / 12.99 / 14.27  (16 rows: 896)
+//   801 x 401, 3 shots:  17.77 / 17.41 / 17.21 / 18.61  (24 rows: 912; 16 rows,
+//                        1344, take 9.87 modelling against 9.18)
+//   801 x 401, 4 shots:  20.47 / 20.43 / 20.24 / 22.75  (24 rows: 1216)
 // and 8 shots of 801 x 401 run fastest on 32 rows.
 int loop_shape(Plan* P, unsigned flags, bool adjoint, int shot0, int nshots) {
-    constexpr struct { int shape, most; } SMALL[] = {{LS_T2_8, 1024}, {LS_T2_16, 1024}, {LS_T2_24, 1280}};
+    constexpr struct { int shape, most; } SMALL[] = {{LS_T2_8, 768}, {LS_T2_16, 1024}, {LS_T2_24, 1280}};
     int want = adjoint ? P->tb_adj : P->tb_fwd;
     if (P->ndim == 2) {
         if (want != LS_ONE && P->small_tiles) {

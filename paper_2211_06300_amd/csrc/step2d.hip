@@ -113,15 +113,15 @@ struct StepPtrs {
 
 // Shot and tile of workgroup L: from the batch's work list when shots have
 // apertures, else tile fastest within a shot.
-__device__ __forceinline__ void work_item(const StepArgs& a, int L, int* s, int* t) {
+__device__ __forceinline__ void work_item(const StepArgs& a, int L, int tiles, int* s, int* t) {
     if (a.work) {
         const int w = a.work[L];
-        const int gs = w / a.tiles;
+        const int gs = w / tiles;
         *s = gs - a.shot0;
-        *t = w - gs * a.tiles;
+        *t = w - gs * tiles;
     } else {
-        *s = L / a.tiles;
-        *t = L - *s * a.tiles;
+        *s = L / tiles;
+        *t = L - *s * tiles;
     }
 }
 
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256, ESI_MINW) void k_step2d(const StepArgs a) {
     // of one shot's fields (shot-fastest, to share c2 in L2, fetched fewer
     // bytes but ran slower: the scattered streams cost more than they save)
     int s, t;
-    work_item(a, xcd_remap(blockIdx.x, gridDim.x), &s, &t);
+    work_item(a, xcd_remap(blockIdx.x, gridDim.x), a.tiles, &s, &t);
     if (a.active && !a.active[s]) return;   // uniform over the workgroup
     const int gs = a.shot0 + s;
     const Aperture ap = aperture(a, gs);
@@ -503,14 +503,22 @@ __global__ __launch_bounds__(256, ESI_MINW) void k_step2d(const StepArgs a) {
 //  * the z differences u_{+k} - u of a row serve as the negated u_{-k} - u of
 //    the row k below: (u_{+k} - u) + (u_{-k} - u) in one subtraction.
 //  * a thread reads the injection entry of its own index while the tile's loads
-//    fly and drops it into an LDS plane that is dead at the time.
+//    fly and drops it into an LDS plane that is dead at the time;
+//  * a launch of few tiles lasts as long as its chain of memory latencies, of
+//    which the arguments, the shot's and tile's entries, the lists and the fields
+//    were six or seven, 1.2 to 2.1 us before the first field load was issued, and
+//    the partial sum at the end another 0.6.  The workgroup now touches every
+//    line of its arguments at once, reads all the uniform values of its shot and
+//    tile in one batch and, on short tiles, has the fields on their way before it
+//    waits for them (T2Head).
 // Interior tiles of the modelling variant issue 725 vector and 427 scalar
 // instructions.  Microseconds per launch on 32-row tiles, before and now:
 // modelling 32 shots of 801 x 401, 60.1 and 41.4 (its state moved at 5.6 TB/s);
 // CG on 8 of them (forward pass, adjoint), 42.7 and 33.6, now 40.4 and 30.4; FWI
 // windows, 32 shots of 1601 x 601 (modelling, segment recompute, correlating
 // adjoint), 65.3, 95.8 and 110.4, now 51.1, 83.8 and 89.0; one shot of 201 x 201
-// (modelling, CG forward and adjoint averaged), 8.7 and 16.3, now 6.9 and 10.2.
+// (modelling, CG forward and adjoint averaged), 8.7 and 16.3, now 6.4 and 9.6 (on
+// 8-row tiles 5.6 and 6.9 before the batched reads, now 4.1 and 6.2).
 constexpr int T2W = 56;                           // output tile width
 constexpr int A_W = T2W + 2 * HALO;               // 64: first-step region width
 constexpr int U0W = T2W + 4 * HALO;               // 72
@@ -588,15 +596,68 @@ struct LapZ {
 template <unsigned FL, int TH>
 constexpr int t2_waves() { return (FL & F_INJ) != 0 && (FL & F_NORMAL) == 0 && TH <= 32 ? 5 : 4; }
 
+template <int TH>
+struct T2 {
+    static constexpr int A_H = TH + 2 * HALO;     // first-step region rows
+    static constexpr int RZ2 = TH / 4;            // tile rows per wave
+    static constexpr int NR = RZ2 + 2;            // rows per wave in the first step: tile rows, then two ring rows
+    static constexpr int U0H = TH + 4 * HALO;
+    static constexpr int RPW0 = U0H / 4, NHL = (U0H + 31) / 32;   // staged rows per wave, loads of the last 8 columns
+};
+
+// Region row of wave wv's row i in the first step: its tile rows, then two ring rows
+template <int TH>
+__device__ __forceinline__ int t2_row(int wv, int i) {
+    constexpr int RZ2 = T2<TH>::RZ2;
+    return i < RZ2 ? wv * RZ2 + HALO + i : (wv < 2 ? 2 * wv : TH + 2 * wv) + i - RZ2;
+}
+
+// Padded (z0 - 8 + r, x0 - 8 + c) of a field for U0 (r, c): 64 columns a row per
+// wave, the other 8 of 32 rows at a time over the workgroup.
+template <int TH, bool GEN>
+__device__ __forceinline__ void t2_stage(const StepArgs& a, const Buf& cur, int z0, int x0, float (&tb)[T2<TH>::RPW0],
+                                         float (&th)[T2<TH>::NHL]) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t XB = 4u * (uint32_t)a.XS;
+    const int xb = x0 - 2 * HALO + lane, hr = tid >> 3;
+    const uint32_t vb = !GEN || (unsigned)xb < (unsigned)a.nxp ? 4u * (uint32_t)(xb + GH) : OOB;
+#pragma unroll
+    for (int k = 0; k < T2<TH>::RPW0; ++k) {
+        const int z = z0 - 2 * HALO + wv + 4 * k;
+        tb[k] = cur.ld(vb, !GEN || (unsigned)z < (unsigned)a.nzp ? (uint32_t)(z + GH) * XB : 0u);
+    }
+    const int xh = x0 - 2 * HALO + 64 + (tid & 7);
+#pragma unroll
+    for (int k = 0; k < T2<TH>::NHL; ++k) {
+        const int z = z0 - 2 * HALO + hr + 32 * k;
+        const bool in = (!GEN || (xh < a.nxp && (unsigned)z < (unsigned)a.nzp)) && hr + 32 * k < T2<TH>::U0H;
+        th[k] = cur.ld(in ? (uint32_t)(z + GH) * XB + 4u * (uint32_t)(xh + GH) : OOB, 0u);
+    }
+}
+
+// What a workgroup reads before it knows which kind of tile it has: the uniform
+// values of its shot and tile, and on short tiles (EARLY) the fields.
+template <int TH>
+struct T2Head {
+    int s, t, lo, hi;                             // shot, tile, aperture
+    int ibeg, iend, gbeg, gend;                   // the tile's injection and recording entries
+    int sx, sz;                                   // the shot's source
+    int64_t rec0, rec_s, rec_e;                   // receivers: first of the batch, the shot's range
+    double al, be, part;
+    float tb[T2<TH>::RPW0], th[T2<TH>::NHL], c[T2<TH>::NR], d[T2<TH>::NR];
+};
+template <int TH>
+constexpr bool t2_early() { return TH <= 16; }
+
 template <unsigned FL, int TH, bool GEN>
-__device__ __forceinline__ void step2d_t2_body(const StepArgs& a, int s, int t, const Aperture& ap, int ibeg, int iend,
-                                               int srow, int scol, float* __restrict__ U0, float* __restrict__ U1,
-                                               double& acc) {
+__device__ __forceinline__ void step2d_t2_body(const StepArgs& a, T2Head<TH>& h, int srow, int scol,
+                                               float* __restrict__ U0, float* __restrict__ U1, double& acc) {
     constexpr int T2Z = TH;                       // output tile rows
-    constexpr int A_H = T2Z + 2 * HALO;           // first-step region rows
-    constexpr int RZ2 = T2Z / 4;                  // tile rows per wave
-    constexpr int NR = RZ2 + 2;                   // rows per wave in the first step: tile rows, then two ring rows
-    constexpr int U0H = T2Z + 4 * HALO;
+    constexpr int A_H = T2<TH>::A_H, RZ2 = T2<TH>::RZ2, NR = T2<TH>::NR, U0H = T2<TH>::U0H;
+    constexpr bool EARLY = t2_early<TH>();
+    const int s = h.s, t = h.t, ibeg = h.ibeg, iend = h.iend;
+    const Aperture ap = {h.lo, h.hi, a.kx + (int64_t)a.kx_stride * (a.shot0 + h.s)};
     static_assert(T2Z % 4 == 0 && U0H % 4 == 0 && U0H <= 64, "two-step tile geometry");
     float* const sinjB = U0;
     static_assert(U0H * U0W >= A_H * A_W, "the second step's injection fits the u^{tA} buffer");
@@ -610,7 +671,6 @@ __device__ __forceinline__ void step2d_t2_body(const StepArgs& a, int s, int t, 
     constexpr bool DENSE = (FL & (F_SRC_DENSE | F_DTFT_SRC | F_CG_FUSE)) != 0;
     constexpr bool RUPD = (FL & F_RUPD) != 0, SCALE = (FL & F_SCALE) != 0;
 
-    const int gs = a.shot0 + s;
     const int tzi = t / a.tiles_x, txi = t - tzi * a.tiles_x;
     const int x0 = txi * T2W, z0 = tzi * T2Z;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -632,30 +692,14 @@ __device__ __forceinline__ void step2d_t2_body(const StepArgs& a, int s, int t, 
     auto prow = [&](int z) -> uint32_t { return zph(z) ? (uint32_t)(z - a.nb) * NXB : 0u; };
     auto pmask = [&](int z) -> uint32_t { return zph(z) ? 0u : OOB; };
 
-    // U0 (r, c) <- padded (z0 - 8 + r, x0 - 8 + c): 64 columns a row per wave,
-    // the other 8 of 32 rows at a time over the workgroup.
-    constexpr int RPW0 = U0H / 4, NHL = (U0H + 31) / 32;
-    float tb[RPW0], th[NHL];
+    constexpr int RPW0 = T2<TH>::RPW0, NHL = T2<TH>::NHL;
+    float (&tb)[RPW0] = h.tb, (&th)[NHL] = h.th;
     const int hr = tid >> 3, hc = tid & 7;
-    {
-        const int xb = x0 - 2 * HALO + lane;
-        const uint32_t vb = !GEN || (unsigned)xb < (unsigned)a.nxp ? 4u * (uint32_t)(xb + GH) : OOB;
-#pragma unroll
-        for (int k = 0; k < RPW0; ++k) tb[k] = cur.ld(vb, frow(z0 - 2 * HALO + wv + 4 * k));
-        const int xh = x0 - 2 * HALO + 64 + hc;
-#pragma unroll
-        for (int k = 0; k < NHL; ++k) {
-            const int z = z0 - 2 * HALO + hr + 32 * k;
-            const bool in = (!GEN || (xh < a.nxp && (unsigned)z < (unsigned)a.nzp)) && hr + 32 * k < U0H;
-            th[k] = cur.ld(in ? (uint32_t)(z + GH) * XB + 4u * (uint32_t)(xh + GH) : OOB, 0u);
-        }
-    }
+    if constexpr (!EARLY) t2_stage<TH, GEN>(a, cur, z0, x0, tb, th);
 
     // ---- this lane's column and this wave's rows: row i of the first step is
     // padded row zrow(i), region row rrow(i)
-    const int zt = z0 + wv * RZ2;                          // first tile row
-    const int rr0 = wv < 2 ? 2 * wv : T2Z + 2 * wv;        // first ring row, region coordinates
-    auto rrow = [&](int i) { return i < RZ2 ? wv * RZ2 + HALO + i : rr0 + i - RZ2; };
+    auto rrow = [&](int i) { return t2_row<TH>(wv, i); };
     auto zrow = [&](int i) { return z0 - HALO + rrow(i); };
     const int x = x0 - HALO + lane;                        // padded column
     const int ix = x - a.nb;
@@ -669,11 +713,16 @@ __device__ __forceinline__ void step2d_t2_body(const StepArgs& a, int s, int t, 
     const uint32_t vc = !GEN || (x >= ap.lo && x < ap.hi + 2 * a.nb) ? 4u * (uint32_t)(x + GH) : OOB;
     const uint32_t vp = xph ? 4u * (uint32_t)ix : OOB;     // dense column
     const uint32_t vo = xout ? 4u * (uint32_t)ix : OOB;    // dense column of the tile
-    float c[NR], d[NR], kz[GEN ? NR : 1], qA[NR], poA[NR], rA[NR], xoA[RZ2], pvA[RZ2];
+    float (&c)[NR] = h.c, (&d)[NR] = h.d;
+    float kz[GEN ? NR : 1], qA[NR], poA[NR], rA[NR], xoA[RZ2], pvA[RZ2];
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
-        c[i] = c2.ld(vc, frow(zrow(i)));
-        d[i] = din.ld(vf, frow(zrow(i)));
+        if constexpr (!EARLY) {
+            c[i] = c2.ld(vc, frow(zrow(i)));
+            d[i] = din.ld(vf, frow(zrow(i)));
+        } else {
+            c[i] = vc != OOB ? c[i] : 0.f;   // 0 outside the aperture
+        }
         if constexpr (GEN) kz[i] = at(a.kz, (uint32_t)min(max(zrow(i), 0), a.nzp - 1));
         qA[i] = 0.f; poA[i] = 0.f; rA[i] = 0.f;
         if (i < RZ2) { xoA[i] = 0.f; pvA[i] = 0.f; }
@@ -709,8 +758,8 @@ __device__ __forceinline__ void step2d_t2_body(const StepArgs& a, int s, int t, 
     if constexpr ((FL & F_DTFT_SRC) != 0) dtft_q(tA, qA, std::integral_constant<int, NR>{});
     float alp = 0.f, bet = 0.f;
     if constexpr ((FL & F_CG_FUSE) != 0) {
-        alp = (float)a.cg_alpha[s];
-        bet = (float)a.cg_beta[s];
+        alp = (float)h.al;
+        bet = (float)h.be;
         dense(a.cg_p + vA, vp, poA, NR);
         dense(a.cg_r + vA, vp, qA, NR);
         dense(a.cg_x + vA, vo, xoA, RZ2);
@@ -728,9 +777,9 @@ __device__ __forceinline__ void step2d_t2_body(const StepArgs& a, int s, int t, 
 
     // ---- the tile's receivers: this thread's entry (cell, values of both
     // steps; more than 256 entries loop), read while the tile's loads fly
-    const int64_t nrec_s = (FL & (F_INJ | F_GATHER)) ? a.rec_ptr[gs + 1] - a.rec_ptr[gs] : 0;
-    const int64_t doff = (FL & (F_INJ | F_GATHER)) ? (int64_t)a.nt * (a.rec_ptr[gs] - a.rec_ptr[a.shot0]) : 0;
-    int gbeg = 0, gend = 0, icell = 0, gcell = 0, grid = 0;
+    const int64_t nrec_s = h.rec_e - h.rec_s, doff = (int64_t)a.nt * (h.rec_s - h.rec0);
+    int icell = 0, gcell = 0, grid = 0;
+    const int gbeg = h.gbeg, gend = h.gend;
     float ivA = 0.f, ivB = 0.f;
     // sum of the data of step `tt` over the receivers of injection entry e
     auto inj_value = [&](int e, int tt) -> float {
@@ -740,16 +789,22 @@ __device__ __forceinline__ void step2d_t2_body(const StepArgs& a, int s, int t, 
         return v;
     };
     if constexpr (GEN && (FL & F_INJ) != 0) {
-        if (ibeg + tid < iend) {
-            icell = a.inj2_cell[ibeg + tid];
-            ivA = inj_value(ibeg + tid, tA);
-            ivB = inj_value(ibeg + tid, tB);
+        // Receiver list entry e is the entry's own while every cell so far holds one
+        // receiver: its data is on the way before the list's bounds say so.
+        const int e = ibeg + tid;
+        if (e < iend) {
+            icell = a.inj2_cell[e];
+            const int r0 = a.inj2_rptr[e], r1 = a.inj2_rptr[e + 1], rid = a.inj2_rid[e];
+            const float* dj = a.inj_data + doff;
+            ivA = 0.f + dj[(int64_t)tA * nrec_s + rid];
+            ivB = 0.f + dj[(int64_t)tB * nrec_s + rid];
+            if (r0 != e || r1 != e + 1) {
+                ivA = inj_value(e, tA);
+                ivB = inj_value(e, tB);
+            }
         }
     }
     if constexpr ((FL & F_GATHER) != 0) {
-        const int32_t* gp = a.gat_ptr + (int64_t)gs * (a.tiles + 1);
-        gbeg = gp[t];
-        gend = gp[t + 1];
         if (gbeg + tid < gend) {
             gcell = a.gat_cell[gbeg + tid];
             grid = a.gat_rid[gbeg + tid];
@@ -788,8 +843,8 @@ __device__ __forceinline__ void step2d_t2_body(const StepArgs& a, int s, int t, 
     // beta B^2 at padded row z of this lane's column
     float sx = 0.f, sz = 0.f;
     if constexpr (WB) {
-        sx = (float)a.src_pos[gs * 3 + 0];
-        sz = (float)a.src_pos[gs * 3 + 1];
+        sx = (float)h.sx;
+        sz = (float)h.sz;
     }
     const float wx = ((float)ix - sx) * ((float)ix - sx);
     auto weight = [&](int z) -> float {
@@ -993,35 +1048,79 @@ void k_step2d_t2(const StepArgs a) {
     __shared__ float U0[(TH + 4 * HALO) * U0W];
     __shared__ float U1[(TH + 2 * HALO) * A_W];
     __shared__ double sred[4];
-    int s, t;
-    work_item(a, xcd_remap(blockIdx.x, gridDim.x), &s, &t);
-    s = __builtin_amdgcn_readfirstlane(s);
-    t = __builtin_amdgcn_readfirstlane(t);
-    if (a.active && !a.active[s]) return;   // uniform over the workgroup
-    const int gs = a.shot0 + s;
-    const Aperture ap = aperture(a, gs);
-    const int tzi = t / a.tiles_x, txi = t - tzi * a.tiles_x;
-    const int px = txi * T2W - HALO - a.nb, pz = tzi * TH - HALO - a.nb;   // the grown region's physical origin
-    int ibeg = 0, iend = 0, srow = -1, scol = -1;
-    if constexpr ((FL & F_INJ) != 0) {
-        const int32_t* ip = a.inj2_ptr + (int64_t)gs * (a.tiles + 1);
-        ibeg = ip[t];
-        iend = ip[t + 1];
+    T2Head<TH> h;
+    // One dword of each cache line of the arguments, before anything waits: later
+    // reads of the line are then short.
+    int tiles = a.tiles;
+    asm("" : "+s"(tiles) : "s"(a.cur), "s"(a.c2), "s"(a.nb), "s"(a.dx2), "s"(a.src_pos), "s"(a.inj2_ptr),
+        "s"(a.gat_data), "s"(a.cg_r), "s"(a.win), "s"(a.work), "s"(a.active), "s"(a.store), "s"(a.dft_nf));
+    const int blocks = a.work ? a.nwork : tiles * a.nshots;   // the launch's
+    work_item(a, xcd_remap(blockIdx.x, blocks), tiles, &h.s, &h.t);
+    h.s = __builtin_amdgcn_readfirstlane(h.s);
+    h.t = __builtin_amdgcn_readfirstlane(h.t);
+    // The shot's and tile's uniform values in one batch without branches: an
+    // array that is not there is read from c2 and the value dropped.
+    const int gs = a.shot0 + h.s;
+    auto pick = [&](const auto* p, int64_t i) { return p ? p + i : (decltype(p))a.c2; };
+    int act = *pick(a.active, h.s);
+    const int32_t* wp = pick(a.win, 2 * (int64_t)gs);
+    h.lo = wp[0]; h.hi = wp[1];
+    h.ibeg = h.iend = h.gbeg = h.gend = 0;
+    const int64_t tp = (int64_t)gs * (tiles + 1) + h.t;
+    if constexpr ((FL & F_INJ) != 0) { h.ibeg = a.inj2_ptr[tp]; h.iend = a.inj2_ptr[tp + 1]; }
+    if constexpr ((FL & F_GATHER) != 0) { h.gbeg = a.gat_ptr[tp]; h.gend = a.gat_ptr[tp + 1]; }
+    h.rec0 = h.rec_s = h.rec_e = 0;
+    if constexpr ((FL & (F_INJ | F_GATHER)) != 0) {
+        h.rec0 = a.rec_ptr[a.shot0];
+        h.rec_s = a.rec_ptr[gs];
+        h.rec_e = a.rec_ptr[gs + 1];
     }
+    h.sx = a.src_pos[gs * 3 + 0];
+    h.sz = a.src_pos[gs * 3 + 1];
+    h.al = h.be = h.part = 0.0;
+    if constexpr ((FL & F_CG_FUSE) != 0) { h.al = a.cg_alpha[h.s]; h.be = a.cg_beta[h.s]; }
+    constexpr bool PART = (FL & (F_NORMAL | F_SCALE | F_PENALTY | F_RUPD)) != 0;
+    const int64_t pidx = (int64_t)h.s * a.part_stride + h.t;
+    if constexpr (PART) h.part = *pick((const double*)a.part, pidx);
+    const int tzi = h.t / a.tiles_x, txi = h.t - tzi * a.tiles_x;
+    __builtin_amdgcn_sched_barrier(0);   // on their way before the fields' loads
+    if constexpr (t2_early<TH>()) {
+        const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const uint32_t fb = buf_bytes(a.fstride / RING);
+        const Buf cur(a.cur + h.s * a.fstride, fb), din(a.din + h.s * a.fstride, fb), c2(a.c2, fb);
+        t2_stage<TH, true>(a, cur, tzi * TH, txi * T2W, h.tb, h.th);
+        const int x = txi * T2W - HALO + lane;
+        const uint32_t vf = (unsigned)x < (unsigned)a.nxp ? 4u * (uint32_t)(x + GH) : OOB;
+#pragma unroll
+        for (int i = 0; i < T2<TH>::NR; ++i) {
+            const int z = tzi * TH - HALO + t2_row<TH>(wv, i);
+            const uint32_t row = (unsigned)z < (unsigned)a.nzp ? 4u * (uint32_t)((z + GH) * a.XS) : 0u;
+            h.c[i] = c2.ld(vf, row);
+            h.d[i] = din.ld(vf, row);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // wait for the batch here, once
+    asm("" : "+s"(act) : "s"(h.lo), "s"(h.hi), "s"(h.ibeg), "s"(h.iend), "s"(h.gbeg), "s"(h.gend), "s"(h.rec0),
+        "s"(h.rec_s), "s"(h.rec_e), "s"(h.sx), "s"(h.sz), "s"(h.al), "s"(h.be), "s"(h.part));
+    if (a.active && !act) return;   // uniform over the workgroup
+    if (!a.win) { h.lo = 0; h.hi = a.nx; }
+    const int px = txi * T2W - HALO - a.nb, pz = tzi * TH - HALO - a.nb;   // the grown region's physical origin
+    int srow = -1, scol = -1;
     if constexpr ((FL & (F_SRC_POINT | F_SRC_REC)) != 0) {   // the source cell in the grown region
-        const int gx = a.src_pos[gs * 3 + 0] - px, gz = a.src_pos[gs * 3 + 1] - pz;
+        const int gx = h.sx - px, gz = h.sz - pz;
         if ((unsigned)gz < (unsigned)(TH + 2 * HALO) && (unsigned)gx < (unsigned)A_W) { srow = gz; scol = gx; }
     }
     // Interior tiles (uniform): the grown region is physical, and neither the
     // source nor a receiver to inject lies in it; the staged region is then on
     // the padded grid (nb >= 4).
-    const bool inner = px >= ap.lo && px + A_W <= ap.hi && pz >= 0 && pz + TH + 2 * HALO <= a.nz && iend == ibeg &&
+    const bool inner = px >= h.lo && px + A_W <= h.hi && pz >= 0 && pz + TH + 2 * HALO <= a.nz && h.iend == h.ibeg &&
                        srow < 0;
     double acc = 0.0;
-    if (inner) step2d_t2_body<FL, TH, false>(a, s, t, ap, ibeg, iend, srow, scol, U0, U1, acc);
-    else step2d_t2_body<FL, TH, true>(a, s, t, ap, ibeg, iend, srow, scol, U0, U1, acc);
+    if (inner) step2d_t2_body<FL, TH, false>(a, h, srow, scol, U0, U1, acc);
+    else step2d_t2_body<FL, TH, true>(a, h, srow, scol, U0, U1, acc);
 
-    if constexpr ((FL & (F_NORMAL | F_SCALE | F_PENALTY | F_RUPD)) != 0) {
+    if constexpr (PART) {
         if (a.part) {   // uniform over the launch
             const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
             acc = wave_sum(acc);
@@ -1030,7 +1129,7 @@ void k_step2d_t2(const StepArgs a) {
             if (threadIdx.x == 0) {
                 double sum = 0.0;
                 for (int w = 0; w < 4; ++w) sum += sred[w];
-                a.part[(int64_t)s * a.part_stride + t] += sum;
+                a.part[pidx] = h.part + sum;
             }
         }
     }
@@ -1080,6 +1179,7 @@ esi_status_t dispatch2d_tuned(Plan* P, unsigned flags, const StepArgs& a) {
         ESI_CASE(F_SRC_POINT | F_STORE)
         ESI_CASE(F_SRC_DENSE | F_GATHER)
         ESI_CASE(F_SRC_DENSE | F_PENALTY)
+        ESI_CASE(F_SRC_POINT | F_SRC_DENSE | F_PENALTY)
         ESI_CASE(F_CG_FUSE | F_GATHER | F_RUPD)
         ESI_CASE(F_SRC_DENSE | F_GATHER | F_RUPD)
         ESI_CASE(F_CG_FUSE | F_GATHER | F_SCALE)
@@ -1098,7 +1198,8 @@ esi_status_t dispatch2d_tuned(Plan* P, unsigned flags, const StepArgs& a) {
 bool tuned_variant(unsigned flags) {
     switch (flags) {
         case F_SRC_POINT | F_GATHER: case F_SRC_POINT | F_STORE: case F_SRC_DENSE | F_GATHER:
-        case F_SRC_DENSE | F_PENALTY: case F_CG_FUSE | F_GATHER | F_RUPD: case F_SRC_DENSE | F_GATHER | F_RUPD:
+        case F_SRC_DENSE | F_PENALTY: case F_SRC_POINT | F_SRC_DENSE | F_PENALTY:
+        case F_CG_FUSE | F_GATHER | F_RUPD: case F_SRC_DENSE | F_GATHER | F_RUPD:
         case F_CG_FUSE | F_GATHER | F_SCALE: case F_SRC_DENSE | F_SCALE | F_GATHER: case F_INJ:
         case F_INJ | F_OUT: case F_INJ | F_NORMAL: case F_INJ | F_NORMAL | F_RUPD: case F_INJ | F_CORR:
             return true;
