@@ -497,22 +497,31 @@ esi_status_t launch_step3d(Plan* P, unsigned flags, const StepArgs& a) {
 }
 
 // Planes per chunk for a plan of `nshots` shots, `plane` floats per field plane.
-// A chunk reads 8 planes of u beyond its own; short ones still win, since they
-// give more workgroups than the CUs hold at once (two each) and keep those that
-// share halos close in time.  Microseconds per step, modelling / gradient
-// (averaged over its three passes), 32 / 16 / 8 / 4 planes, n^3 grids with nb 20:
-//   64, 1 shot:    28.2 / 16.4 / 10.3 /  9.5      32.0 / 18.4 / 11.5 / 10.5
-//   64, 2 shots:   28.7 / 17.2 / 15.3 / 13.7      33.0 / 20.0 / 17.3 / 16.2
-//   96, 1 shot:    28.5 / 17.2 / 15.2 / 15.9      33.2 / 20.2 / 17.4 / 18.3
-//   128, 4 shots:   125 /  108 /  106 /  111       144 /  126 /  120 /  123
-//   256, 4 shots:   582 /  545 /  524 /  565       682 /  640 /  609 /  638
-// 8 planes, or 4 where those make fewer than 400 workgroups.
+// A launch takes as long as the CU with most workgroups: their count over the
+// CUs, rounded up, times the planes of each and 0.7 for the 8 planes of u that a
+// chunk reads beyond its own.  Alone on its CU a workgroup hides little of its
+// latency, and two hold together.  Microseconds per step, modelling / gradient
+// (averaged over its three passes), n^3 grids with nb 20, by planes (workgroups):
+//   40, 1 shot:    3 (270)  8.2 / 8.8    4 (200)  7.3 / 8.0    8 (100) 10.1 / 11.2
+//   48, 1 shot:    3 (360)  8.5 / 9.2    4 (264)  9.2 / 10.1   5 (216)  8.3 / 9.2
+//   64, 1 shot:    3 (490)  8.7 / 9.5    4 (364)  9.6 / 10.6   6 (252)  9.1 / 10.1
+//   64, 2 shots:   4 (728) 13.7 / 16.2   6 (504) 13.0 / 15.1   8 (364) 15.3 / 17.3
+//   96, 1 shot:    4 (918) 16.0 / 18.3   6 (621) 16.9 / 19.5   8 (459) 15.2 / 17.5
+//   163, 1 shot:   4 (2652) 39.7 / 52.3  7 (1508) 36.6 / 51.3  8 (1352) 40.7 / 53.6
+//   256, 4 shots:  4 (28120)  565 / 638  8 (14060)  524 / 609  16 (7220)  545 / 640
 int step3d_chunk(int nxp, int nyp, int nzp, int64_t plane, int nshots) {
-    int ch = 8;
-    const int64_t wg = (int64_t)nshots * ((nxp + TX - 1) / TX) * ((nyp + TY - 1) / TY) * ((nzp + ch - 1) / ch);
-    // (and where a chunk with its halo would pass 2 GiB, which buffers cannot)
-    if (wg < 400 || (ch + 2 * HALO + 1) * 4 * plane >= (int64_t)1 << 31) ch = 4;
-    return ch;
+    constexpr int64_t CUS = 256;
+    const int64_t columns = (int64_t)nshots * ((nxp + TX - 1) / TX) * ((nyp + TY - 1) / TY);
+    int best = 4;
+    int64_t least = INT64_MAX;
+    for (int ch = 3; ch <= 8; ++ch) {
+        // (a chunk with its halo must not pass 2 GiB, which buffers cannot)
+        if ((ch + 2 * HALO + 1) * 4 * plane >= (int64_t)1 << 31) break;
+        const int64_t rounds = (columns * ((nzp + ch - 1) / ch) + CUS - 1) / CUS;
+        const int64_t cost = rounds * (10 * ch + 7) * (rounds == 1 ? 117 : rounds == 2 ? 97 : 100);
+        if (cost <= least) { least = cost; best = ch; }
+    }
+    return best;
 }
 
 void step3d_tile_shape(int* tx, int* ty, int* tz) { *tx = TX; *ty = TY; *tz = TZC; }
