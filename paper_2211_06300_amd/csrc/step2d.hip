@@ -533,12 +533,15 @@ struct Buf {
     __amdgpu_buffer_rsrc_t r;
     __device__ __forceinline__ Buf(const float* p, uint32_t bytes)
         : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)bytes, 0x00027000)) {}
-    // element at byte offset v (per lane) + s (uniform)
+    // element at byte offset v (per lane) + s (uniform); NT: not kept in the caches
+    static constexpr int NT = 2;
+    template <int AUX = 0>
     __device__ __forceinline__ float ld(uint32_t v, uint32_t s) const {
-        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)v, (int)s, 0));
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)v, (int)s, AUX));
     }
+    template <int AUX = 0>
     __device__ __forceinline__ void st(float x, uint32_t v, uint32_t s) const {
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, (int)v, (int)s, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, (int)v, (int)s, AUX);
     }
 };
 __device__ __forceinline__ uint32_t buf_bytes(int64_t floats) {
@@ -590,6 +593,10 @@ struct LapZ {
         return lz;
     }
 };
+
+// A segment's store of (dA/dm) u that outgrows the 256 MB of last-level cache is
+// written and read past the caches, which keep the fields (launch2d).
+constexpr unsigned F_STREAM = 1u << 30;
 
 // Occupancy target, waves per SIMD: LDS (24 KB at 32 rows) would hold six
 // workgroups per CU, the registers of a variant decide.
@@ -666,6 +673,7 @@ __device__ __forceinline__ void step2d_t2_body(const StepArgs& a, T2Head<TH>& h,
     // as two one-step launches would add them (the DTFT source keeps one update
     // per step).
     constexpr bool CORR = (FL & F_CORR) != 0;
+    constexpr int STREAM = (FL & F_STREAM) != 0 ? Buf::NT : 0;
     constexpr bool CHAIN_PEN = (FL & F_PENALTY) != 0 && (FL & (F_DTFT_SRC | F_INJ)) == 0;
     constexpr bool WB = (FL & (F_NORMAL | F_PENALTY | F_RUPD)) != 0;   // needs beta B^2
     constexpr bool DENSE = (FL & (F_SRC_DENSE | F_DTFT_SRC | F_CG_FUSE)) != 0;
@@ -733,6 +741,11 @@ __device__ __forceinline__ void step2d_t2_body(const StepArgs& a, T2Head<TH>& h,
         const Buf b(base, pb);
 #pragma unroll
         for (int i = 0; i < n; ++i) out[i] = b.ld(v | pmask(zrow(i)), prow(zrow(i)));
+    };
+    auto stored = [&](const float* base, auto& out) {   // of the tile's rows
+        const Buf b(base, pb);
+#pragma unroll
+        for (int i = 0; i < RZ2; ++i) out[i] = b.template ld<STREAM>(vo | pmask(zrow(i)), prow(zrow(i)));
     };
     if constexpr ((FL & F_SRC_DENSE) != 0) {
         dense(a.dsrc + blk_off(a, s, tA, vA), vp, qA, NR);
@@ -895,7 +908,7 @@ __device__ __forceinline__ void step2d_t2_body(const StepArgs& a, T2Head<TH>& h,
             const float qs = on ? q : 0.f;
             acc += (double)(wb * qs) * (double)qs;   // penalty term beta W q^2 (kept when a.part is set)
         }
-        if constexpr ((FL & F_STORE) != 0) Buf(o.store, pb).st(c[i] * a.inv_dt2 * lq, v, so);
+        if constexpr ((FL & F_STORE) != 0) Buf(o.store, pb).template st<STREAM>(c[i] * a.inv_dt2 * lq, v, so);
     };
     // one cell of a step: field cv, Laplacian, source (extended part qd) -> new
     // increment into d[i], the new field returned, lap + dx^2 q in lq
@@ -975,8 +988,8 @@ __device__ __forceinline__ void step2d_t2_body(const StepArgs& a, T2Head<TH>& h,
         if constexpr (RUPD) dense(a.cg_rw + vB, vo, rB, RZ2);   // r^tB (no F_SCALE here)
     }
     if constexpr (CORR) {
-        dense(oA.stin, vo, stA, RZ2);
-        dense(oB.stin, vo, stB, RZ2);
+        stored(oA.stin, stA);
+        stored(oB.stin, stB);
     }
     if constexpr (CORR || CHAIN_PEN) dense(oB.gacc, vo, gv, RZ2);
     __syncthreads();
@@ -1161,6 +1174,19 @@ template <unsigned FL, int TH>
 esi_status_t launch2d(Plan* P, const StepArgs& a) {
     const int blocks = a.work ? a.nwork : a.tiles * a.nshots;
     if (blocks == 0) return ESI_OK;
+    // A store larger than the last-level cache (256 MB) is read back from memory
+    // anyway and pushes the fields out on its way.  FWI gradient of 32 windowed
+    // shots of 1601 x 601, 50 slots (6.2 GB): 34.7 ms, 30.4 past the caches; 16 shots
+    // of 801 x 401, 25 slots (514 MB): 5.83 and 5.58; 4 shots, 50 slots (257 MB): 3.88
+    // and 3.90; 12 shots of 401 x 201, 20 slots (77 MB): 4.14 and 4.25.
+    constexpr bool STORES = TH >= 24 && (FL & (F_STORE | F_CORR)) != 0;   // shorter tiles: small launches
+    if constexpr (STORES) {
+        if (a.nshots * a.store_stride > (int64_t)1 << 26) {
+            hipLaunchKernelGGL((k_step2d_t2<FL | F_STREAM, TH>), dim3(blocks), dim3(256), 0, P->stream, a);
+            ESI_HIP_TRY(hipGetLastError());
+            return ESI_OK;
+        }
+    }
     if constexpr (TH > 0)
         hipLaunchKernelGGL((k_step2d_t2<FL, TH>), dim3(blocks), dim3(256), 0, P->stream, a);
     else
