@@ -19,6 +19,7 @@ void step3d_tile_shape(int* tx, int* ty, int* tz);
 void step3d_t2_tile_shape(int* tx, int* ty, int* tz);
 esi_status_t launch_dot(Plan* P, const float* x, const float* y, int nshots, int64_t len,
                         double* out);
+esi_status_t launch_cg_start(Plan* P, float* p, float* x, const float* r, int nshots, int64_t len, double* rr);
 esi_status_t launch_fill_d(Plan* P, double* p, int64_t n);
 
 esi_status_t check_shots(Plan* P, int shot0, int nshots) {
@@ -657,9 +658,7 @@ esi_status_t cg_solve_impl(Plan* P, int32_t shot0, int32_t ns, const float* d_ob
             int cs = 0;
             ESI_TRY(adjoint_loop(P, a, F_INJ | F_OUT, P->ring, &cs, 0, P->nt));
         }
-        ESI_TRY(launch_copy(P, c.p, c.r, ns * c.len));
-        ESI_TRY(launch_fill(P, x, ns * c.len, 0.f));
-        ESI_TRY(launch_dot(P, c.r, c.r, ns, c.len, c.rr));
+        ESI_TRY(launch_cg_start(P, c.p, x, c.r, ns, c.len, c.rr));
         ESI_HIP_TRY(hipMemcpyAsync(c.rr0, c.rr, ns * sizeof(double), hipMemcpyDeviceToDevice, P->stream));
         ESI_TRY(launch_cg_init(P, c.rr0, c.active, c.finish, c.iters, c.status, c.hist, hs, c.ctl, ns));
         ESI_HIP_TRY(hipMemcpyAsync(P->h_ctl, c.ctl, 2 * sizeof(int), hipMemcpyDeviceToHost, P->stream));

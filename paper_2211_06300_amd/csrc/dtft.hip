@@ -24,7 +24,7 @@
 
 namespace esi {
 
-esi_status_t launch_dot(Plan* P, const float* x, const float* y, int nshots, int64_t len, double* out);
+esi_status_t launch_cg_start(Plan* P, float* p, float* x, const float* r, int nshots, int64_t len, double* rr);
 
 namespace {
 
@@ -613,9 +613,7 @@ extern "C" esi_status_t esi_dtft_cg_solve(esi_plan_t plan, int32_t shot0, int32_
     int* ctl = P->cgi + 2 * P->nshots;
     ESI_TRY(grow_t(&P->cg_hist, &P->cg_hist_cap, (int64_t)ns * (max_iter + 1), P->stream));
     ESI_TRY(dtft_rhs(P, shot0, ns, d_obs, (float2*)r));
-    ESI_TRY(launch_copy(P, p, r, ns * len));
-    ESI_TRY(launch_fill(P, xbar, ns * len, 0.f));
-    ESI_TRY(launch_dot(P, r, r, ns, len, rr));
+    ESI_TRY(launch_cg_start(P, p, xbar, r, ns, len, rr));
     ESI_HIP_TRY(hipMemcpyAsync(rr0, rr, ns * sizeof(double), hipMemcpyDeviceToDevice, P->stream));
     ESI_TRY(launch_cg_init(P, rr0, active, finish, iters, status, P->cg_hist, max_iter + 1, ctl, ns));
     ESI_HIP_TRY(hipMemcpyAsync(P->h_ctl, ctl, 2 * sizeof(int), hipMemcpyDeviceToHost, P->stream));

@@ -92,6 +92,42 @@ __global__ __launch_bounds__(NT) void k_r_update(float* __restrict__ r, const fl
     if (threadIdx.x == 0) part[(int64_t)s * bps + b] = t;
 }
 
+// Start of a CG solve: p = r, x = 0, part[s][b] = sum r^2 over the block's chunk
+// (grid, chunks and alignment as k_r_update).  Memory bound: 12 bytes an element
+// in one pass.  As a copy, a fill and a dot product, 20 bytes, 8 shots of
+// 801 x 401 x 500 took 4.6 ms, now 3.4; with the blocks' elements side by side,
+// one shot after another 4.0 and all shots at once 5.0.
+__global__ __launch_bounds__(NT) void k_cg_start(float* __restrict__ p, float* __restrict__ x,
+                                                 const float* __restrict__ r, int64_t len,
+                                                 double* __restrict__ part) {
+    __shared__ double sm[NT / 64];
+    const int s = blockIdx.y, b = blockIdx.x, bps = gridDim.x;
+    const int64_t chunk = ((len + bps - 1) / bps + 3) & ~(int64_t)3;
+    const int64_t beg = min(len, (int64_t)b * chunk), n = min(len, beg + chunk) - beg;
+    float* ps = p + (int64_t)s * len + beg;
+    float* xs = x + (int64_t)s * len + beg;
+    const float* rs = r + (int64_t)s * len + beg;
+    const bool vec = ((reinterpret_cast<uintptr_t>(ps) | reinterpret_cast<uintptr_t>(xs) |
+                       reinterpret_cast<uintptr_t>(rs)) & 15) == 0;
+    const int64_t nv = vec ? n >> 2 : 0;
+    double acc = 0.0;
+#pragma unroll 4
+    for (int64_t k = threadIdx.x; k < nv; k += NT) {
+        const float4 v = reinterpret_cast<const float4*>(rs)[k];
+        reinterpret_cast<float4*>(ps)[k] = v;
+        reinterpret_cast<float4*>(xs)[k] = float4{0.f, 0.f, 0.f, 0.f};
+        acc += (double)v.x * v.x + (double)v.y * v.y + (double)v.z * v.z + (double)v.w * v.w;
+    }
+    for (int64_t i = 4 * nv + threadIdx.x; i < n; i += NT) {
+        const float v = rs[i];
+        ps[i] = v;
+        xs[i] = 0.f;
+        acc += (double)v * (double)v;
+    }
+    const double t = block_sum(acc, sm);
+    if (threadIdx.x == 0) part[(int64_t)s * bps + b] = t;
+}
+
 // grid: (bps, nshots).  part[s][b] = sum a.b over the block's chunk.
 __global__ __launch_bounds__(NT) void k_dot(const float* __restrict__ x, const float* __restrict__ y,
                                             int64_t len, double* __restrict__ part) {
@@ -378,6 +414,15 @@ esi_status_t launch_dot(Plan* P, const float* x, const float* y, int nshots, int
     hipLaunchKernelGGL(k_dot, dim3(bps, nshots), dim3(NT), 0, P->stream, x, y, len, P->part);
     ESI_HIP_TRY(hipGetLastError());
     return launch_reduce_parts(P, P->part, bps, nshots, out);
+}
+
+// p = r, x = 0, rr[s] = r . r
+esi_status_t launch_cg_start(Plan* P, float* p, float* x, const float* r, int nshots, int64_t len, double* rr) {
+    const int bps = bps_for(len);
+    ESI_TRY(grow_t(&P->part, &P->part_cap, (int64_t)bps * nshots, P->stream));
+    hipLaunchKernelGGL(k_cg_start, dim3(bps, nshots), dim3(NT), 0, P->stream, p, x, r, len, P->part);
+    ESI_HIP_TRY(hipGetLastError());
+    return launch_reduce_parts(P, P->part, bps, nshots, rr);
 }
 
 esi_status_t launch_axpy_flag(Plan* P, float* x, const float* p, const double* alpha,
