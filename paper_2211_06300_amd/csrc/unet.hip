@@ -555,6 +555,79 @@ __device__ __forceinline__ bf16x8 bf_ones() {
     return u.v;
 }
 
+// Staging of an NHWC tile (C channels of ROWS rows of 64 CW pixels, with HALO one
+// more row and column on each side) by a workgroup: a thread keeps its column
+// and channels, a load is 16 bytes, its row a scalar; the HALO's last two columns
+// are one more load.  Loads off the image, and all of them without `any`, give 0:
+// no branches, whose joins would wait for the loads.
+template <int C, int ROWS, int CW, bool HALO>
+struct Stage {
+    static constexpr int SUB = C / 8, RPL = NT / (64 * SUB), TR = ROWS + (HALO ? 2 : 0);
+    static constexpr int PW = 64 * CW + (HALO ? 2 : 0), NL = (TR * CW + RPL - 1) / RPL;
+    static_assert(RPL >= 1 && (!HALO || (CW == 1 && TR * 2 * SUB <= NT)), "tile staging");
+    u32x4 v[NL + (HALO ? 1 : 0)];
+    uint32_t moff, hoff;
+    int wrow, mpx, msub, hrow, hpx;
+
+    // s: pixel stride, W: row pitch (pixels), add: bytes from the base to this thread's channels
+    __device__ __forceinline__ void init(int s, int W, uint32_t add) {
+        const int tid = threadIdx.x;
+        wrow = __builtin_amdgcn_readfirstlane(tid >> 6) / SUB;
+        mpx = (tid % (64 * SUB)) / SUB;
+        msub = tid % SUB;
+        hrow = tid / (2 * SUB);
+        hpx = 64 + (tid % (2 * SUB)) / SUB;
+        moff = 2 * mpx * s + add;
+        hoff = 2 * (hrow * W + hpx) * s + add;
+    }
+    // tile at (x0, y0) of the H x W image at `img`, its base at the first of the
+    // thread's channel group
+    __device__ __forceinline__ void load(const bf16_t* img, int s, int H, int W, int x0, int y0, bool any) {
+        constexpr int O = HALO ? 1 : 0;
+        const __amdgpu_buffer_rsrc_t r = rsrc(img - (int64_t)O * (1 + W) * s);   // offsets stay positive
+        uint32_t mo[CW];
+#pragma unroll
+        for (int k = 0; k < CW; ++k) mo[k] = (uint32_t)(x0 - O + 64 * k + mpx) < (uint32_t)W ? moff : OOB;
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            const int h = l * RPL + wrow, row = h / CW, half = h % CW, yy = y0 - O + row;
+            const bool in = any & ((uint32_t)yy < (uint32_t)H) & (row < TR);
+            v[l] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(in ? (half ? mo[CW - 1] : mo[0]) : OOB),
+                                                         2 * ((yy + O) * W + x0 + 64 * half) * s, 0);
+        }
+        if constexpr (HALO) {
+            const bool in = any & (hrow < TR) & ((uint32_t)(y0 - 1 + hrow) < (uint32_t)H) & (x0 - 1 + hpx < W);
+            v[NL] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(in ? hoff : OOB), 2 * (y0 * W + x0) * s, 0);
+        }
+    }
+    __device__ __forceinline__ void put(bf16_t* lds) const {
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            const int h = l * RPL + wrow, row = h / CW, half = 64 * (h % CW);
+            if ((l + 1) * RPL <= TR * CW || row < TR)
+                *reinterpret_cast<u32x4*>(lds + (row * PW + half + mpx) * C + msub * 8) = v[l];
+        }
+        if constexpr (HALO)
+            if (hrow < TR) *reinterpret_cast<u32x4*>(lds + (hrow * PW + hpx) * C + msub * 8) = v[NL];
+    }
+};
+
+// Tiles b, b + step, ... of an image batch, as (x, y, image): scalar additions
+struct TileWalk {
+    int x, y, n, gx, gy, gn, ntx, nty;
+    __device__ __forceinline__ TileWalk(int b, int step, int ntx_, int nty_) : ntx(ntx_), nty(nty_) {
+        x = b % ntx; y = (b / ntx) % nty; n = b / (ntx * nty);
+        gx = step % ntx; gy = (step / ntx) % nty; gn = step / (ntx * nty);
+    }
+    __device__ __forceinline__ void next() {
+        x += gx;
+        if (x >= ntx) x -= ntx, ++y;
+        y += gy;
+        if (y >= nty) y -= nty, ++n;
+        n += gn;
+    }
+};
+
 // Sum the four waves' accumulators of a workgroup in a fixed order and write
 // them as part[tap][co][ci] of this chunk (TAPS x CO x CI of the layer's TAPS x
 // Cout x Cin, at co0, ci0), the bias sums (column 0 of bacc) after them.
@@ -607,15 +680,14 @@ __device__ __forceinline__ void wgrad_out(const f4 (&acc)[TAPS][CB][IB], const f
 // One wave per 16 x 16 channels fetching every operand element by itself (two
 // bytes a load) and a thread per output adding up to 1664 chunks took 183 and 143
 // us a layer on average on 16 images of 208 x 408.  Now 22 us at 16 x 16 channels
-// (87 MB read, 4 TB/s), 35 us at 32 x 32 and above, 6 us for the sum; the whole
-// training gradient went from 6.58 to 1.55 ms.
+// (87 MB read, 4 TB/s), 27 us at 32 x 32 and above (35 with an index, a branch and
+// a wait per staged piece), 6 us for the sum; the whole training gradient went
+// from 6.58 to 1.55 ms, and with the convolutions' new kernel to 1.24 ms.
 template <int CB, int IB, int ROWS>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3_wgrad(
     const bf16_t* __restrict__ GY, int sg, int Cout, const bf16_t* __restrict__ X, int sx, int64_t xhs, int xsplit,
     int Cin, int H, int W, int N, float* __restrict__ part, float* __restrict__ bpart) {
     constexpr int CO = 16 * CB, CI = 16 * IB, TW = 64, XW = TW + 2;
-    constexpr int NGQ = ROWS * TW * CO / 8, NXQ = (ROWS + 2) * XW * CI / 8;   // 16-byte pieces of a tile
-    constexpr int NG = (NGQ + NT - 1) / NT, NX = (NXQ + NT - 1) / NT;
     constexpr int SM_TILE = (ROWS * TW * CO + (ROWS + 2) * XW * CI) * 2, SM_OUT = (9 * CO * CI + CO) * 4;
     __shared__ __align__(16) char smem[SM_TILE > SM_OUT ? SM_TILE : SM_OUT];
     bf16_t* gs = reinterpret_cast<bf16_t*>(smem);
@@ -624,33 +696,19 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
     const int nci = Cin / CI;
     const int co0 = (int)(blockIdx.y / nci) * CO, ci0 = (int)(blockIdx.y % nci) * CI;
     const int ntx = (W + TW - 1) / TW, nty = (H + ROWS - 1) / ROWS, ntiles = ntx * nty * N;
-    const bf16_t* Gc = GY + co0;
-    // this thread's channels of X, the same for each piece it stages; a channel
-    // tile may span the halves of a concatenation
-    const int xch = ci0 + (int)(threadIdx.x % (CI / 8)) * 8;
-    const bf16_t* Xc = X + xch + (xch >= xsplit ? xhs - xsplit : 0);
-    static_assert(NT % (CI / 8) == 0, "a thread stages the same channels throughout");
-
-    uint4 rg[NG], rx[NX];
-    auto fetch = [&](int t) {
-        const int x0 = (t % ntx) * TW, y0 = ((t / ntx) % nty) * ROWS, n = t / (ntx * nty);
-        const bf16_t* Gn = Gc + (int64_t)n * H * W * sg;
-        const bf16_t* Xn = Xc + (int64_t)n * H * W * sx;
-#pragma unroll
-        for (int l = 0; l < NG; ++l) {
-            const int q = threadIdx.x + l * NT, sub = q % (CO / 8), px = (q / (CO / 8)) % TW, row = q / (CO / 8 * TW);
-            rg[l] = uint4{0u, 0u, 0u, 0u};
-            if (q < NGQ && y0 + row < H && x0 + px < W)
-                rg[l] = *reinterpret_cast<const uint4*>(Gn + ((int64_t)(y0 + row) * W + x0 + px) * sg + sub * 8);
-        }
-#pragma unroll
-        for (int l = 0; l < NX; ++l) {
-            const int q = threadIdx.x + l * NT, px = (q / (CI / 8)) % XW, row = q / (CI / 8 * XW);
-            const int yy = y0 - 1 + row, xx = x0 - 1 + px;
-            rx[l] = uint4{0u, 0u, 0u, 0u};
-            if (q < NXQ && yy >= 0 && yy < H && xx >= 0 && xx < W)
-                rx[l] = *reinterpret_cast<const uint4*>(Xn + ((int64_t)yy * W + xx) * sx);
-        }
+    Stage<CO, ROWS, 1, false> sg_;
+    Stage<CI, ROWS, 1, true> sx_;
+    sg_.init(sg, W, 16u * (threadIdx.x % (CO / 8)));
+    {   // a channel tile may span the halves of a concatenation
+        const int xch = ci0 + (int)(threadIdx.x % (CI / 8)) * 8;
+        const int64_t hop = xch >= xsplit && ci0 < xsplit ? xhs - xsplit : 0;
+        sx_.init(sx, W, 16u * (threadIdx.x % (CI / 8)) + 2u * (uint32_t)hop);
+    }
+    const bf16_t* Xc = X + ci0 + (ci0 >= xsplit ? xhs - xsplit : 0);
+    TileWalk tw(blockIdx.x, gridDim.x, ntx, nty);
+    auto fetch = [&](bool any) {
+        sg_.load(GY + co0 + (int64_t)tw.n * H * W * sg, sg, H, W, tw.x * TW, tw.y * ROWS, any);
+        sx_.load(Xc + (int64_t)tw.n * H * W * sx, sx, H, W, tw.x * TW, tw.y * ROWS, any);
     };
     f4 acc[9][CB][IB], bacc[CB];
 #pragma unroll
@@ -663,17 +721,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
     }
     // this lane's pixel and channel quarter in a group of 16 pixels
     const int pl = 4 * (lane >> 4) + ((lane & 15) >> 2), cq = 4 * (lane & 3);
-    if ((int)blockIdx.x < ntiles) fetch(blockIdx.x);
+    fetch((int)blockIdx.x < ntiles);
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
         __syncthreads();   // every wave is done with the previous tile
-#pragma unroll
-        for (int l = 0; l < NG; ++l)
-            if (threadIdx.x + l * NT < NGQ) *reinterpret_cast<uint4*>(gs + (threadIdx.x + l * NT) * 8) = rg[l];
-#pragma unroll
-        for (int l = 0; l < NX; ++l)
-            if (threadIdx.x + l * NT < NXQ) *reinterpret_cast<uint4*>(xs + (threadIdx.x + l * NT) * 8) = rx[l];
+        sg_.put(gs);
+        sx_.put(xs);
         __syncthreads();
-        if (t + (int)gridDim.x < ntiles) fetch(t + gridDim.x);
+        tw.next();
+        fetch(t + (int)gridDim.x < ntiles);
+        __builtin_amdgcn_sched_barrier(0);   // issued here, not where registers are free
 #pragma unroll
         for (int r0 = 0; r0 < ROWS; r0 += 4) {
             const int row = r0 + wave;
@@ -851,52 +907,77 @@ __global__ __launch_bounds__(NT) void k_convT_dgrad_mfma(const bf16_t* __restric
                                                          const bf16_t* __restrict__ WT, bf16_t* __restrict__ GX,
                                                          int sx, int Cin, int Hi, int Wi,
                                                          const bf16_t* __restrict__ act) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    static_assert(CB % 2 == 0, "blocks of 16 outputs are stored in pairs");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ncog = Cin / (16 * CB);
     const int n = blockIdx.z / ncog;
     const int c0 = (blockIdx.z % ncog) * 16 * CB;
     const int y = blockIdx.y * 4 + wave;
     if (y >= Hi) return;
     const int x0 = blockIdx.x * 64;
-    const int jl = lane & 15, kq = (lane >> 4) * 4;
+    const int jl = lane & 15, g = lane >> 4;
     const int K = 4 * Cout, Wo = 2 * Wi;
+    auto load8 = [](__amdgpu_buffer_rsrc_t r, uint32_t v, int o) {
+        union { u32x2 u; s4 h; } q;
+        q.u = __builtin_amdgcn_raw_buffer_load_b64(r, (int)v, o, 0);
+        return q.h;
+    };
+    const __amdgpu_buffer_rsrc_t rg = rsrc(GY + (((int64_t)n * 2 * Hi + 2 * y) * Wo + 2 * x0) * sg), rw = rsrc(WT);
+    const int64_t row = (((int64_t)n * Hi + y) * Wi + x0) * sx + c0;
+    const __amdgpu_buffer_rsrc_t rx = rsrc(GX + row), rm = rsrc(act + row);
+    uint32_t bo[4], po[4], wo[CB];   // byte offsets: gradient, outputs (as stored), weights
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int px = p * 16 + jl;
+        bo[p] = x0 + px < Wi ? 2 * (2 * px * sg + 4 * g) : OOB;
+        po[p] = x0 + px < Wi ? 2 * (px * sx + 16 * (g & 1) + 8 * (g >> 1)) : OOB;
+    }
+#pragma unroll
+    for (int c = 0; c < CB; ++c) wo[c] = 2 * ((c0 + c * 16 + jl) * K + 4 * g);
     f4 acc[4][CB];
 #pragma unroll
     for (int p = 0; p < 4; ++p)
 #pragma unroll
         for (int c = 0; c < CB; ++c) acc[p][c] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int k = 0; k < K; k += 16) {
-        const int ad = k / Cout, co = k - ad * Cout;
-        const bf16_t* Gr = GY + (((int64_t)n * 2 * Hi + 2 * y + (ad >> 1)) * Wo + (ad & 1)) * sg + co + kq;
-        s4 b[4];
+    // four blocks of 16 contraction indices at a time (K is a multiple of 64):
+    // their loads fly together
+    for (int k0 = 0; k0 < K; k0 += 64) {
+        s4 b[4][4], av[4][CB];
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const int xx = x0 + p * 16 + jl;
-            b[p] = xx < Wi ? *reinterpret_cast<const s4*>(Gr + (int64_t)2 * xx * sg) : s4{0, 0, 0, 0};
+        for (int u = 0; u < 4; ++u) {
+            const int k = k0 + 16 * u, ad = k / Cout, co = k - ad * Cout;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) b[u][p] = load8(rg, bo[p], 2 * (((ad >> 1) * Wo + (ad & 1)) * sg + co));
+#pragma unroll
+            for (int c = 0; c < CB; ++c) av[u][c] = load8(rw, wo[c], 2 * k);
         }
 #pragma unroll
-        for (int c = 0; c < CB; ++c) {
-            const s4 av = *reinterpret_cast<const s4*>(WT + (int64_t)(c0 + c * 16 + jl) * K + k + kq);
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int p = 0; p < 4; ++p)
-                acc[p][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, b[p], acc[p][c], 0, 0, 0);
-        }
+            for (int c = 0; c < CB; ++c)
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+                    acc[p][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[u][c], b[u][p], acc[p][c], 0, 0, 0);
     }
-    const int64_t row = ((int64_t)n * Hi + y) * Wi * sx;
+    u32x4 on[4][CB / 2];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const int xx = x0 + p * 16 + jl;
-        if (xx >= Wi) continue;
+    for (int p = 0; p < 4; ++p)
 #pragma unroll
-        for (int c = 0; c < CB; ++c) {
-            const int64_t at = row + (int64_t)xx * sx + c0 + c * 16 + kq;
-            const s4 on = *reinterpret_cast<const s4*>(act + at);
-            s4 o;
+        for (int c = 0; c < CB; c += 2) on[p][c / 2] = __builtin_amdgcn_raw_buffer_load_b128(rm, (int)po[p], 32 * c, 0);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = bf2f((bf16_t)on[e]) > 0.f ? (short)f2bf(acc[p][c][e]) : (short)0;
-            *reinterpret_cast<s4*>(GX + at) = o;
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int c = 0; c < CB; c += 2) {
+            u32x2 m[2], o[2];
+            split_blocks(on[p][c / 2], m[0], m[1]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f4 v = acc[p][c + h];
+                o[h] = u32x2{pk_bf16(bf_lo(m[h].x) > 0.f ? v[0] : 0.f, bf_hi(m[h].x) > 0.f ? v[1] : 0.f),
+                             pk_bf16(bf_lo(m[h].y) > 0.f ? v[2] : 0.f, bf_hi(m[h].y) > 0.f ? v[3] : 0.f)};
+            }
+            store16(merge_blocks(o[0], o[1]), rx, po[p] + 32 * c);
         }
-    }
 }
 
 // Weight gradient of the transposed convolution: part[chunk][ad][co][ci] = sum
@@ -909,8 +990,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
     const bf16_t* __restrict__ X, int sx, int Cin, const bf16_t* __restrict__ GY, int sg, int Cout, int Hi, int Wi,
     int N, float* __restrict__ part, float* __restrict__ bpart) {
     constexpr int CO = 16 * CB, CI = 16 * IB, TW = 64, ROWS = 2;
-    constexpr int NGQ = 4 * ROWS * TW * CO / 8, NXQ = ROWS * TW * CI / 8;
-    constexpr int NG = (NGQ + NT - 1) / NT, NX = (NXQ + NT - 1) / NT;
     constexpr int SM_TILE = (4 * ROWS * TW * CO + ROWS * TW * CI) * 2, SM_OUT = (4 * CO * CI + CO) * 4;
     __shared__ __align__(16) char smem[SM_TILE > SM_OUT ? SM_TILE : SM_OUT];
     bf16_t* gs = reinterpret_cast<bf16_t*>(smem);
@@ -920,27 +999,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
     const int co0 = (int)(blockIdx.y / nci) * CO, ci0 = (int)(blockIdx.y % nci) * CI;
     const int ntx = (Wi + TW - 1) / TW, nty = (Hi + ROWS - 1) / ROWS, ntiles = ntx * nty * N;
     const int Wo = 2 * Wi, Ho = 2 * Hi;
-
-    uint4 rg[NG], rx[NX];
-    auto fetch = [&](int t) {
-        const int x0 = (t % ntx) * TW, y0 = ((t / ntx) % nty) * ROWS, n = t / (ntx * nty);
-#pragma unroll
-        for (int l = 0; l < NG; ++l) {
-            const int q = threadIdx.x + l * NT, sub = q % (CO / 8), px = (q / (CO / 8)) % (2 * TW),
-                      row = q / (CO / 8 * 2 * TW);
-            rg[l] = uint4{0u, 0u, 0u, 0u};
-            if (q < NGQ && 2 * y0 + row < Ho && 2 * x0 + px < Wo)
-                rg[l] = *reinterpret_cast<const uint4*>(
-                    GY + (((int64_t)n * Ho + 2 * y0 + row) * Wo + 2 * x0 + px) * sg + co0 + sub * 8);
-        }
-#pragma unroll
-        for (int l = 0; l < NX; ++l) {
-            const int q = threadIdx.x + l * NT, sub = q % (CI / 8), px = (q / (CI / 8)) % TW, row = q / (CI / 8 * TW);
-            rx[l] = uint4{0u, 0u, 0u, 0u};
-            if (q < NXQ && y0 + row < Hi && x0 + px < Wi)
-                rx[l] = *reinterpret_cast<const uint4*>(X + (((int64_t)n * Hi + y0 + row) * Wi + x0 + px) * sx + ci0 +
-                                                        sub * 8);
-        }
+    Stage<CO, 2 * ROWS, 2, false> sg_;
+    Stage<CI, ROWS, 1, false> sx_;
+    sg_.init(sg, Wo, 16u * (threadIdx.x % (CO / 8)));
+    sx_.init(sx, Wi, 16u * (threadIdx.x % (CI / 8)));
+    TileWalk tw(blockIdx.x, gridDim.x, ntx, nty);
+    auto fetch = [&](bool any) {
+        sg_.load(GY + co0 + (int64_t)tw.n * Ho * Wo * sg, sg, Ho, Wo, 2 * tw.x * TW, 2 * tw.y * ROWS, any);
+        sx_.load(X + ci0 + (int64_t)tw.n * Hi * Wi * sx, sx, Hi, Wi, tw.x * TW, tw.y * ROWS, any);
     };
     f4 acc[4][CB][IB], bacc[CB];
 #pragma unroll
@@ -953,17 +1019,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
     }
     const int pl = 4 * (lane >> 4) + ((lane & 15) >> 2), cq = 4 * (lane & 3);
     const int row = wave >> 1, k0 = 32 * (wave & 1);
-    if ((int)blockIdx.x < ntiles) fetch(blockIdx.x);
+    fetch((int)blockIdx.x < ntiles);
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
         __syncthreads();   // every wave is done with the previous tile
-#pragma unroll
-        for (int l = 0; l < NG; ++l)
-            if (threadIdx.x + l * NT < NGQ) *reinterpret_cast<uint4*>(gs + (threadIdx.x + l * NT) * 8) = rg[l];
-#pragma unroll
-        for (int l = 0; l < NX; ++l)
-            if (threadIdx.x + l * NT < NXQ) *reinterpret_cast<uint4*>(xs + (threadIdx.x + l * NT) * 8) = rx[l];
+        sg_.put(gs);
+        sx_.put(xs);
         __syncthreads();
-        if (t + (int)gridDim.x < ntiles) fetch(t + gridDim.x);
+        tw.next();
+        fetch(t + (int)gridDim.x < ntiles);
+        __builtin_amdgcn_sched_barrier(0);   // issued here, not where registers are free
         bf16x8 bv[IB];
         const bf16_t* xp = xs + (row * TW + k0 + pl) * CI + cq;
 #pragma unroll
