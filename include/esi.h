@@ -513,7 +513,7 @@ esi_status_t esi_plan_set_time_block(esi_plan_t plan, int32_t steps);
 /*
  * Launch shapes of the time loops, the autotuner's candidates:
  *   ESI_LAUNCH_ONE_STEP (1): one time step per launch (2D: 64 x 32 tiles;
- *   3D: 64 x 16 columns, chunks of 8 or 4 planes);
+ *   3D: 64 x 16 columns, chunks of 3 to 8 planes);
  *   ESI_LAUNCH_TWO_STEP_32 (2, default), _24 (3), _40 (4): two time steps per
  *   launch on 56-column tiles of 32, 24 or 40 rows (2D), or on 56 x 24 columns
  *   and 64-plane chunks (3D, shape 2 only); the wavefield state crosses HBM

@@ -15,11 +15,11 @@
 //                  tile of u^n plus a 4-cell halo is staged in LDS, each lane
 //                  owns a column and 8 rows, z neighbours from registers, x
 //                  neighbours from LDS.
-// k_step2d_t2<FL>: two steps per launch (time blocking) on 56 x 32 tiles.
-//                  u^n is staged on the tile grown by 8 cells, the first step
-//                  is computed on the tile grown by 4 cells (64 columns: one
-//                  wave across) into LDS, the second on the tile.  The
-//                  wavefield state crosses HBM once per two steps.
+// k_step2d_t2<FL, TH>: two steps per launch (time blocking) on tiles of 56
+//                  columns and TH rows.  u^n is staged on the tile grown by 8
+//                  cells, the first step is computed on the tile grown by 4
+//                  cells (64 columns: one wave across) into LDS, the second on
+//                  the tile.  The wavefield state crosses HBM once per two steps.
 //
 // Workgroup ids are remapped so that consecutive tiles land on the same XCD
 // (8 XCDs take workgroups round-robin), keeping halo neighbours in one L2.

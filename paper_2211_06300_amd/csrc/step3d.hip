@@ -21,7 +21,7 @@
 // so that the windows move once per UZ planes.  Microseconds per launch, before
 // (addresses and masks per plane, receivers counted one by one, 32-plane
 // chunks) and now, modelling / segment recompute / adjoint / correlating
-// adjoint: one shot of 64^3, 32.4 / 35.6 / 52.4 / 60.8, now 9.3 / 9.9 / 9.5 / 11.8;
+// adjoint: one shot of 64^3, 32.4 / 35.6 / 52.4 / 60.8, now 8.2 / 9.1 / 9.4 / 10.7;
 // 4 shots of 256^3, 560 / 662 / 591 / 888, now 509 / 589 / 530 / 755.  The latter
 // moves 2.76 GB a modelling launch by counters (20 B a cell are 2.07), 5.4 TB/s:
 // halo planes that neither L2 nor a neighbour still holds.  Non-temporal loads

@@ -15,8 +15,7 @@
 // 3x3 convolutions (forward and data gradient) are implicit GEMMs on
 // v_mfma_f32_16x16x32_bf16: D[cout][pixel] = sum_{tap, ci} W[tap][cout][ci]
 // X[pixel + tap][ci], with each input tile staged in LDS once and read by all
-// nine taps, and the weights packed in the instruction's operand order.  A
-// lane stores four consecutive output channels of one pixel (8 bytes).  The
+// nine taps, and the weights packed in the instruction's operand order.  The
 // data gradient is the same kernel with taps reversed and weights transposed.
 // Transposed convolutions use the same instruction with operands loaded
 // straight from memory (each input pixel is read once); their data gradient
