@@ -118,6 +118,8 @@ esi_status_t loop_lists(Plan* P, unsigned fflags, unsigned aflags, int shot0, in
 // Point the tile fields and sparse lists of `a` at the tiling `L`.
 void apply_lists(StepArgs& a, const TileLists* L) {
     a.tiles_x = L->tiles_x; a.tiles_y = L->tiles_y; a.tiles_z = L->tiles_z; a.tiles = L->tiles;
+    a.tiles_m = UINT32_MAX / (uint32_t)std::max(1, L->tiles);
+    a.tiles_xm = UINT32_MAX / (uint32_t)std::max(1, L->tiles_x);
     a.chunk = L->tz;
     a.inj_ptr = L->inj_ptr; a.inj_cell = L->inj_cell; a.inj_rptr = L->inj_rptr; a.inj_rid = L->inj_rid;
     a.gat_ptr = L->gat_ptr; a.gat_cell = L->gat_cell; a.gat_rid = L->gat_rid;

@@ -236,6 +236,7 @@ struct StepArgs {
     int step;                // n (forward) or j (adjoint)
     int nt;
     int tiles_x, tiles_y, tiles_z, tiles;   // per shot
+    uint32_t tiles_m, tiles_xm;             // (2^32 - 1) / tiles, / tiles_x: for division by them
     int chunk;               // planes (3D) or rows (2D) of a tile
     int nshots;
     int shot0;               // global index of the first shot
