@@ -125,6 +125,7 @@ void apply_lists(StepArgs& a, const TileLists* L) {
     a.gat_ptr = L->gat_ptr; a.gat_cell = L->gat_cell; a.gat_rid = L->gat_rid;
     a.src_tile = L->src_tile; a.src_cell = L->src_cell;
     a.inj2_ptr = L->inj2_ptr; a.inj2_cell = L->inj2_cell; a.inj2_rptr = L->inj2_rptr; a.inj2_rid = L->inj2_rid;
+    a.inj2_first = L->inj2_first;
     if (L->work) {
         a.work = L->work + L->work_ptr[a.shot0];
         a.nwork = (int)(L->work_ptr[a.shot0 + a.nshots] - L->work_ptr[a.shot0]);

@@ -69,6 +69,7 @@ struct TileLists {
     int32_t* inj2_cell = nullptr;
     int32_t* inj2_rptr = nullptr;
     int32_t* inj2_rid = nullptr;
+    int32_t* inj2_first = nullptr;       // first receiver of each cell's range, by cell
     // with apertures: the (shot, tile) items whose tile meets the shot's
     // window plus its absorbing layer, shot-major; work_ptr[gs] indexes it
     int32_t* work = nullptr;
@@ -296,6 +297,7 @@ struct StepArgs {
     // blk_T > 0: dsrc and dout hold blk_T steps, step n in slot n % blk_T
     // ([nshots][blk_T][phys]); 0: the whole time axis
     int blk_T;
+    const int32_t* inj2_first;   // tile list, as those above
 };
 
 // kernel flag bits

@@ -13,6 +13,7 @@
 namespace esi {
 
 void step3d_tile_shape(int* tx, int* ty, int* tz);   // step3d.hip
+void step2d_shape_tile(int shape, int* tx, int* tz);   // step2d.hip
 int step3d_chunk(int nxp, int nyp, int nzp, int64_t plane, int nshots);
 
 static thread_local std::string g_err;
@@ -188,12 +189,17 @@ static esi_status_t set_model(Plan* P, const float* vel, bool first, double eta_
 }
 
 // ---- per-tile lists -------------------------------------------------------------
-esi_status_t get_lists(Plan* P, int tx, int tz, int ty, bool grown, TileLists** out) {
-    for (TileLists* L : P->lists)   // (one- and two-step tiles differ in width)
-        if (L->tx == tx && L->tz == tz && L->ty == ty) { *out = L; return ESI_OK; }
-    TileLists* L = new (std::nothrow) TileLists();
-    if (!L) return fail(ESI_ERR_OOM, "host allocation failed");
-    L->tx = tx; L->tz = tz; L->ty = ty;
+namespace {
+
+// A tiling's lists on the host, named as in TileLists.
+struct HostLists {
+    std::vector<int32_t> inj_ptr, inj_cell, inj_rptr{0}, inj_rid, gat_ptr, gat_cell, gat_rid, src_tile, src_cell;
+    std::vector<int32_t> inj2_ptr, inj2_cell, inj2_rptr{0}, inj2_rid, inj2_first, work;
+};
+
+// Fill L's tile counts and work_ptr, and the lists in h, for L's tile shape.
+void build_lists(const Plan* P, bool grown, TileLists* L, HostLists& h) {
+    const int tx = L->tx, tz = L->tz, ty = L->ty;
     L->tiles_x = (P->nxp + tx - 1) / tx;
     L->tiles_z = (P->nzp + tz - 1) / tz;
     L->tiles_y = P->ndim == 3 ? (P->nyp + ty - 1) / ty : 1;
@@ -208,13 +214,14 @@ esi_status_t get_lists(Plan* P, int tx, int tz, int ty, bool grown, TileLists** 
         *cell = nd == 3 ? ((lz * ty + ly) * tx + lx) : (lz * tx + lx);
     };
     const int T = L->tiles, S = P->nshots;
-    std::vector<int32_t> inj_ptr((size_t)S * (T + 1)), gat_ptr((size_t)S * (T + 1));
-    std::vector<int32_t> inj_cell, inj_rptr{0}, inj_rid, gat_cell, gat_rid;
-    std::vector<int32_t> src_tile(S), src_cell(S);
+    h.inj_ptr.resize((size_t)S * (T + 1));
+    h.gat_ptr.resize((size_t)S * (T + 1));
+    h.src_tile.resize(S);
+    h.src_cell.resize(S);
     // grown-tile injection lists: a receiver belongs to every tile whose region
     // grown by one stencil radius, [x0-4, x0+tx+4) x [z0-4, z0+tz+4)
     // (x [y0-4, y0+ty+4) in 3D), holds it; cells are indexed on the grown tile
-    std::vector<int32_t> inj2_ptr(grown ? (size_t)S * (T + 1) : 0), inj2_cell, inj2_rptr{0}, inj2_rid;
+    if (grown) h.inj2_ptr.resize((size_t)S * (T + 1));
     const int gw = tx + 2 * HALO, gh = tz + 2 * HALO, gy3 = ty + 2 * HALO;
     for (int s = 0; s < S; ++s) {
         int64_t r0 = P->h_rec_ptr[s], r1 = P->h_rec_ptr[s + 1];
@@ -229,26 +236,26 @@ esi_status_t get_lists(Plan* P, int tx, int tz, int ty, bool grown, TileLists** 
         }
         std::sort(e.begin(), e.end());
         size_t k = 0;
-        int32_t* ip = &inj_ptr[(size_t)s * (T + 1)];
-        int32_t* gp = &gat_ptr[(size_t)s * (T + 1)];
+        int32_t* ip = &h.inj_ptr[(size_t)s * (T + 1)];
+        int32_t* gp = &h.gat_ptr[(size_t)s * (T + 1)];
         for (int t = 0; t < T; ++t) {
-            ip[t] = (int32_t)inj_cell.size();
-            gp[t] = (int32_t)gat_cell.size();
+            ip[t] = (int32_t)h.inj_cell.size();
+            gp[t] = (int32_t)h.gat_cell.size();
             while (k < e.size() && e[k][0] == t) {
                 // one unique cell, all its receivers in increasing id order
                 int32_t cell = e[k][1];
-                inj_cell.push_back(cell);
+                h.inj_cell.push_back(cell);
                 while (k < e.size() && e[k][0] == t && e[k][1] == cell) {
-                    inj_rid.push_back(e[k][2]);
-                    gat_cell.push_back(cell);
-                    gat_rid.push_back(e[k][2]);
+                    h.inj_rid.push_back(e[k][2]);
+                    h.gat_cell.push_back(cell);
+                    h.gat_rid.push_back(e[k][2]);
                     ++k;
                 }
-                inj_rptr.push_back((int32_t)inj_rid.size());
+                h.inj_rptr.push_back((int32_t)h.inj_rid.size());
             }
         }
-        ip[T] = (int32_t)inj_cell.size();
-        gp[T] = (int32_t)gat_cell.size();
+        ip[T] = (int32_t)h.inj_cell.size();
+        gp[T] = (int32_t)h.gat_cell.size();
         if (grown) {
             // (tile, grown cell, rid) for every tile region holding each receiver
             std::vector<std::array<int32_t, 3>> g2;
@@ -273,22 +280,22 @@ esi_status_t get_lists(Plan* P, int tx, int tz, int ty, bool grown, TileLists** 
             }
             std::sort(g2.begin(), g2.end());
             size_t q = 0;
-            int32_t* ip2 = &inj2_ptr[(size_t)s * (T + 1)];
+            int32_t* ip2 = &h.inj2_ptr[(size_t)s * (T + 1)];
             for (int t = 0; t < T; ++t) {
-                ip2[t] = (int32_t)inj2_cell.size();
+                ip2[t] = (int32_t)h.inj2_cell.size();
                 while (q < g2.size() && g2[q][0] == t) {
                     const int32_t cell = g2[q][1];
-                    inj2_cell.push_back(cell);
-                    while (q < g2.size() && g2[q][0] == t && g2[q][1] == cell) inj2_rid.push_back(g2[q++][2]);
-                    inj2_rptr.push_back((int32_t)inj2_rid.size());
+                    h.inj2_cell.push_back(cell);
+                    h.inj2_first.push_back(g2[q][2]);
+                    while (q < g2.size() && g2[q][0] == t && g2[q][1] == cell) h.inj2_rid.push_back(g2[q++][2]);
+                    h.inj2_rptr.push_back((int32_t)h.inj2_rid.size());
                 }
             }
-            ip2[T] = (int32_t)inj2_cell.size();
+            ip2[T] = (int32_t)h.inj2_cell.size();
         }
         const int32_t* ps = &P->h_src[(size_t)s * nd];
-        locate(ps[0] + P->nb, ps[1] + P->nb, nd == 3 ? ps[2] + P->nb : 0, &src_tile[s], &src_cell[s]);
+        locate(ps[0] + P->nb, ps[1] + P->nb, nd == 3 ? ps[2] + P->nb : 0, &h.src_tile[s], &h.src_cell[s]);
     }
-    std::vector<int32_t> work;
     if (!P->h_win.empty()) {
         // the (shot, tile) items whose tile columns meet the shot's window plus layer
         L->work_ptr.assign(P->nshots + 1, 0);
@@ -297,19 +304,31 @@ esi_status_t get_lists(Plan* P, int tx, int tz, int ty, bool grown, TileLists** 
             for (int t = 0; t < L->tiles; ++t) {
                 const int txi = t % L->tiles_x;
                 const int a0 = txi * tx, a1 = a0 + tx;
-                if (a0 < hi && a1 > lo) work.push_back(s * L->tiles + t);
+                if (a0 < hi && a1 > lo) h.work.push_back(s * L->tiles + t);
             }
-            L->work_ptr[s + 1] = (int64_t)work.size();
+            L->work_ptr[s + 1] = (int64_t)h.work.size();
         }
     }
+}
+
+}  // namespace
+
+esi_status_t get_lists(Plan* P, int tx, int tz, int ty, bool grown, TileLists** out) {
+    for (TileLists* L : P->lists)   // (one- and two-step tiles differ in width)
+        if (L->tx == tx && L->tz == tz && L->ty == ty) { *out = L; return ESI_OK; }
+    TileLists* L = new (std::nothrow) TileLists();
+    if (!L) return fail(ESI_ERR_OOM, "host allocation failed");
+    L->tx = tx; L->tz = tz; L->ty = ty;
+    HostLists h;
+    build_lists(P, grown, L, h);
     // one device array holds all lists, each starting on a 256-byte boundary
     struct Part { const std::vector<int32_t>* h; int32_t** d; };
-    std::vector<Part> parts = {{&inj_ptr, &L->inj_ptr}, {&inj_cell, &L->inj_cell}, {&inj_rptr, &L->inj_rptr},
-                               {&inj_rid, &L->inj_rid}, {&gat_ptr, &L->gat_ptr}, {&gat_cell, &L->gat_cell},
-                               {&gat_rid, &L->gat_rid}, {&src_tile, &L->src_tile}, {&src_cell, &L->src_cell},
-                               {&inj2_ptr, &L->inj2_ptr}, {&inj2_cell, &L->inj2_cell}, {&inj2_rptr, &L->inj2_rptr},
-                               {&inj2_rid, &L->inj2_rid}};
-    if (!P->h_win.empty()) parts.push_back({&work, &L->work});
+    std::vector<Part> parts = {{&h.inj_ptr, &L->inj_ptr}, {&h.inj_cell, &L->inj_cell}, {&h.inj_rptr, &L->inj_rptr},
+                               {&h.inj_rid, &L->inj_rid}, {&h.gat_ptr, &L->gat_ptr}, {&h.gat_cell, &L->gat_cell},
+                               {&h.gat_rid, &L->gat_rid}, {&h.src_tile, &L->src_tile}, {&h.src_cell, &L->src_cell},
+                               {&h.inj2_ptr, &L->inj2_ptr}, {&h.inj2_cell, &L->inj2_cell}, {&h.inj2_rptr, &L->inj2_rptr},
+                               {&h.inj2_rid, &L->inj2_rid}, {&h.inj2_first, &L->inj2_first}};
+    if (!P->h_win.empty()) parts.push_back({&h.work, &L->work});
     size_t total = 0;
     for (const Part& q : parts) total += (q.h->size() + 64) / 64 * 64;   // at least one element's room each
     std::vector<int32_t> all(total, 0);
@@ -494,6 +513,38 @@ extern "C" esi_status_t esi_plan_create(esi_plan_t* plan, const esi_grid_t* g, c
     if (e != hipSuccess) return cleanup(fail(ESI_ERR_HIP, hipGetErrorString(e)));
     *plan = (esi_plan_t)P;
     return ESI_OK;
+}
+
+// Host only, for tests (no device is touched): the entries of the grown-tile
+// injection lists of two-step 2D tiles of `rows` rows, in list order.  Of each
+// entry out[e] holds shot, tile, cell, the receiver that a launch reads ahead,
+// the first receiver and the number of receivers of the entry's own list.
+// Returns the entry count; at most `cap` are written.
+extern "C" int64_t esi_host_injection(const esi_grid_t* g, const esi_geom_t* geo, int32_t rows, int64_t cap,
+                                      int32_t* out) {
+    Plan P;
+    P.ndim = 2; P.nb = g->nb; P.nshots = geo->nshots;
+    P.nzp = g->nz + 2 * g->nb;
+    P.nxp = g->nx + 2 * g->nb;
+    P.h_src.assign(geo->src, geo->src + (size_t)geo->nshots * 2);
+    P.h_rec_ptr.assign(geo->rec_ptr, geo->rec_ptr + geo->nshots + 1);
+    P.h_rec.assign(geo->rec, geo->rec + 2 * geo->rec_ptr[geo->nshots]);
+    TileLists L;
+    step2d_shape_tile(LS_T2_32, &L.tx, &L.tz);
+    L.tz = rows;
+    L.ty = 1;
+    HostLists h;
+    build_lists(&P, true, &L, h);
+    for (int s = 0; s < P.nshots; ++s)
+        for (int t = 0; t < L.tiles; ++t) {
+            const int32_t* ip = &h.inj2_ptr[(size_t)s * (L.tiles + 1) + t];
+            for (int64_t e = ip[0]; e < ip[1] && e < cap; ++e) {
+                const int32_t v[6] = {s, t, h.inj2_cell[e], h.inj2_first[e], h.inj2_rid[h.inj2_rptr[e]],
+                                      h.inj2_rptr[e + 1] - h.inj2_rptr[e]};
+                std::copy(v, v + 6, out + 6 * e);
+            }
+        }
+    return (int64_t)h.inj2_cell.size();
 }
 
 extern "C" esi_status_t esi_plan_set_model(esi_plan_t plan, const float* vel) {

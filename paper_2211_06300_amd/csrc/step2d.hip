@@ -836,16 +836,17 @@ __device__ __forceinline__ void step2d_t2_body(const StepArgs& a, T2Head<TH>& h,
         return v;
     };
     if constexpr (GEN && (FL & F_INJ) != 0) {
-        // Receiver list entry e is the entry's own while every cell so far holds one
-        // receiver: its data is on the way before the list's bounds say so.
+        // An entry's first receiver is listed by entry (it is the shot's own, also
+        // where cells hold several): its data is on the way before the bounds of
+        // the entry's list say whether more follow.
         const int e = ibeg + tid;
         if (e < iend) {
             icell = a.inj2_cell[e];
-            const int r0 = a.inj2_rptr[e], r1 = a.inj2_rptr[e + 1], rid = a.inj2_rid[e];
+            const int r0 = a.inj2_rptr[e], r1 = a.inj2_rptr[e + 1], rid = a.inj2_first[e];
             const float* dj = a.inj_data + doff;
             ivA = 0.f + dj[(int64_t)tA * nrec_s + rid];
             ivB = 0.f + dj[(int64_t)tB * nrec_s + rid];
-            if (r0 != e || r1 != e + 1) {
+            if (r1 != r0 + 1) {
                 ivA = inj_value(e, tA);
                 ivB = inj_value(e, tB);
             }
