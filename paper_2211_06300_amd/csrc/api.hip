@@ -66,16 +66,20 @@ static int64_t launch_tiles(Plan* P, int tx, int tz, int shot0, int nshots) {
 //                        1344, take 9.87 modelling against 9.18)
 //   801 x 401, 4 shots:  20.47 / 20.43 / 20.24 / 22.75  (24 rows: 1216)
 // and 8 shots of 801 x 401 run fastest on 32 rows.
+static constexpr struct { int shape, most; } SMALL[] = {{LS_T2_8, 768}, {LS_T2_16, 1024}, {LS_T2_24, 1280}};
+
+static int64_t launch_tiles(Plan* P, int shape, int shot0, int nshots) {
+    int tx, tz;
+    step2d_shape_tile(shape, &tx, &tz);
+    return launch_tiles(P, tx, tz, shot0, nshots);
+}
+
 int loop_shape(Plan* P, unsigned flags, bool adjoint, int shot0, int nshots) {
-    constexpr struct { int shape, most; } SMALL[] = {{LS_T2_8, 768}, {LS_T2_16, 1024}, {LS_T2_24, 1280}};
     int want = adjoint ? P->tb_adj : P->tb_fwd;
     if (P->ndim == 2) {
         if (want != LS_ONE && P->small_tiles) {
-            for (const auto& t : SMALL) {
-                int tx, tz;
-                step2d_shape_tile(t.shape, &tx, &tz);
-                if (launch_tiles(P, tx, tz, shot0, nshots) <= t.most) { want = t.shape; break; }
-            }
+            for (const auto& t : SMALL)
+                if (launch_tiles(P, t.shape, shot0, nshots) <= t.most) { want = t.shape; break; }
         }
         return step2d_loop_shape(flags, want, P->fsize);
     }
@@ -96,6 +100,26 @@ esi_status_t shape_lists(Plan* P, int shape, TileLists** L) {
     int tx, ty, tz;
     shape_tile(P, shape, &tx, &ty, &tz);
     return get_lists(P, tx, tz, ty, shape != LS_ONE, L);
+}
+
+// The tilings that loops over any of the plan's shots take without a shape set
+// by the caller: one step, the plan's two-step tiles and, in 2D, the 32 rows of
+// the variants without other heights and the shorter tiles of the ranges of shots
+// that are small enough for them.  (A range counts at least the tiles of one of its
+// shots and at most those of all.)
+esi_status_t default_tilings(Plan* P) {
+    TileLists* L;
+    ESI_TRY(shape_lists(P, LS_ONE, &L));
+    if (P->ndim != 2) return ESI_OK;   // two steps per launch on request
+    if (step2d_loop_shape(0, LS_T2_32, P->fsize) == LS_ONE) return ESI_OK;
+    ESI_TRY(shape_lists(P, LS_T2_32, &L));
+    for (const auto& t : SMALL) {
+        int64_t least = INT64_MAX;
+        for (int s = 0; s < (P->h_win.empty() ? 1 : P->nshots); ++s) least = std::min(least, launch_tiles(P, t.shape, s, 1));
+        if (least <= t.most) ESI_TRY(shape_lists(P, t.shape, &L));
+        if (launch_tiles(P, t.shape, 0, P->nshots) <= t.most) break;   // no range takes a taller one
+    }
+    return ESI_OK;
 }
 
 int max_tiles(Plan* P) {

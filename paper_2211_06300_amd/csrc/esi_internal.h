@@ -388,6 +388,8 @@ esi_status_t lists_for(Plan* P, TileLists** L);
 // tiles for variants without other heights), and its tiling
 int loop_shape(Plan* P, unsigned flags, bool adjoint, int shot0, int nshots);
 esi_status_t shape_lists(Plan* P, int shape, TileLists** L);
+// build the tilings of the plan's default loops (at plan creation)
+esi_status_t default_tilings(Plan* P);
 void shape_tile(Plan* P, int shape, int* tx, int* ty, int* tz);
 // the largest tile count of the plan's tilings (stride of per-tile partials)
 int max_tiles(Plan* P);

@@ -222,34 +222,50 @@ void build_lists(const Plan* P, bool grown, TileLists* L, HostLists& h) {
     // grown by one stencil radius, [x0-4, x0+tx+4) x [z0-4, z0+tz+4)
     // (x [y0-4, y0+ty+4) in 3D), holds it; cells are indexed on the grown tile
     if (grown) h.inj2_ptr.resize((size_t)S * (T + 1));
-    const int gw = tx + 2 * HALO, gh = tz + 2 * HALO, gy3 = ty + 2 * HALO;
+    const int gw = tx + 2 * HALO, gy3 = ty + 2 * HALO;
+    // entries of one shot by tile, then cell, then receiver (pushed in receiver
+    // order, so that mostly a counting sort by tile is all)
+    struct Entry { int32_t tile, cell, rid; };
+    std::vector<Entry> e, sorted;
+    std::vector<int32_t> at(T + 1);
+    auto by_tile = [&]() {
+        std::fill(at.begin(), at.end(), 0);
+        for (const Entry& q : e) ++at[q.tile + 1];
+        for (int t = 0; t < T; ++t) at[t + 1] += at[t];
+        sorted.resize(e.size());
+        for (const Entry& q : e) sorted[at[q.tile]++] = q;      // at[t]: now the end of tile t
+        auto less = [](const Entry& x, const Entry& y) { return x.cell != y.cell ? x.cell < y.cell : x.rid < y.rid; };
+        for (size_t i = 0, j; i < sorted.size(); i = j) {
+            j = at[sorted[i].tile];
+            if (!std::is_sorted(sorted.begin() + i, sorted.begin() + j, less))
+                std::sort(sorted.begin() + i, sorted.begin() + j, less);
+        }
+    };
     for (int s = 0; s < S; ++s) {
-        int64_t r0 = P->h_rec_ptr[s], r1 = P->h_rec_ptr[s + 1];
-        // (tile, cell, rid) for every receiver of this shot, sorted
-        std::vector<std::array<int32_t, 3>> e;
-        e.reserve(r1 - r0);
+        const int64_t r0 = P->h_rec_ptr[s], r1 = P->h_rec_ptr[s + 1];
+        e.clear();
         for (int64_t r = r0; r < r1; ++r) {
             const int32_t* pr = &P->h_rec[r * nd];
-            int tile, cell;
-            locate(pr[0] + P->nb, pr[1] + P->nb, nd == 3 ? pr[2] + P->nb : 0, &tile, &cell);
-            e.push_back({tile, cell, (int32_t)(r - r0)});
+            Entry q;
+            locate(pr[0] + P->nb, pr[1] + P->nb, nd == 3 ? pr[2] + P->nb : 0, &q.tile, &q.cell);
+            q.rid = (int32_t)(r - r0);
+            e.push_back(q);
         }
-        std::sort(e.begin(), e.end());
-        size_t k = 0;
+        by_tile();
         int32_t* ip = &h.inj_ptr[(size_t)s * (T + 1)];
         int32_t* gp = &h.gat_ptr[(size_t)s * (T + 1)];
+        size_t k = 0;
         for (int t = 0; t < T; ++t) {
             ip[t] = (int32_t)h.inj_cell.size();
             gp[t] = (int32_t)h.gat_cell.size();
-            while (k < e.size() && e[k][0] == t) {
+            while (k < sorted.size() && sorted[k].tile == t) {
                 // one unique cell, all its receivers in increasing id order
-                int32_t cell = e[k][1];
+                const int32_t cell = sorted[k].cell;
                 h.inj_cell.push_back(cell);
-                while (k < e.size() && e[k][0] == t && e[k][1] == cell) {
-                    h.inj_rid.push_back(e[k][2]);
+                for (; k < sorted.size() && sorted[k].tile == t && sorted[k].cell == cell; ++k) {
+                    h.inj_rid.push_back(sorted[k].rid);
                     h.gat_cell.push_back(cell);
-                    h.gat_rid.push_back(e[k][2]);
-                    ++k;
+                    h.gat_rid.push_back(sorted[k].rid);
                 }
                 h.inj_rptr.push_back((int32_t)h.inj_rid.size());
             }
@@ -257,37 +273,36 @@ void build_lists(const Plan* P, bool grown, TileLists* L, HostLists& h) {
         ip[T] = (int32_t)h.inj_cell.size();
         gp[T] = (int32_t)h.gat_cell.size();
         if (grown) {
-            // (tile, grown cell, rid) for every tile region holding each receiver
-            std::vector<std::array<int32_t, 3>> g2;
+            // an entry for every tile region that holds a receiver (whose padded
+            // coordinates are at least nb >= HALO)
+            e.clear();
             for (int64_t r = r0; r < r1; ++r) {
                 const int32_t* pr = &P->h_rec[r * nd];
                 const int x = pr[0] + P->nb, z = pr[1] + P->nb, y = nd == 3 ? pr[2] + P->nb : 0;
-                for (int tzi = 0; tzi < L->tiles_z; ++tzi) {
-                    const int gz = z - (tzi * tz - HALO);
-                    if (gz < 0 || gz >= gh) continue;
-                    for (int tyi = 0; tyi < L->tiles_y; ++tyi) {
-                        const int gy = nd == 3 ? y - (tyi * ty - HALO) : 0;
-                        if (nd == 3 && (gy < 0 || gy >= gy3)) continue;
-                        for (int txi = 0; txi < L->tiles_x; ++txi) {
-                            const int gx = x - (txi * tx - HALO);
-                            if (gx < 0 || gx >= gw) continue;
-                            const int tile = (tzi * L->tiles_y + tyi) * L->tiles_x + txi;
-                            const int cell = nd == 3 ? (gz * gy3 + gy) * gw + gx : gz * gw + gx;
-                            g2.push_back({tile, cell, (int32_t)(r - r0)});
+                const int tx0 = (x - HALO) / tx, tx1 = std::min((x + HALO) / tx, L->tiles_x - 1);
+                const int tz0 = (z - HALO) / tz, tz1 = std::min((z + HALO) / tz, L->tiles_z - 1);
+                const int ty0 = nd == 3 ? (y - HALO) / ty : 0;
+                const int ty1 = nd == 3 ? std::min((y + HALO) / ty, L->tiles_y - 1) : 0;
+                for (int tzi = tz0; tzi <= tz1; ++tzi)
+                    for (int tyi = ty0; tyi <= ty1; ++tyi)
+                        for (int txi = tx0; txi <= tx1; ++txi) {
+                            const int gx = x - (txi * tx - HALO), gz = z - (tzi * tz - HALO);
+                            const int gy = nd == 3 ? y - (tyi * ty - HALO) : 0;
+                            e.push_back({(tzi * L->tiles_y + tyi) * L->tiles_x + txi,
+                                         nd == 3 ? (gz * gy3 + gy) * gw + gx : gz * gw + gx, (int32_t)(r - r0)});
                         }
-                    }
-                }
             }
-            std::sort(g2.begin(), g2.end());
-            size_t q = 0;
+            by_tile();
             int32_t* ip2 = &h.inj2_ptr[(size_t)s * (T + 1)];
+            k = 0;
             for (int t = 0; t < T; ++t) {
                 ip2[t] = (int32_t)h.inj2_cell.size();
-                while (q < g2.size() && g2[q][0] == t) {
-                    const int32_t cell = g2[q][1];
+                while (k < sorted.size() && sorted[k].tile == t) {
+                    const int32_t cell = sorted[k].cell;
                     h.inj2_cell.push_back(cell);
-                    h.inj2_first.push_back(g2[q][2]);
-                    while (q < g2.size() && g2[q][0] == t && g2[q][1] == cell) h.inj2_rid.push_back(g2[q++][2]);
+                    h.inj2_first.push_back(sorted[k].rid);
+                    while (k < sorted.size() && sorted[k].tile == t && sorted[k].cell == cell)
+                        h.inj2_rid.push_back(sorted[k++].rid);
                     h.inj2_rptr.push_back((int32_t)h.inj2_rid.size());
                 }
             }
@@ -501,13 +516,9 @@ extern "C" esi_status_t esi_plan_create(esi_plan_t* plan, const esi_grid_t* g, c
     esi_status_t st = set_model(P, vel, true, g->eta_max);
     if (st != ESI_OK) return cleanup(st);
     // the tilings of the default time loops are built now, so that calls that
-    // must not allocate (esi_forward_noalloc) find them
-    {
-        TileLists* L = nullptr;
-        st = lists_for(P, &L);
-        if (st == ESI_OK) st = shape_lists(P, loop_shape(P, F_SRC_POINT | F_GATHER, false, 0, P->nshots), &L);
-        if (st != ESI_OK) return cleanup(st);
-    }
+    // must not allocate (esi_forward_noalloc, work under capture) find them
+    st = default_tilings(P);
+    if (st != ESI_OK) return cleanup(st);
     noalloc_init_device(P->device);
     hipError_t e = hipStreamSynchronize(P->stream);
     if (e != hipSuccess) return cleanup(fail(ESI_ERR_HIP, hipGetErrorString(e)));

@@ -1,0 +1,92 @@
+"""Plans have the tile lists of every loop they may run from the start: calls on
+fewer shots than warmed up with, and solves whose iterations take another tiling
+than the first one, run under capture, where lists cannot be built."""
+import numpy as np
+import pytest
+import torch
+
+from tests.test_gpu_parity import _plan, _ragged_cfg
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def esi():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    from paper_2211_06300_amd import esi as e
+    e.load_library()
+    return e
+
+
+def test_graph_solve_with_separate_residual(esi):
+    # iteration 0 runs short tiles, the captured ones 32-row tiles forward
+    cfg = _ragged_cfg(nt=40)
+    plan = _plan(esi, cfg)
+    d = torch.randn(plan.data_shape(), generator=torch.Generator(device=DEV).manual_seed(3), device=DEV)
+    plan.set_cg_rfuse(False)
+    plan.set_cg_graph(True)
+    x, work = plan.new_vec(3), torch.empty((3, *plan.vec_shape(3)), device=DEV)
+    got = []
+    for _ in range(3):
+        _, rep = plan.cg_solve(d, max_iter=5, x=x, work=work)
+        got.append((x.clone(), rep["res_hist"]))
+        work[1].fill_(0.5)
+        torch.cuda.synchronize()
+    plan.set_cg_graph(False)
+    ref, rep = plan.cg_solve(d, max_iter=5)
+    for a, hist in got:
+        assert torch.equal(a, ref)
+        np.testing.assert_array_equal(hist, rep["res_hist"])
+    plan.close()
+
+
+def _line_plan(esi, ns, nt, stream=None, windows=False):
+    """ns shots on 152 x 88 cells with a line of receivers: 24-row tiles for all
+    of 60 shots (1500 workgroups of 16 rows), 8-row tiles for a few."""
+    nx, nz, nb = 152, 88, 8
+    rng = np.random.default_rng(2)
+    src = np.stack([rng.integers(40, 100, ns), rng.integers(0, 12, ns)], 1).astype(np.int32)
+    cols = np.arange(30, 130)
+    rec = np.concatenate([np.stack([cols, np.full(cols.size, 3)], 1)] * ns).astype(np.int32)
+    win = np.tile(np.array([[20, 140]], np.int32), (ns, 1)) if windows else None
+    vel = torch.from_numpy(rng.uniform(1900.0, 2700.0, (nz, nx)).astype(np.float32)).to(DEV)
+    return esi.Plan(ndim=2, nz=nz, nx=nx, nb=nb, nt=nt, dx=10.0, dt=1e-3, beta=1e-2, src=src,
+                    rec_ptr=np.arange(ns + 1) * cols.size, rec=rec, vel=vel, stream=stream, window=win)
+
+
+@pytest.mark.parametrize("windows", [False, True])
+def test_captured_range_of_shots(esi, windows):
+    ns, nt = 60, 9
+    g = torch.Generator(device=DEV).manual_seed(4)
+    w = torch.randn((ns, nt), generator=g, device=DEV)
+    plain = _line_plan(esi, ns, nt, windows=windows)
+    d = torch.randn(plain.data_shape(), generator=g, device=DEV)
+    d1 = torch.randn(plain.data_shape(7, 1), generator=g, device=DEV)
+    ref = plain.forward(w[7:8], shot0=7, nshots=1), plain.adjoint(d1, shot0=7, nshots=1)
+    assert all(float(a.abs().max()) > 0 for a in ref)
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        plan = _line_plan(esi, ns, nt, stream=stream, windows=windows)
+        plan.forward(w)            # scratch for every shot
+        plan.adjoint(d)
+        out, mu = torch.empty_like(ref[0]), torch.empty_like(ref[1])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        plan.forward(w[7:8], shot0=7, nshots=1, out=out)
+        plan.adjoint(d1, shot0=7, nshots=1, out=mu)
+    for _ in range(3):
+        out.fill_(float("nan"))
+        mu.zero_()                 # (columns off the aperture are not written)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref[0]) and torch.equal(mu, ref[1])
+        with torch.cuda.stream(stream):
+            plan.forward(w)        # eager work between replays
+        torch.cuda.synchronize()
+    plan.close()
+    plain.close()
