@@ -94,29 +94,12 @@ extern "C" esi_status_t esi_forward_noalloc(esi_plan_t plan, int32_t shot0, int3
     TileLists* L;
     ESI_TRY(existing_lists(P, tx, tz, ty, &L));
     const unsigned fl = F_GATHER | (src_kind == ESI_SRC_POINT ? F_SRC_POINT : F_SRC_DENSE);
-    // plan creation builds the lists of one two-step tiling, that of the whole
-    // plan; calls that would take another run on it (the same bits)
-    struct Keep {
-        Plan* P; int fwd; bool small;
-        explicit Keep(Plan* p) : P(p), fwd(p->tb_fwd), small(p->small_tiles) {}
-        ~Keep() { P->tb_fwd = fwd; P->small_tiles = small; }
-    } keep(P);
-    auto have = [&](int shape) {
+    const int shape = loop_shape(P, fl, false, shot0, nshots);
+    if (shape != LS_ONE) {
         TileLists* L2;
         shape_tile(P, shape, &tx, &ty, &tz);
-        return shape == LS_ONE || existing_lists(P, tx, tz, ty, &L2) == ESI_OK;
-    };
-    int shape = loop_shape(P, fl, false, shot0, nshots);
-    for (const int other : {LS_T2_32, LS_T2_16, LS_T2_8, LS_ONE}) {
-        if (have(shape)) break;
-        if (P->ndim == 2) shape = other;
+        ESI_TRY(existing_lists(P, tx, tz, ty, &L2));
     }
-    if (!have(shape)) return fail(ESI_ERR_ARG, "tile lists of this tiling were not built at plan creation");
-    if (P->ndim == 2) {
-        P->tb_fwd = shape;
-        P->small_tiles = false;
-    }
-    set_error("");
     // the scratch keeps the last call's contents: the state starts at zero
     ESI_TRY(launch_fill(P, ring, ring_floats, 0.f));
     StepArgs a = base_args(P, L, shot0, nshots);

@@ -90,3 +90,25 @@ def test_captured_range_of_shots(esi, windows):
         torch.cuda.synchronize()
     plan.close()
     plain.close()
+
+
+def test_noalloc_takes_the_loops_own_tiling(esi):
+    # a plan of 24-row tiles for all shots, called on one: 8-row tiles, two steps a launch
+    ns, nt = 60, 9
+    plan = _line_plan(esi, ns, nt)
+    w = torch.randn((ns, nt), generator=torch.Generator(device=DEV).manual_seed(4), device=DEV)
+    for n, rows in ((1, "8"), (30, "16"), (ns, "24")):
+        plan.profile(True)
+        out = plan.forward_noalloc(w[:n], nshots=n)
+        ran = plan.profile_read()
+        plan.profile(False)
+        assert {k: v["launches"] for k, v in ran.items()} == {"SRC_POINT|GATHER": 1,
+                                                             f"SRC_POINT|GATHER|TWO_STEP@56x{rows}": 4}
+        assert torch.equal(out, plan.forward(w[:n], nshots=n))
+    # a tiling that no call has built yet is refused, not replaced
+    plan.set_launch_shape(4, 4)
+    with pytest.raises(esi.EsiError, match="tile lists"):
+        plan.forward_noalloc(w[:1], nshots=1)
+    ref = plan.forward(w[:1], nshots=1)
+    assert torch.equal(plan.forward_noalloc(w[:1], nshots=1), ref)
+    plan.close()
