@@ -122,20 +122,18 @@ esi_status_t default_tilings(Plan* P) {
     return ESI_OK;
 }
 
-int max_tiles(Plan* P) {
-    int m = 0;
-    for (const TileLists* L : P->lists) m = std::max(m, L->tiles);
-    return m;
-}
-
 namespace {
 // Build the tilings of the time loops of `fflags` (forward) and `aflags`
-// (adjoint) before per-tile partials are sized by max_tiles.
-esi_status_t loop_lists(Plan* P, unsigned fflags, unsigned aflags, int shot0, int ns) {
-    TileLists* L;
-    ESI_TRY(lists_for(P, &L));
-    ESI_TRY(shape_lists(P, loop_shape(P, fflags, false, shot0, ns), &L));
-    return shape_lists(P, loop_shape(P, aflags, true, shot0, ns), &L);
+// (adjoint) and size the per-tile partials by the largest of them: by these
+// alone, so that a solve's partials do not move because other calls built finer
+// tilings since (captured iterations hold their address).
+esi_status_t loop_lists(Plan* P, unsigned fflags, unsigned aflags, int shot0, int ns, int64_t least = 0) {
+    TileLists *one, *fwd, *adj;
+    ESI_TRY(lists_for(P, &one));
+    ESI_TRY(shape_lists(P, loop_shape(P, fflags, false, shot0, ns), &fwd));
+    ESI_TRY(shape_lists(P, loop_shape(P, aflags, true, shot0, ns), &adj));
+    P->part_stride = std::max({one->tiles, fwd->tiles, adj->tiles});
+    return grow_t(&P->part, &P->part_cap, ns * std::max<int64_t>(P->part_stride, least), P->stream);
 }
 }  // namespace
 
@@ -345,8 +343,6 @@ esi_status_t do_normal(Plan* P, int shot0, int ns, const float* p, float* Ap, co
     ESI_TRY(ring_for(P, &P->ring, &P->ring_cap, ns));
     ESI_TRY(loop_lists(P, cg_fuse ? F_CG_FUSE | F_GATHER | (cg_s ? F_SCALE : 0u) : F_SRC_DENSE | F_GATHER,
                        F_INJ | F_NORMAL, shot0, ns));
-    P->part_stride = max_tiles(P);
-    ESI_TRY(grow_t(&P->part, &P->part_cap, (int64_t)ns * P->part_stride, P->stream));
     StepArgs a = base_args(P, L, shot0, ns);
     a.active = active;
     a.gat_data = P->dscr;
@@ -396,9 +392,7 @@ esi_status_t do_normal_rupd(Plan* P, int shot0, int ns, const float* p, float* p
     ESI_TRY(grow_t(&P->dscr, &P->dscr_cap, std::max<int64_t>(dl, 1), P->stream));
     ESI_TRY(ring_for(P, &P->ring, &P->ring_cap, ns));
     ESI_TRY(loop_lists(P, (first ? F_SRC_DENSE : F_CG_FUSE) | F_GATHER | F_RUPD, F_INJ | F_NORMAL | F_RUPD,
-                       shot0, ns));
-    P->part_stride = max_tiles(P);
-    ESI_TRY(grow_t(&P->part, &P->part_cap, (int64_t)ns * std::max(P->part_stride, DATA_BLOCKS), P->stream));
+                       shot0, ns, DATA_BLOCKS));
     ESI_TRY(launch_fill_d(P, P->part, (int64_t)ns * P->part_stride));
     StepArgs a = base_args(P, L, shot0, ns);
     a.active = active;
@@ -545,7 +539,7 @@ std::vector<uintptr_t> cg_graph_key(Plan* P, const CgState& c) {
     return {(uintptr_t)c.shot0, (uintptr_t)c.ns, (uintptr_t)c.max_iter,
             (uintptr_t)std::llround(c.rtol * 1e18), (uintptr_t)c.L, (uintptr_t)c.x,
             (uintptr_t)c.r, (uintptr_t)c.hist, (uintptr_t)P->ring, (uintptr_t)P->dscr,
-            (uintptr_t)P->part, (uintptr_t)((P->tb_fwd * 8 + P->tb_adj) * 2 + P->small_tiles), (uintptr_t)P->part_stride,
+            (uintptr_t)P->part, (uintptr_t)((P->tb_fwd * 8 + P->tb_adj) * 2 + P->small_tiles),
             (uintptr_t)P->w_identity, beta_bits(P->beta), (uintptr_t)P->cg_rfuse};
 }
 
@@ -660,8 +654,9 @@ esi_status_t cg_solve_impl(Plan* P, int32_t shot0, int32_t ns, const float* d_ob
     const int hs = max_iter + 1;
     ESI_TRY(grow_t(&P->cg_hist, &P->cg_hist_cap, (int64_t)ns * hs, P->stream));
     c.hist = P->cg_hist;
-    // the fused-residual iterations' data partials (sized here, outside any capture)
-    ESI_TRY(grow_t(&P->part, &P->part_cap, (int64_t)ns * DATA_BLOCKS, P->stream));
+    // tilings and partials of the iterations that may be captured (here, outside any capture)
+    const unsigned ru = P->cg_rfuse ? F_RUPD : 0u;
+    ESI_TRY(loop_lists(P, F_CG_FUSE | F_GATHER | ru, F_INJ | F_NORMAL | ru, shot0, ns, DATA_BLOCKS));
 
     std::vector<int> h_status(ns, 0);
     auto read_status = [&]() -> esi_status_t {
@@ -1100,8 +1095,6 @@ esi_status_t penalty_eval(Plan* P, int shot0, int ns, const float* q, const floa
     ESI_TRY(lists_for(P, &L));
     const unsigned pfl = F_SRC_DENSE | F_PENALTY | F_GATHER | (bg ? F_SRC_POINT : 0u);
     ESI_TRY(loop_lists(P, pfl, F_INJ, shot0, ns));
-    P->part_stride = max_tiles(P);
-    ESI_TRY(grow_t(&P->part, &P->part_cap, (int64_t)ns * P->part_stride, P->stream));
     ESI_TRY(launch_fill_d(P, P->part, (int64_t)ns * P->part_stride));
     ESI_TRY(ring_for(P, &P->ring, &P->ring_cap, ns));
     StepArgs a = base_args(P, L, shot0, ns);

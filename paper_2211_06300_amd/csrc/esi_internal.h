@@ -258,7 +258,7 @@ struct StepArgs {
     float* dout;             // dense output (adjoint mu^j, or N p)
     const float* dp;         // p for N p = mu + beta B^2 p
     double* part;            // per-(shot, tile) float64 partial sums, accumulated
-    int part_stride;         // partials per shot (the largest tile count in use)
+    int part_stride;         // partials per shot (the largest tile count of the call's loops)
     // CG fused direction update (forward): p = r + b p_old; x += a p_old
     const float* cg_r;
     const float* cg_p;       // p_old (read)
@@ -391,8 +391,6 @@ esi_status_t shape_lists(Plan* P, int shape, TileLists** L);
 // build the tilings of the plan's default loops (at plan creation)
 esi_status_t default_tilings(Plan* P);
 void shape_tile(Plan* P, int shape, int* tx, int* ty, int* tz);
-// the largest tile count of the plan's tilings (stride of per-tile partials)
-int max_tiles(Plan* P);
 StepArgs base_args(Plan* P, const TileLists* L, int shot0, int nshots);
 esi_status_t ring_for(Plan* P, float** ring, int* cap, int nshots);
 int64_t data_len(Plan* P, int shot0, int nshots);

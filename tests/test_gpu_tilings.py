@@ -112,3 +112,46 @@ def test_noalloc_takes_the_loops_own_tiling(esi):
     ref = plan.forward(w[:1], nshots=1)
     assert torch.equal(plan.forward_noalloc(w[:1], nshots=1), ref)
     plan.close()
+
+
+def test_graph_solve_after_finer_tilings(esi):
+    # other calls build tilings of more tiles than the solve's partials hold: the
+    # captured iterations' partials stay where they are
+    nx, nz, ns, nt = 801, 281, 8, 9
+    rng = np.random.default_rng(5)
+    src = np.stack([rng.integers(0, nx, ns), np.full(ns, 2)], 1).astype(np.int32)
+    rec = np.concatenate([np.stack([np.arange(0, nx, 4), np.full(201, 3)], 1)] * ns).astype(np.int32)
+    vel = torch.from_numpy(rng.uniform(1900.0, 2700.0, (nz, nx)).astype(np.float32)).to(DEV)
+    plan = esi.Plan(ndim=2, nz=nz, nx=nx, nb=20, nt=nt, dx=10.0, dt=1e-3, beta=1e-2, src=src,
+                    rec_ptr=np.arange(ns + 1) * 201, rec=rec, vel=vel)
+    g = torch.Generator(device=DEV).manual_seed(4)
+    w, d = torch.randn((ns, nt), generator=g, device=DEV), torch.randn(plan.data_shape(), generator=g, device=DEV)
+    x, work = plan.new_vec(ns), torch.empty((3, *plan.vec_shape(ns)), device=DEV)
+    plan.set_cg_graph(True)
+    for other in (lambda: plan.forward(w[:1], nshots=1), lambda: plan.set_launch_shape(3, 3),
+                  lambda: plan.normal_apply(x, out=work[2]), lambda: plan.set_time_block(2)):
+        plan.cg_solve(d, max_iter=4, x=x, work=work)
+        other()
+        torch.cuda.synchronize()
+    plan.set_cg_graph(False)
+    ref, _ = plan.cg_solve(d, max_iter=4)
+    plan.set_cg_graph(True)
+    for _ in range(2):
+        plan.cg_solve(d, max_iter=4, x=x, work=work)
+        assert torch.equal(x, ref)
+    plan.close()
+
+
+@pytest.mark.parametrize("shape", [1, 2, 3, 4])
+def test_graph_solve_with_separate_residual_on_set_shapes(esi, shape):
+    cfg = _ragged_cfg(nt=30)
+    plan = _plan(esi, cfg)
+    d = torch.randn(plan.data_shape(), generator=torch.Generator(device=DEV).manual_seed(3), device=DEV)
+    plan.set_cg_rfuse(False)
+    plan.set_launch_shape(shape, shape)
+    plan.set_cg_graph(True)
+    got = [plan.cg_solve(d, max_iter=4)[0] for _ in range(2)]
+    plan.set_cg_graph(False)
+    ref, _ = plan.cg_solve(d, max_iter=4)
+    assert all(torch.equal(x, ref) for x in got)
+    plan.close()
