@@ -214,7 +214,8 @@ void build_lists(const Plan* P, bool grown, TileLists* L, HostLists& h) {
         *cell = nd == 3 ? ((lz * ty + ly) * tx + lx) : (lz * tx + lx);
     };
     const int T = L->tiles, S = P->nshots;
-    h.inj_ptr.resize((size_t)S * (T + 1));
+    const bool inj = nd == 3 || !grown;   // two-step 2D launches inject by the grown tile alone
+    if (inj) h.inj_ptr.resize((size_t)S * (T + 1));
     h.gat_ptr.resize((size_t)S * (T + 1));
     h.src_tile.resize(S);
     h.src_cell.resize(S);
@@ -252,25 +253,25 @@ void build_lists(const Plan* P, bool grown, TileLists* L, HostLists& h) {
             e.push_back(q);
         }
         by_tile();
-        int32_t* ip = &h.inj_ptr[(size_t)s * (T + 1)];
+        int32_t* ip = inj ? &h.inj_ptr[(size_t)s * (T + 1)] : nullptr;
         int32_t* gp = &h.gat_ptr[(size_t)s * (T + 1)];
         size_t k = 0;
         for (int t = 0; t < T; ++t) {
-            ip[t] = (int32_t)h.inj_cell.size();
+            if (inj) ip[t] = (int32_t)h.inj_cell.size();
             gp[t] = (int32_t)h.gat_cell.size();
             while (k < sorted.size() && sorted[k].tile == t) {
                 // one unique cell, all its receivers in increasing id order
                 const int32_t cell = sorted[k].cell;
-                h.inj_cell.push_back(cell);
+                if (inj) h.inj_cell.push_back(cell);
                 for (; k < sorted.size() && sorted[k].tile == t && sorted[k].cell == cell; ++k) {
-                    h.inj_rid.push_back(sorted[k].rid);
+                    if (inj) h.inj_rid.push_back(sorted[k].rid);
                     h.gat_cell.push_back(cell);
                     h.gat_rid.push_back(sorted[k].rid);
                 }
-                h.inj_rptr.push_back((int32_t)h.inj_rid.size());
+                if (inj) h.inj_rptr.push_back((int32_t)h.inj_rid.size());
             }
         }
-        ip[T] = (int32_t)h.inj_cell.size();
+        if (inj) ip[T] = (int32_t)h.inj_cell.size();
         gp[T] = (int32_t)h.gat_cell.size();
         if (grown) {
             // an entry for every tile region that holds a receiver (whose padded
@@ -316,11 +317,8 @@ void build_lists(const Plan* P, bool grown, TileLists* L, HostLists& h) {
         L->work_ptr.assign(P->nshots + 1, 0);
         for (int s = 0; s < P->nshots; ++s) {
             const int lo = P->h_win[2 * s], hi = P->h_win[2 * s + 1] + 2 * P->nb;   // padded [lo, hi)
-            for (int t = 0; t < L->tiles; ++t) {
-                const int txi = t % L->tiles_x;
-                const int a0 = txi * tx, a1 = a0 + tx;
-                if (a0 < hi && a1 > lo) h.work.push_back(s * L->tiles + t);
-            }
+            for (int row = 0; row < L->tiles; row += L->tiles_x)
+                for (int txi = lo / tx; txi * tx < hi; ++txi) h.work.push_back(s * L->tiles + row + txi);
             L->work_ptr[s + 1] = (int64_t)h.work.size();
         }
     }
