@@ -522,10 +522,10 @@ esi_status_t esi_plan_set_time_block(esi_plan_t plan, int32_t steps);
  * Every shape gives the same wavefield, data, dense outputs and gradients bit
  * for bit; float64 dot products sum their per-tile partials over a different
  * tiling, so CG results agree to rounding.  Time-loop variants the shapes of
- * 24 and 40 rows do not cover run on 32-row tiles.  A 2D plan whose two-step
- * shape is its default or the autotuner's takes shorter tiles (24, 16 or 8
- * rows) for loops too small to fill the GPU; a shape set by
- * esi_plan_set_launch_shape is taken as it is.
+ * 24 and 40 rows do not cover run on 32-row tiles.  A 2D plan whose shape is
+ * the default two steps takes shorter tiles (24, 16 or 8 rows) for loops too
+ * small to fill the GPU; a shape set by esi_plan_set_launch_shape is taken as
+ * it is.
  */
 enum { ESI_LAUNCH_ONE_STEP = 1, ESI_LAUNCH_TWO_STEP_32 = 2, ESI_LAUNCH_TWO_STEP_24 = 3,
        ESI_LAUNCH_TWO_STEP_40 = 4 };
@@ -538,7 +538,11 @@ esi_status_t esi_plan_set_launch_shape(esi_plan_t plan, int32_t forward, int32_t
  * Autotuner of the launch shape.  For the plan's grid and a batch of nshots
  * shots it times every candidate shape (2D: the four above; 3D: 1 and 2), after a
  * warm-up run of each, with the plan's hipEvent profiling, and keeps the
- * fastest for forward-type and for adjoint-type loops separately.
+ * fastest for forward-type and for adjoint-type loops separately.  In 2D the
+ * choice ESI_LAUNCH_TWO_STEP_32 is the default two steps, timed as the plan then
+ * runs them: on shorter tiles if the loop is small enough for those.  The other
+ * choices run as timed for nshots shots and more; calls on fewer shots take
+ * shorter tiles where the default would.
  *   p, Ap device [nshots][nt][phys] (contents irrelevant; Ap is overwritten):
  *     the candidates are timed on one application of the normal operator;
  *   p = Ap = NULL: on a point-source forward pass over the first min(nt, 64)

@@ -77,7 +77,7 @@ static int64_t launch_tiles(Plan* P, int shape, int shot0, int nshots) {
 int loop_shape(Plan* P, unsigned flags, bool adjoint, int shot0, int nshots) {
     int want = adjoint ? P->tb_adj : P->tb_fwd;
     if (P->ndim == 2) {
-        if (want != LS_ONE && P->small_tiles) {
+        if (want != LS_ONE && (nshots < P->short_below || (want == LS_T2_32 && P->short_below > 0))) {
             for (const auto& t : SMALL)
                 if (launch_tiles(P, t.shape, shot0, nshots) <= t.most) { want = t.shape; break; }
         }
@@ -539,7 +539,7 @@ std::vector<uintptr_t> cg_graph_key(Plan* P, const CgState& c) {
     return {(uintptr_t)c.shot0, (uintptr_t)c.ns, (uintptr_t)c.max_iter,
             (uintptr_t)std::llround(c.rtol * 1e18), (uintptr_t)c.L, (uintptr_t)c.x,
             (uintptr_t)c.r, (uintptr_t)c.hist, (uintptr_t)P->ring, (uintptr_t)P->dscr,
-            (uintptr_t)P->part, (uintptr_t)((P->tb_fwd * 8 + P->tb_adj) * 2 + P->small_tiles),
+            (uintptr_t)P->part, (uintptr_t)(P->tb_fwd * 8 + P->tb_adj), (uintptr_t)P->short_below,
             (uintptr_t)P->w_identity, beta_bits(P->beta), (uintptr_t)P->cg_rfuse};
 }
 
@@ -1208,7 +1208,7 @@ extern "C" esi_status_t esi_plan_set_time_block(esi_plan_t plan, int32_t steps) 
     if (!plan) return fail(ESI_ERR_ARG, "null plan");
     if (steps != 1 && steps != 2) return fail(ESI_ERR_ARG, "time block must be 1 or 2");
     ((Plan*)plan)->tb_fwd = ((Plan*)plan)->tb_adj = steps == 1 ? LS_ONE : LS_T2_32;
-    ((Plan*)plan)->small_tiles = true;
+    ((Plan*)plan)->short_below = INT_MAX;
     return ESI_OK;
 }
 
@@ -1293,7 +1293,7 @@ extern "C" esi_status_t esi_plan_autotune(esi_plan_t plan, int32_t shot0, int32_
             if (e.key == key) {
                 P->tb_fwd = e.fwd;
                 P->tb_adj = e.adj;
-                P->small_tiles = true;
+                P->short_below = ns;
                 P->tune_rows = e.rows;
                 if (choice) { choice[0] = e.fwd; choice[1] = e.adj; }
                 return ESI_OK;
@@ -1318,8 +1318,7 @@ extern "C" esi_status_t esi_plan_autotune(esi_plan_t plan, int32_t shot0, int32_
     pend.swap(P->prof_pending);
     tot.swap(P->prof_tot);
     const int tf0 = P->tb_fwd, ta0 = P->tb_adj;
-    const bool small0 = P->small_tiles;
-    P->small_tiles = false;   // each candidate as it is
+    const int short0 = P->short_below;
     double best_f = 1e300, best_a = 1e300;
     int sf = LS_T2_32, sa = LS_T2_32;
     esi_status_t st = ESI_OK;
@@ -1328,6 +1327,7 @@ extern "C" esi_status_t esi_plan_autotune(esi_plan_t plan, int32_t shot0, int32_
                                                 : std::vector<int>{LS_ONE, LS_T2_32};
     for (int shape : cands) {
         P->tb_fwd = P->tb_adj = shape;
+        P->short_below = shape == LS_T2_32 ? INT_MAX : 0;   // what each choice would run
         P->prof_on = false;   // first run builds the tile lists of this shape and warms up
         st = tune_run(P, shot0, ns, p, Ap, probe, nprobe, L);
         if (st != ESI_OK) break;
@@ -1350,12 +1350,12 @@ extern "C" esi_status_t esi_plan_autotune(esi_plan_t plan, int32_t shot0, int32_
     if (st != ESI_OK) {
         P->tb_fwd = tf0;
         P->tb_adj = ta0;
-        P->small_tiles = small0;
+        P->short_below = short0;
         return st;
     }
     P->tb_fwd = sf;
     P->tb_adj = sa;
-    P->small_tiles = true;
+    P->short_below = ns;
     P->tune_rows = rows;
     g_tune_cache.push_back({key, sf, sa, rows});
     if (choice) { choice[0] = sf; choice[1] = sa; }
@@ -1387,7 +1387,7 @@ extern "C" esi_status_t esi_plan_set_launch_shape(esi_plan_t plan, int32_t forwa
         return fail(ESI_ERR_ARG, "3D plans run shape 1 (one step per launch) or 2 (two steps)");
     P->tb_fwd = forward;
     P->tb_adj = adjoint;
-    P->small_tiles = false;
+    P->short_below = 0;
     return ESI_OK;
 }
 

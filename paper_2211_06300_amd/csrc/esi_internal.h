@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <climits>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -175,7 +176,10 @@ struct Plan {
 
     std::vector<TileLists*> lists;       // one per tile shape used
     int tb_fwd = LS_T2_32, tb_adj = LS_T2_32;   // launch shape of forward / adjoint loops (2D)
-    bool small_tiles = true;             // two-step loops too small for the GPU take shorter tiles (2D)
+    // two-step loops too small for the GPU take shorter tiles (2D): of LS_T2_32
+    // unless 0 (a shape set by hand), of other shapes (the autotuner's choice for
+    // as many shots) over fewer shots than this
+    int short_below = INT_MAX;
     // the autotuner's last candidate table: shape, forward ms, adjoint ms
     struct TuneRow { int shape; double fwd_ms, adj_ms; };
     std::vector<TuneRow> tune_rows;

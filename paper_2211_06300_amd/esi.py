@@ -20,8 +20,8 @@ GRAD_PENALTY, GRAD_ADJOINT, GRAD_SEED, GRAD_SEED_REUSE = 0, 1, 2, 3
 WEIGHT_ANNIHILATOR, WEIGHT_IDENTITY = 0, 1
 BETA_FIXED, BETA_DISCREPANCY = 0, 1
 LAUNCH_ONE_STEP, LAUNCH_TWO_STEP_32, LAUNCH_TWO_STEP_24, LAUNCH_TWO_STEP_40 = 1, 2, 3, 4
-LAUNCH_NAMES = {1: "1 step, 64x32 tiles", 2: "2 steps, 56x32 tiles", 3: "2 steps, 56x24 tiles",
-                4: "2 steps, 56x40 tiles"}
+LAUNCH_NAMES = {1: "1 step, 64x32 tiles", 2: "2 steps, 56x32 tiles (shorter in small loops)",
+                3: "2 steps, 56x24 tiles", 4: "2 steps, 56x40 tiles"}
 LAUNCH_TILES = {1: "64x32", 2: "56x32", 3: "56x24", 4: "56x40", 5: "56x16", 6: "56x8"}
 LAUNCH_NAMES_3D = {1: "1 step, 64x16 columns, 3- to 8-plane chunks", 2: "2 steps, 56x24 columns, 64-plane chunks"}
 INNER_CG, INNER_FCG_SCALE, INNER_DATASPACE = 0, 1, 2

@@ -155,3 +155,35 @@ def test_graph_solve_with_separate_residual_on_set_shapes(esi, shape):
     ref, _ = plan.cg_solve(d, max_iter=4)
     assert all(torch.equal(x, ref) for x in got)
     plan.close()
+
+
+@pytest.mark.parametrize("ns", [1, 30, 60, 130])
+def test_autotuned_loops_run_what_was_timed(esi, ns):
+    # the tiles that the reported choice stands for: its own, or for the default two
+    # steps those of an untuned plan (8, 16, 24 and 32 rows here)
+    nt = 9
+    plan, plain = _line_plan(esi, ns, nt), _line_plan(esi, ns, nt)
+    rows = {1: 6, 30: 5, 60: 3, 130: 2}[ns]
+    p, Ap = plan.new_vec(ns), plan.new_vec(ns)
+
+    def shapes(pl, n=ns):
+        pl.profile(True)
+        pl.normal_apply(p[:n], out=Ap[:n], nshots=n)
+        ran = [v["flags"] for v in pl.profile_read().values()]
+        pl.profile(False)
+        return [max((f >> 16) & 7 for f in ran if bool(f & 8) == adj) or 1 for adj in (False, True)]
+
+    assert shapes(plain) == [rows, rows]
+    for probe in (False, True):
+        ch = plan.autotune(p=None if probe else p, Ap=None if probe else Ap, probe=probe, force=True)
+        assert shapes(plan) == [rows if c == 2 else c for c in ch]
+        # the cached choice as well
+        plan.set_time_block(2)
+        assert plan.autotune(p=None if probe else p, Ap=None if probe else Ap, probe=probe) == ch
+        assert shapes(plan) == [rows if c == 2 else c for c in ch]
+        if ns > 1:   # a call on fewer shots takes shorter tiles, unless one step a launch was chosen
+            assert shapes(plan, 1) == [1 if c == 1 else 6 for c in ch]
+        plan.set_launch_shape(*ch)
+        assert shapes(plan) == list(ch)
+    plan.close()
+    plain.close()
