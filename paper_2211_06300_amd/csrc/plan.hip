@@ -478,7 +478,13 @@ extern "C" esi_status_t esi_plan_create(esi_plan_t* plan, const esi_grid_t* g, c
     lap_weights(w);
     for (int k = 0; k < 5; ++k) P->lap_w[k] = (float)w[k];
     P->nshots = geo->nshots;
-    if (nd == 3) P->chunk3d = step3d_chunk(P->nxp, P->nyp, P->nzp, (int64_t)P->XS * P->YS, P->nshots);
+    if (nd == 3) {
+        P->chunk3d = step3d_chunk(P->nxp, P->nyp, P->nzp, (int64_t)P->XS * P->YS, P->nshots);
+        if (P->chunk3d == 0) {
+            delete P;
+            return fail(ESI_ERR_SHAPE, "a horizontal plane of the 3D grid is too large (2 GiB for ten planes)");
+        }
+    }
     P->h_src.assign(geo->src, geo->src + (size_t)geo->nshots * nd);
     P->h_rec_ptr.assign(geo->rec_ptr, geo->rec_ptr + geo->nshots + 1);
     if (geo->window) P->h_win.assign(geo->window, geo->window + 2 * (size_t)geo->nshots);

@@ -512,16 +512,22 @@ esi_status_t launch_step3d(Plan* P, unsigned flags, const StepArgs& a) {
 int step3d_chunk(int nxp, int nyp, int nzp, int64_t plane, int nshots) {
     constexpr int64_t CUS = 256;
     const int64_t columns = (int64_t)nshots * ((nxp + TX - 1) / TX) * ((nyp + TY - 1) / TY);
-    int best = 4;
+    // a chunk with its halo must not pass 2 GiB, which buffers cannot: shorter
+    // chunks where 3 planes would, none (0) where one would (planes of 53 million floats)
+    auto fits = [&](int ch) { return (ch + 2 * HALO + 1) * 4 * plane < (int64_t)1 << 31; };
+    int best = fits(2) ? 2 : fits(1) ? 1 : 0;
     int64_t least = INT64_MAX;
-    for (int ch = 3; ch <= 8; ++ch) {
-        // (a chunk with its halo must not pass 2 GiB, which buffers cannot)
-        if ((ch + 2 * HALO + 1) * 4 * plane >= (int64_t)1 << 31) break;
+    for (int ch = 3; ch <= 8 && fits(ch); ++ch) {
         const int64_t rounds = (columns * ((nzp + ch - 1) / ch) + CUS - 1) / CUS;
         const int64_t cost = rounds * (10 * ch + 7) * (rounds == 1 ? 117 : rounds == 2 ? 97 : 100);
         if (cost <= least) { least = cost; best = ch; }
     }
     return best;
+}
+
+// (host only, for tests)
+extern "C" int esi_host_step3d_chunk(int nxp, int nyp, int nzp, int64_t plane, int nshots) {
+    return step3d_chunk(nxp, nyp, nzp, plane, nshots);
 }
 
 void step3d_tile_shape(int* tx, int* ty, int* tz) { *tx = TX; *ty = TY; *tz = TZC; }
