@@ -1441,6 +1441,11 @@ esi_status_t conv3(const Ctx& c, const Tv& X, int K, int layer, const Tv& Y, int
     if constexpr (EPI == E_OUT || IN) {
         if (K != 16 || M != 16) return fail(ESI_ERR_SHAPE, "fused first and last convolutions have 16 channels");
         launch_conv3<1, 16, EPI, true, IN>(c, A, M);
+    } else if constexpr (EPI == E_POOL) {
+        if (K != M || M > 64) return fail(ESI_ERR_SHAPE, "pooled convolutions have 16, 32 or 64 channels");
+        if (M == 16) launch_conv3<1, 16, EPI, true, false>(c, A, M);
+        else if (M == 32) launch_conv3<2, 32, EPI, true, false>(c, A, M);
+        else launch_conv3<4, 32, EPI, false, false>(c, A, M);
     } else if (ck == 16) {
         if (M == 16) launch_conv3<1, 16, EPI, true, false>(c, A, M);
         else launch_conv3<2, 16, EPI, true, false>(c, A, M);
@@ -1450,8 +1455,8 @@ esi_status_t conv3(const Ctx& c, const Tv& X, int K, int layer, const Tv& Y, int
         if (K == 32) launch_conv3<2, 32, EPI, true, false>(c, A, M);
         else launch_conv3<2, 32, EPI, false, false>(c, A, M);
     } else {
-        if (K == 32) launch_conv3<1, 32, EPI, true, false>(c, A, M);
-        else launch_conv3<1, 32, EPI, false, false>(c, A, M);
+        if (K != 32) return fail(ESI_ERR_SHAPE, "16 outputs are those of at most 32 channels");
+        launch_conv3<1, 32, EPI, true, false>(c, A, M);
     }
     ESI_HIP_TRY(hipGetLastError());
     return ESI_OK;
