@@ -242,8 +242,38 @@ void build_lists(const Plan* P, bool grown, TileLists* L, HostLists& h) {
                 std::sort(sorted.begin() + i, sorted.begin() + j, less);
         }
     };
+    // a shot with the receivers of the one before it (a fixed spread) repeats that
+    // one's lists: [of, to) of a list, moved by the list's growth
+    auto repeat = [](std::vector<int32_t>& v, size_t of, size_t to, int32_t add) {
+        for (size_t i = of; i < to; ++i) v.push_back(v[i] + add);
+    };
+    struct Mark { size_t cell, rid, gat, cell2, rid2; } was = {}, now = {};
     for (int s = 0; s < S; ++s) {
         const int64_t r0 = P->h_rec_ptr[s], r1 = P->h_rec_ptr[s + 1];
+        const int32_t* ps = &P->h_src[(size_t)s * nd];
+        locate(ps[0] + P->nb, ps[1] + P->nb, nd == 3 ? ps[2] + P->nb : 0, &h.src_tile[s], &h.src_cell[s]);
+        was = now;
+        now = {h.inj_cell.size(), h.inj_rid.size(), h.gat_cell.size(), h.inj2_cell.size(), h.inj2_rid.size()};
+        if (s > 0 && r1 - r0 == r0 - P->h_rec_ptr[s - 1] &&
+            std::equal(P->h_rec.begin() + r0 * nd, P->h_rec.begin() + r1 * nd, P->h_rec.begin() + P->h_rec_ptr[s - 1] * nd)) {
+            repeat(h.inj_cell, was.cell, now.cell, 0);
+            repeat(h.inj_rptr, was.cell + 1, inj ? now.cell + 1 : 0, (int32_t)(now.rid - was.rid));
+            repeat(h.inj_rid, was.rid, now.rid, 0);
+            repeat(h.gat_cell, was.gat, now.gat, 0);
+            repeat(h.gat_rid, was.gat, now.gat, 0);
+            repeat(h.inj2_cell, was.cell2, now.cell2, 0);
+            repeat(h.inj2_first, was.cell2, now.cell2, 0);
+            repeat(h.inj2_rptr, was.cell2 + 1, grown ? now.cell2 + 1 : 0, (int32_t)(now.rid2 - was.rid2));
+            repeat(h.inj2_rid, was.rid2, now.rid2, 0);
+            auto ptrs = [&](std::vector<int32_t>& v, size_t grown_by) {
+                int32_t* p = &v[(size_t)s * (T + 1)];
+                for (int t = 0; t <= T; ++t) p[t] = p[t - (T + 1)] + (int32_t)grown_by;
+            };
+            if (inj) ptrs(h.inj_ptr, now.cell - was.cell);
+            ptrs(h.gat_ptr, now.gat - was.gat);
+            if (grown) ptrs(h.inj2_ptr, now.cell2 - was.cell2);
+            continue;
+        }
         e.clear();
         for (int64_t r = r0; r < r1; ++r) {
             const int32_t* pr = &P->h_rec[r * nd];
@@ -309,8 +339,6 @@ void build_lists(const Plan* P, bool grown, TileLists* L, HostLists& h) {
             }
             ip2[T] = (int32_t)h.inj2_cell.size();
         }
-        const int32_t* ps = &P->h_src[(size_t)s * nd];
-        locate(ps[0] + P->nb, ps[1] + P->nb, nd == 3 ? ps[2] + P->nb : 0, &h.src_tile[s], &h.src_cell[s]);
     }
     if (!P->h_win.empty()) {
         // the (shot, tile) items whose tile columns meet the shot's window plus layer

@@ -187,3 +187,40 @@ def test_autotuned_loops_run_what_was_timed(esi, ns):
         assert shapes(plan) == list(ch)
     plan.close()
     plain.close()
+
+
+@pytest.mark.parametrize("ndim", [2, 3])
+@pytest.mark.parametrize("steps", [1, 2])
+def test_fixed_spread_equals_single_shots(esi, ndim, steps):
+    # shots that repeat the receivers of the one before them, and shots that do not
+    rng = np.random.default_rng(9)
+    nx, nz, ny, nb, nt, ns = (70, 37, 1, 8, 20, 6) if ndim == 2 else (40, 20, 19, 4, 10, 6)
+    dims = [nx, nz] + [ny] * (ndim - 2)
+    spot = lambda n: np.stack([rng.integers(0, k, n) for k in dims], 1).astype(np.int32)
+    a, b = spot(50), spot(9)
+    a[11], a[12] = a[10], a[10]
+    recs = [a, a, b, a, a, a[:0]]
+    src = spot(ns)
+    src[:, 1] = 2
+    vel = torch.from_numpy(rng.uniform(1900.0, 2700.0, (nz, ny, nx) if ndim == 3 else (nz, nx)).astype(np.float32)).to(DEV)
+
+    def plan_of(shots):
+        pl = esi.Plan(ndim=ndim, nz=nz, ny=ny, nx=nx, nb=nb, nt=nt, dx=10.0, dt=1e-3, beta=1e-2, src=src[shots],
+                      rec_ptr=np.concatenate([[0], np.cumsum([len(recs[s]) for s in shots])]),
+                      rec=np.concatenate([recs[s] for s in shots]), vel=vel)
+        pl.set_time_block(steps)
+        return pl
+
+    w = torch.randn((ns, nt), generator=torch.Generator(device=DEV).manual_seed(1), device=DEV)
+    plan = plan_of(list(range(ns)))
+    d = plan.forward(w)
+    mu = plan.adjoint(d)
+    at = 0
+    for s in range(ns):
+        one, n = plan_of([s]), nt * len(recs[s])
+        assert torch.equal(one.forward(w[s:s + 1]), d[at:at + n]), s
+        assert torch.equal(one.adjoint(d[at:at + n].clone()), mu[s:s + 1]), s
+        at += n
+        one.close()
+    assert float(d.abs().max()) > 0 and float(mu.abs().max()) > 0
+    plan.close()
