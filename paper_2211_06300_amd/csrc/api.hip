@@ -57,15 +57,16 @@ static int64_t launch_tiles(Plan* P, int tx, int tz, int shot0, int nshots) {
 // take the shortest tiles that keep the launch within about four workgroups per
 // CU (three of 8 rows, whose rings cost most).  Microseconds per launch, CG
 // (forward pass and adjoint, averaged) on grids of 10 m cells, 32 / 24 / 16 / 8 rows:
-//   201 x 201, 1 shot:    9.56 /  8.57 /  7.09 /  6.25  (8 rows: 155 workgroups)
-//   401 x 201, 3 shots:  10.94 / 10.21 /  9.18 /  8.69  (8 rows: 744)
-//   401 x 201, 4 shots:  11.48 / 10.78 /  9.59 /  9.73  (8 rows: 992)
-//   401 x 201, 8 shots:  14.15 / 13.83 / 13.16 / 14.78  (16 rows: 1024)
-//   801 x 401, 2 shots:  14.10 / 13.77 / 12.99 / 14.27  (16 rows: 896)
-//   801 x 401, 3 shots:  17.77 / 17.41 / 17.21 / 18.61  (24 rows: 912; 16 rows,
-//                        1344, take 9.87 modelling against 9.18)
-//   801 x 401, 4 shots:  20.47 / 20.43 / 20.24 / 22.75  (24 rows: 1216)
-// and 8 shots of 801 x 401 run fastest on 32 rows.
+//   201 x 201, 1 shot:    9.14 /  8.08 /  6.79 /  5.88  (8 rows: 155 workgroups)
+//   401 x 201, 3 shots:  10.24 /  9.52 /  8.39 /  8.04  (8 rows: 744)
+//   401 x 201, 4 shots:  10.78 / 10.17 /  8.83 /  9.04  (8 rows: 992)
+//   401 x 201, 8 shots:  13.27 / 13.08 / 12.39 / 13.92  (16 rows: 1024)
+//   801 x 401, 2 shots:  13.10 / 12.86 / 12.02 / 13.37  (16 rows: 896)
+//   801 x 401, 3 shots:  16.50 / 16.34 / 16.19 / 17.40  (24 rows: 912; 16 rows,
+//                        1344, take 9.52 modelling against 9.06)
+//   801 x 401, 4 shots:  19.41 / 19.29 / 19.31 / 21.61  (24 rows: 1216)
+// and 8 shots of 801 x 401 run fastest on 32 rows.  Shapes set by hand, and the
+// autotuner's for as many shots as it timed, are taken as they are (short_below).
 static constexpr struct { int shape, most; } SMALL[] = {{LS_T2_8, 768}, {LS_T2_16, 1024}, {LS_T2_24, 1280}};
 
 static int64_t launch_tiles(Plan* P, int shape, int shot0, int nshots) {

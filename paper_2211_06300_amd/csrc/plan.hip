@@ -486,8 +486,8 @@ extern "C" esi_status_t esi_plan_create(esi_plan_t* plan, const esi_grid_t* g, c
         // round_up(nxp, 256) plus the ghost frame, and 56-wide two-step tiles
         // whose staged region reaches 72 columns past the last tile origin
         P->XS = round_up(std::max(round_up(P->nxp, 256) + 2 * GH, P->nxp + 80), 32);
-        // rows: whole tiles of every height in use (64-row one-step tiles,
-        // two-step tiles of 24, 32 or 40 rows) plus the ghost frame
+        // rows: whole tiles of every height in use (one-step tiles of 32 rows,
+        // two-step tiles of 8, 16, 24, 32 or 40 rows) plus the ghost frame
         P->ZS = std::max({round_up(P->nzp, 64), round_up(P->nzp, 24), round_up(P->nzp, 40)}) + 2 * GH;
         P->YS = 1;
     } else {

@@ -141,8 +141,6 @@ struct StepPtrs {
     float al;            // the shot's CG step length (RUPD with NORMAL)
 };
 
-// Shot and tile of workgroup L: from the batch's work list when shots have
-// apertures, else tile fastest within a shot.
 // n / d and the remainder, n < 2^31, with m = (2^32 - 1) / d: the estimate is at
 // most one short.  A few scalar instructions in place of the compiler's division
 // (a reciprocal and its corrections in the vector unit, before the first load):
@@ -155,6 +153,8 @@ __device__ __forceinline__ int div_by(int n, int d, uint32_t m, int* rem) {
     return q;
 }
 
+// Shot and tile of workgroup L: from the batch's work list when shots have
+// apertures, else tile fastest within a shot.
 __device__ __forceinline__ void work_item(const StepArgs& a, int L, int tiles, int* s, int* t) {
     *s = div_by(a.work ? a.work[L] : L, tiles, a.tiles_m, t) - (a.work ? a.shot0 : 0);
 }
@@ -545,14 +545,15 @@ __global__ __launch_bounds__(256, ESI_MINW) void k_step2d(const StepArgs a) {
 //    line of its arguments at once, reads all the uniform values of its shot and
 //    tile in one batch and, on short tiles, has the fields on their way before it
 //    waits for them (T2Head).
-// Interior tiles of the modelling variant issue 725 vector and 427 scalar
-// instructions.  Microseconds per launch on 32-row tiles, before and now:
-// modelling 32 shots of 801 x 401, 60.1 and 41.4 (its state moved at 5.6 TB/s);
-// CG on 8 of them (forward pass, adjoint), 42.7 and 33.6, now 40.4 and 30.4; FWI
-// windows, 32 shots of 1601 x 601 (modelling, segment recompute, correlating
-// adjoint), 65.3, 95.8 and 110.4, now 51.1, 83.8 and 89.0; one shot of 201 x 201
-// (modelling, CG forward and adjoint averaged), 8.7 and 16.3, now 6.4 and 9.6 (on
-// 8-row tiles 5.6 and 6.9 before the batched reads, now 4.1 and 6.2).
+// A wave of the modelling variant issues 699 vector and 358 scalar instructions
+// (81 % of the vector issue slots; 246 MB a launch by counters, 6.1 TB/s).
+// Microseconds per launch on 32-row tiles, before and now:
+// modelling 32 shots of 801 x 401, 60.1 and 40.1; CG on 8 of them (forward pass,
+// adjoint), 42.7 and 33.6, now 38.9 and 29.3; FWI windows, 32 shots of 1601 x 601
+// (modelling, segment recompute, correlating adjoint), 65.3, 95.8 and 110.4, now
+// 48.9, 61.6 and 81.1 (store past the caches); one shot of 201 x 201 (modelling,
+// CG forward and adjoint averaged), 8.7 and 16.3, now 6.3 and 9.1 (on the 8-row
+// tiles it takes, 5.6 and 6.9 before the batched reads, now 4.0 and 5.8).
 constexpr int T2W = 56;                           // output tile width
 constexpr int A_W = T2W + 2 * HALO;               // 64: first-step region width
 constexpr int U0W = T2W + 4 * HALO;               // 72

@@ -21,9 +21,9 @@
 // so that the windows move once per UZ planes.  Microseconds per launch, before
 // (addresses and masks per plane, receivers counted one by one, 32-plane
 // chunks) and now, modelling / segment recompute / adjoint / correlating
-// adjoint: one shot of 64^3, 32.4 / 35.6 / 52.4 / 60.8, now 8.2 / 9.1 / 9.4 / 10.7;
+// adjoint: one shot of 64^3, 32.4 / 35.6 / 52.4 / 60.8, now 8.5 / 8.9 / 9.8 / 11.1;
 // 4 shots of 256^3, 560 / 662 / 591 / 888, now 509 / 589 / 530 / 755.  The latter
-// moves 2.76 GB a modelling launch by counters (20 B a cell are 2.07), 5.4 TB/s:
+// moves 2.79 GB a modelling launch by counters (20 B a cell are 2.07), 5.5 TB/s:
 // halo planes that neither L2 nor a neighbour still holds.  Non-temporal loads
 // or stores of the streams without reuse were slower by 7 to 27 % (they pass
 // the memory-side cache by), loads two planes ahead by nothing.

@@ -91,10 +91,10 @@ static uint16_t f2bf_host(float f) {
 // fixed but for the image's edges and a scalar one per row, and outputs are
 // rounded two at a time by the instruction.  Stores are 16 bytes a lane (8 bytes
 // left four partial writes in a line: 467 us for the pass below against 428).
-// The layers of 16 channels are bound by memory (38 us for 189 MB, 5 TB/s), the
+// The layers of 16 channels are bound by memory (37 us for 223 MB by counters, 6 TB/s), the
 // others by the last wave of tiles and what it leaves exposed: 64 channels on 8
 // images of 102 x 202 have 416 tiles for 256 CUs (28 us, of which 8 MFMAs).
-// The forward pass on 8 images of 408 x 808 takes 428 us; with 1369 vector
+// The forward pass on 8 images of 408 x 808 takes 428 to 441 us; with 1369 vector
 // instructions for 144 MFMAs (now 513), pooling and first and last layer as
 // kernels of their own, it took 652.
 constexpr int frag_ck(int K) { return K % 32 == 0 ? 32 : 16; }
@@ -679,7 +679,7 @@ __device__ __forceinline__ void wgrad_out(const f4 (&acc)[TAPS][CB][IB], const f
 // One wave per 16 x 16 channels fetching every operand element by itself (two
 // bytes a load) and a thread per output adding up to 1664 chunks took 183 and 143
 // us a layer on average on 16 images of 208 x 408.  Now 22 us at 16 x 16 channels
-// (87 MB read, 4 TB/s), 27 us at 32 x 32 and above (35 with an index, a branch and
+// (87 MB once, 107 moved by counters, 4.9 TB/s), 27 us at 32 x 32 and above (35 with an index, a branch and
 // a wait per staged piece), 6 us for the sum; the whole training gradient went
 // from 6.58 to 1.55 ms, and with the convolutions' new kernel to 1.24 ms.
 template <int CB, int IB, int ROWS>
